@@ -57,6 +57,8 @@ struct sop_ctx {
     long long energy_every = 0;
     int batch_wg_req = 0, batch_wg = 1024, batch_steps = 100;
     long long max_len = 0;           // longest trajectory
+    int max_bonds = 0, max_natives = 0;  // of a residue
+    double min_r0 = 0.0;             // shortest bonded or native reference length (huge if none)
     std::vector<int> pack_off;       // batched: first slot of each pack
     std::vector<int> slot_res;       // batched: residue of each slot
     hipGraphExec_t bgraphs[2][2] = {};  // batched launch graphs by layer parity, records
@@ -149,15 +151,17 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
     const size_t n = (size_t)c->n_res;
     const size_t T = (size_t)c->n_traj;
     const bool plain = c->schedule == SOP_SCHEDULE_PLAIN;
-    // padded for the largest tile so that any tile size fits
-    const size_t n_pad = ((n + 255) / 256) * 256;
-    const size_t list16_elems = plain ? n_pad * (size_t)c->cap : n * (size_t)c->cap;
     // per-tile blocks, for the largest need over the tile sizes
-    size_t topo2_elems = 0, n_tiles_max = 0, stage_elems = 0, tf_elems[3] = {1, 1, 1};
+    size_t n_tiles_max = 0, stage_elems = 0, tf_elems[3] = {1, 1, 1};
+    size_t chunk_elems = 0, ltop_elems = 0, wg_elems = 0;
     if (plain)
         for (int k = 0; k < 3; ++k) {
             const size_t T = (size_t)64 << k, nt = c->tiles[k].size() - 1;
-            topo2_elems = std::max(topo2_elems, nt * T * TOPO_CAP);
+            const int nl = lanes_for((int)T, (int)nt);
+            const size_t wgs = nt * (T * nl / 256);
+            chunk_elems = std::max(chunk_elems, wgs * 1024 * (size_t)lane_chunks(c->cap, nl));
+            ltop_elems = std::max(ltop_elems, wgs * 256 * (size_t)top_rounds(c->max_bonds, c->max_natives, nl));
+            wg_elems = std::max(wg_elems, wgs);
             stage_elems = std::max(stage_elems, nt * (size_t)stage_max_host((int)T));
             n_tiles_max = std::max(n_tiles_max, nt);
             tf_elems[k] = nt + 1;
@@ -170,18 +174,26 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
         return p;
     };
     DevBufs d{};
+    d.max_bonds = c->max_bonds;
+    d.max_natives = c->max_natives;
     d.pos[0] = (float4 *)take(2 * n * sizeof(float4));
     d.pos[1] = (float4 *)take(2 * n * sizeof(float4));
     d.trow = (int2 *)take(n * sizeof(int2));
     d.tent = (float2 *)take(c->tent.size() * sizeof(float2));
     d.list_cnt = (int *)take(n * sizeof(int));
-    d.list16 = (unsigned short *)take(list16_elems * sizeof(unsigned short));
-    d.fcnt = (int *)take((plain ? n : 0) * sizeof(int));
-    d.flist16 = (unsigned short *)take((plain ? list16_elems : 0) * sizeof(unsigned short));
+    d.list16 = (unsigned short *)take((plain ? chunk_elems : n * (size_t)c->cap) * sizeof(unsigned short));
+    d.flist16 = (unsigned short *)take(chunk_elems * sizeof(unsigned short));
+    d.skin_len = (unsigned short *)take(wg_elems * 256 * sizeof(unsigned short));
+    d.llen = (unsigned short *)take(wg_elems * 256 * sizeof(unsigned short));
+    d.grho = (unsigned char *)take(wg_elems * 256);
+    d.wg_rec = (WgRec *)take(wg_elems * sizeof(WgRec));
+    d.tile_top = (int4 *)take(n_tiles_max * sizeof(int4));
+    d.ltop = (uint2 *)take(ltop_elems * sizeof(uint2));
+    for (auto &f : d.fix)
+        f = (int4 *)take((plain ? n : 0) * sizeof(int4));
     d.hi_skin = (float4 *)take((plain ? n : 0) * sizeof(float4));
     d.skin_flag = (unsigned *)take(sizeof(unsigned));
     d.list_stats = (unsigned long long *)take(2 * sizeof(unsigned long long));
-    d.tile_ord = (unsigned char *)take(plain ? n_tiles_max * 256 : 0);
     d.skin_ord = (unsigned short *)take((plain ? n_tiles_max * 256 : 0) * sizeof(unsigned short));
     d.vel = (float4 *)take((plain ? n : 0) * sizeof(float4));
     d.facc = (float4 *)take((plain ? n : 0) * sizeof(float4));
@@ -190,8 +202,8 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
     d.re_tscale = (float *)take((plain ? 0 : T) * sizeof(float));
     d.re_stats = (unsigned long long *)take((plain ? 0 : 2 * T) * sizeof(unsigned long long));
     d.eacc = (double4 *)take((plain ? n : 0) * sizeof(double4));
-    d.topo2 = (uint2 *)take(topo2_elems * sizeof(uint2));
     d.stage = (int *)take(stage_elems * sizeof(int));
+    d.stage16 = (unsigned short *)take(stage_elems * sizeof(unsigned short));
     d.stage_cnt = (int *)take(n_tiles_max * sizeof(int));
     d.pack_off = (int *)take((T + 1) * sizeof(int));
     d.slot_res = (int *)take(n * sizeof(int));
@@ -337,6 +349,34 @@ StepConsts step_consts(const sop_ctx *c)
     return k;
 }
 
+// Scale of the fixed-point copies (plain schedule): the coarsest power of two
+// that keeps 2.5 times the distance a listed pair can have (r_list, and 16
+// standard deviations of the thermal drift of a list period, eight for each
+// partner) inside half the period of 2^32 units, so that a listed pair would
+// have to move 3 list cutoffs further apart within a list period before its
+// difference wrapped to a wrong near one.  At r_list = 20 A: k = 25, half a
+// period 64 A, unit 3e-8 A.  Bonded and native terms, which are steep where the forces cancel,
+// use the copies only while a unit is below 2^-24 of the shortest reference
+// length (the rounding of that length in single precision), the list only
+// while it is below 2e-6 sigma.
+FixDev fix_consts(const sop_ctx *c)
+{
+    const double drift = 16.0 * std::sqrt(2.0 * c->p.kBT * c->p.h / c->p.zeta * c->p.list_every);
+    const double half = 2.5 * (c->p.r_list + drift);
+    int k = 31 - (int)std::ceil(std::log2(std::min(std::max(half, 1e-9), 1e30)));
+    k = std::max(-60, std::min(60, k));
+    FixDev f{};
+    f.scale = std::ldexp(1.0, k);
+    f.period = std::ldexp(1.0, 32 - k);
+    f.inv_period = std::ldexp(1.0, k - 32);
+    f.unit = (float)std::ldexp(1.0, -k);
+    f.s2 = (float)std::ldexp(1.0, 2 * k);
+    f.reach = (float)std::ldexp(1.0, 30 - k);
+    f.list_far = (half > std::ldexp(1.0, 31 - k) || f.unit > 2e-6 * c->p.sigma) ? 1 : 0;
+    f.bond_far = f.unit > std::ldexp(c->min_r0, -24) ? 1 : 0;
+    return f;
+}
+
 // Underdamped integrator: the kick of the next step (h/2m right after the
 // velocities were set, else h/m); 0 selects the overdamped update.
 float ud_kick(const sop_ctx *c)
@@ -467,7 +507,7 @@ void rebuild(sop_ctx *c, hipStream_t s, bool advance, bool captured = false, boo
     const bool binned = captured || c->binned_at == c->step;
     if (skin_check_thr2(c) <= 0.0f || !checked)
         launch_force_skin(c->b, s);
-    launch_rebuild(c->b, c->cur, (int)c->n_res, c->cap, c->tile, c->grid, list_rc2(c), skin_rs2(c),
+    launch_rebuild(c->b, c->cur, (int)c->n_res, c->cap, c->tile, c->grid, fix_consts(c), list_rc2(c), skin_rs2(c),
                    c->n_traj > 1 ? 1 : 0, s, advance, c->p.list_every, binned, filter);
     if (!captured)
         c->binned_at = -1;
@@ -489,7 +529,7 @@ bool fuses_filter(const sop_ctx *c, bool check) { return c->force_mode == SOP_FO
 void one_step(sop_ctx *c, hipStream_t s, const long long *base, long long off, bool energy, bool check,
               bool first = false)
 {
-    launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), c->tip,
+    launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), fix_consts(c), c->tip,
                 c->pulls.empty() ? 0 : 1, energy, 0, base, off, check ? skin_check_thr2(c) : 0.0f, s,
                 c->force_mode, ud_kick(c), check ? &c->grid : nullptr, first ? list_rc2(c) : 0.0f,
                 c->grid.n_cells);
@@ -726,11 +766,14 @@ sop_status sop_load_topology(sop_ctx *c, int32_t n_traj, const int64_t *res_offs
         rn[j].push_back({i, (float)native_r0[k]});
     }
     c->trow.assign(n, int2{0, 0});
+    c->max_bonds = c->max_natives = 0;
     c->tent.clear();
     c->tent.reserve((size_t)(2 * (n_bonds + n_native)));
     for (long long i = 0; i < n; ++i) {
         std::sort(rb[i].begin(), rb[i].end());
         std::sort(rn[i].begin(), rn[i].end());
+        c->max_bonds = std::max(c->max_bonds, (int)rb[i].size());
+        c->max_natives = std::max(c->max_natives, (int)rn[i].size());
         if (rb[i].size() + rn[i].size() > (size_t)TOPO_CAP)
             return fail(c, SOP_E_ARG, "more than " + std::to_string(TOPO_CAP) +
                                           " bonded and native partners on residue " + std::to_string(i));
@@ -790,6 +833,11 @@ sop_status sop_load_topology(sop_ctx *c, int32_t n_traj, const int64_t *res_offs
     c->pull_slot.assign(n, -1);
     c->tip = TipDev{};
     c->tile = c->tile_req ? c->tile_req : default_tile(n);
+    c->min_r0 = 1e300;
+    for (long long k = 0; k < n_bonds; ++k)
+        c->min_r0 = std::min(c->min_r0, bond_r0[k]);
+    for (long long k = 0; k < n_native; ++k)
+        c->min_r0 = std::min(c->min_r0, native_r0[k]);
     c->max_len = 0;
     for (int t = 0; t < n_traj; ++t)
         c->max_len = std::max<long long>(c->max_len, res_offsets[t + 1] - res_offsets[t]);
@@ -1020,7 +1068,7 @@ sop_status sop_get_velocities(sop_ctx *c, double *v)
         if (!c->list_valid || c->step % c->p.list_every == 0)
             rebuild(c, c->stream, false);
         c->list_valid = true;
-        launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), c->tip,
+        launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), fix_consts(c), c->tip,
                     c->pulls.empty() ? 0 : 1, false, 1, nullptr, c->step, 0.0f, c->stream, c->force_mode);
         HIP_TRY(c, hipGetLastError());
         st = check_device_errors(c);
@@ -1231,26 +1279,19 @@ sop_status sop_bind_workspace(sop_ctx *c, void *dev, size_t bytes)
                               hipMemcpyHostToDevice, s));
     HIP_TRY(c, hipMemsetAsync(b.list_cnt, 0, n * sizeof(int), s));
     if (c->schedule == SOP_SCHEDULE_PLAIN) {
-        // slot arrays start as slot 0, which every tile's staging holds
-        const size_t n_pad = ((n + 255) / 256) * 256;
-        size_t topo2_elems = 0, n_tiles_max = 0;
+        size_t n_tiles_max = 0;
         for (int k = 0; k < 3; ++k) {
             const size_t nt = c->tiles[k].size() - 1;
-            topo2_elems = std::max(topo2_elems, nt * ((size_t)64 << k) * TOPO_CAP);
             n_tiles_max = std::max(n_tiles_max, nt);
             HIP_TRY(c, hipMemcpyAsync(b.tile_first[k], c->tiles[k].data(), c->tiles[k].size() * sizeof(int),
                                       hipMemcpyHostToDevice, s));
         }
-        HIP_TRY(c, hipMemsetAsync(b.list16, 0, n_pad * c->cap * sizeof(unsigned short), s));
-        HIP_TRY(c, hipMemsetAsync(b.flist16, 0, n_pad * c->cap * sizeof(unsigned short), s));
-        HIP_TRY(c, hipMemsetAsync(b.fcnt, 0, n * sizeof(int), s));
+        HIP_TRY(c, hipMemsetAsync(b.tile_top, 0, n_tiles_max * sizeof(int4), s));
         HIP_TRY(c, hipMemsetAsync(b.cell_count, 0, (size_t)c->n_cells_cap * sizeof(int), s));
         HIP_TRY(c, hipMemsetAsync(b.facc, 0, n * sizeof(float4), s));
         HIP_TRY(c, hipMemsetAsync(b.vel, 0, n * sizeof(float4), s));
-        HIP_TRY(c, hipMemsetAsync(b.tile_ord, 0, n_tiles_max * 256, s));
         HIP_TRY(c, hipMemsetAsync(b.skin_ord, 0, n_tiles_max * 256 * sizeof(unsigned short), s));
         HIP_TRY(c, hipMemsetAsync(b.eacc, 0, n * sizeof(double4), s));
-        HIP_TRY(c, hipMemsetAsync(b.topo2, 0, topo2_elems * sizeof(uint2), s));
         HIP_TRY(c, hipMemsetAsync(b.stage_cnt, 0, n_tiles_max * sizeof(int), s));
     }
     HIP_TRY(c, hipMemsetAsync(b.res_energy, 0, n * RES_E * sizeof(double), s));
@@ -1382,10 +1423,10 @@ sop_status sop_get_pairlist(sop_ctx *c, int64_t cap, int32_t *ij, int64_t *n_pai
     if (st != SOP_OK)
         return st;
     const long long n = c->n_res;
-    std::vector<int> cnt(n);
-    HIP_TRY(c, hipMemcpy(cnt.data(), c->b.list_cnt, n * sizeof(int), hipMemcpyDeviceToHost));
     std::vector<std::pair<int, int>> pairs;
     if (c->schedule == SOP_SCHEDULE_BATCHED) {
+        std::vector<int> cnt(n);
+        HIP_TRY(c, hipMemcpy(cnt.data(), c->b.list_cnt, n * sizeof(int), hipMemcpyDeviceToHost));
         std::vector<unsigned short> list((size_t)n * c->cap);
         HIP_TRY(c, hipMemcpy(list.data(), c->b.list16, list.size() * sizeof(unsigned short),
                              hipMemcpyDeviceToHost));
@@ -1405,30 +1446,35 @@ sop_status sop_get_pairlist(sop_ctx *c, int64_t cap, int32_t *ij, int64_t *n_pai
             }
         }
     } else {
-        // rows hold slots of their tile; the tile's stage maps slots to ids
+        // rows hold slots of their tile, in lane order; the tile's stage maps slots to ids
         const int T = c->tile, SM = stage_max_host(T);
         const auto &tl = c->tiles[tile_index(T)];
-        const size_t n_tiles = tl.size() - 1;
-        std::vector<unsigned short> list((size_t)n * c->cap);
+        const int n_tiles = (int)tl.size() - 1, nl = lanes_for(T, n_tiles), W = T * nl / 256;
+        const int chunks = lane_chunks(c->cap, nl);
+        std::vector<unsigned short> list((size_t)n_tiles * W * chunks * 1024);
+        std::vector<unsigned short> llen((size_t)n_tiles * W * 256);
+        std::vector<unsigned char> grho((size_t)n_tiles * T);
         std::vector<int> stage(n_tiles * (size_t)SM), stage_cnt(n_tiles);
         HIP_TRY(c, hipMemcpy(list.data(), c->b.flist16, list.size() * sizeof(unsigned short),
                              hipMemcpyDeviceToHost));
-        HIP_TRY(c, hipMemcpy(cnt.data(), c->b.fcnt, n * sizeof(int), hipMemcpyDeviceToHost));
+        HIP_TRY(c, hipMemcpy(llen.data(), c->b.llen, llen.size() * sizeof(unsigned short), hipMemcpyDeviceToHost));
+        HIP_TRY(c, hipMemcpy(grho.data(), c->b.grho, grho.size(), hipMemcpyDeviceToHost));
         HIP_TRY(c, hipMemcpy(stage.data(), c->b.stage, stage.size() * sizeof(int), hipMemcpyDeviceToHost));
         HIP_TRY(c, hipMemcpy(stage_cnt.data(), c->b.stage_cnt, n_tiles * sizeof(int), hipMemcpyDeviceToHost));
-        size_t tile = 0;
-        for (long long i = 0; i < n; ++i) {
-            while (i >= tl[tile + 1])
-                ++tile;
-            for (int k = 0; k < std::min(cnt[i], c->cap); ++k) {
-                const int sl = list[list16_index_host(i, k, c->cap)];
-                if (sl >= stage_cnt[tile])
-                    return fail(c, SOP_E_LIST_OVERFLOW, "list entry outside its tile's staging set");
-                const int j = stage[tile * SM + sl];
-                if (i < j)
-                    pairs.push_back({(int)i, j});
-            }
-        }
+        for (int tile = 0; tile < n_tiles; ++tile)
+            for (int w = 0; w < W; ++w)
+                for (int lane = 0; lane < 256; ++lane) {
+                    const int wg = tile * W + w;
+                    const int i = tl[tile] + grho[(size_t)wg * (256 / nl) + lane / nl];
+                    for (int k = 0; k < std::min((int)llen[(size_t)wg * 256 + lane], 4 * chunks); ++k) {
+                        const int sl = list[chunk_index(wg, k / 4, lane, chunks) * 4 + k % 4] >> 2;
+                        if (sl >= stage_cnt[tile])
+                            return fail(c, SOP_E_LIST_OVERFLOW, "list entry outside its tile's staging set");
+                        const int j = stage[(size_t)tile * SM + sl];
+                        if (i < j)
+                            pairs.push_back({i, j});
+                    }
+                }
     }
     std::sort(pairs.begin(), pairs.end());
     *n_pairs = (int64_t)pairs.size();
@@ -1452,7 +1498,7 @@ sop_status sop_compute_forces(sop_ctx *c, double *f, double *energies, double *f
     } else {
         if (stale)
             rebuild(c, c->stream, false);
-        launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), c->tip,
+        launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), fix_consts(c), c->tip,
                     c->pulls.empty() ? 0 : 1, true, 1, nullptr, c->step, 0.0f, c->stream, c->force_mode);
         launch_reduce_energy(c->b, c->n_traj, c->stream);
     }
@@ -1562,7 +1608,7 @@ sop_status sop_step(sop_ctx *c, int64_t n_steps)
             // the graph's first rebuild relies on the cells holding the
             // current positions and on the displacement check
             if (c->binned_at != c->step)
-                launch_bin_all(c->b, c->cur, (int)c->n_res, c->grid, c->stream);
+                launch_bin_all(c->b, c->cur, (int)c->n_res, c->grid, fix_consts(c), c->stream);
             if (c->skin_checked != c->step)
                 launch_force_skin(c->b, c->stream);
             HIP_TRY(c, hipGraphLaunch(c->graphs[c->cur][en], c->stream));
@@ -1688,7 +1734,7 @@ sop_status sop_step_timed(sop_ctx *c, int64_t n_steps, double *ms_out)
         }
         for (long long q = 0; q < K; ++q) {
             if (kind == 0) {
-                launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), c->tip,
+                launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), fix_consts(c), c->tip,
                             c->pulls.empty() ? 0 : 1, false, 0, nullptr, c->step + q, 0.0f,
                             c->cap_stream, c->force_mode, 0.0f);
                 c->cur ^= 1;

@@ -64,24 +64,55 @@ constexpr int TOPO_CAP = 64;
 // the kernels hold 1,024 or 2,048 of them in LDS at once).
 constexpr int STAGE_MAX = 4096;
 
+// Fixed-point copies of the positions (plain schedule): whole numbers of
+// units of 2^-k, modulo 2^32 units.  `reach` is a quarter of the period, in
+// the caller's units: a bonded or native pair within it on every axis at a
+// rebuild is taken from the copies until the next one, others (and every
+// such pair when `bond_far`, every list pair when `list_far`) from the
+// compensated positions.
+struct FixDev {
+    double scale, period, inv_period;  // 2^k, 2^(32-k), 2^(k-32)
+    float unit, s2, reach;             // 2^-k, 2^2k, 2^(30-k)
+    int list_far, bond_far;
+};
+
+// Plain schedule: what a workgroup's steps need to know of it, written at
+// each rebuild; one scalar load.
+struct WgRec {
+    int ox, oy, oz;    // origin (fixed-point)
+    int flags;         // WG_*
+    int first, count;  // the tile's residues
+    int slots;         // its staging set
+    int base;          // lowest id of its slots
+    int waves[4];      // per wave: list chunks | rounds of bonded entries << 16 | all rounds << 24
+    int pad[4];
+};
+
 // Device buffers carved out of the caller's workspace.
 struct DevBufs {
     // positions, two time layers; residue i is pos[l][2i] = {hi.xyz, tag},
     // pos[l][2i+1] = {lo.xyz, trajectory}; tag = index inside the
     // trajectory | fixed << 31.  x = hi + lo.
     float4 *pos[2];
+    int4 *fix[2];     // plain: fixed-point copies of the positions, per layer
     int2 *trow;       // per residue: {first entry, n_bond | n_native << 12}
     float2 *tent;     // {partner id bits, r0}: bonds first, then natives
     int *list_cnt;    // partners per residue (plain: of the skin rows)
-    unsigned short *list16;  // rows by residue (cap entries): plain, skin rows (pairs within
-                             // r_list + skin at the last skin build) as slots of its tile;
-                             // batched, the list as local slots of its pack
-    int *fcnt;               // plain: list partners per residue (the skin rows filtered at r_list)
-    unsigned short *flist16; // plain: the list rows (cap entries), slots of the residue's tile
+    unsigned short *list16;  // plain: skin rows (pairs within r_list + skin at the last skin build),
+                             // lane order; batched: the list, rows by residue (cap entries) of local
+                             // slots of its pack
+    unsigned short *skin_len;  // plain: skin entries of each lane (workgroup * 256 + lane)
+    unsigned short *flist16; // plain: the list rows (the skin rows filtered at r_list), lane order;
+                             // during a skin search its rows by residue (cap entries)
+    unsigned short *llen;    // plain: list entries of each lane (workgroup * 256 + lane)
+    unsigned char *grho;     // plain: residue in the tile of each lane group (workgroup * groups + group)
+    WgRec *wg_rec;           // plain: per workgroup, what its steps need of it
+    int4 *tile_top;          // plain: per tile, rounds of bonded and of native entries in `ltop`,
+                             // lowest id of its slots, whether stage16 holds them
+    uint2 *ltop;             // plain: bonded and native entries in lane order (top_index): {partner, r0 bits}
     float4 *hi_skin;         // plain: high parts of the positions at the last skin build
     unsigned *skin_flag;     // plain: nonzero when the next rebuild must rebuild the skin
     unsigned long long *list_stats;  // plain: {rebuilds, skin builds} since binding
-    unsigned char *tile_ord; // plain: per tile (tile * T + rank), its residues by decreasing list length
     unsigned short *skin_ord;  // plain: per tile (tile * T + rank), 1 + its residues by decreasing
                                // skin row length (0 before the first skin search: identity)
     float4 *vel;             // plain, underdamped: per-residue velocity before its last half kick
@@ -91,8 +122,9 @@ struct DevBufs {
     unsigned long long *re_stats;  // batched, replica exchange: {accepted, attempted} per ladder pair
     float4 *facc;            // plain, pair-based forces: per-residue force accumulator
     double4 *eacc;           // plain, pair-based forces: per-residue energy accumulator
-    uint2 *topo2;            // plain: {slot, r0 bits} of bonded/native partners, (i/T)*TOPO_CAP*T + e*T + i%T
     int *stage;       // plain: per tile, global ids of its slots (stage_max per tile)
+    unsigned short *stage16;  // plain: the same less the tile's lowest id (tile_top), where all
+                              // differences fit 16 bits: half the bytes of every step's ids
     int *stage_cnt;   // plain: slots per tile
     int *pack_off;    // batched form: first slot of each pack (n_packs + 1)
     int *slot_res;    // batched form: residue of each slot (a permutation of the residues)
@@ -102,6 +134,7 @@ struct DevBufs {
     int *cell_of;     // per residue: its cell at the last rebuild
     int *tile_first[3];  // plain: first residue of each tile (+ n) for tiles of 64, 128, 256
     int n_tiles[3];
+    int max_bonds, max_natives;  // most bonded and native entries of a residue
     int4 *traj_cell;  // per trajectory: cell-index offset that keeps trajectories apart
     int *traj_lo;     // per residue: first residue of its trajectory
     int *traj_hi;     // per residue: one past the last residue of its trajectory
@@ -141,12 +174,13 @@ struct StepConsts {
 // positions (binned by the last step kernel of the period); otherwise they
 // are cleared and filled first.
 void launch_rebuild(const DevBufs &b, int cur, int n_res, int cap, int tile, const GridDev &g,
-                    float rc2, float rs2, int multi, hipStream_t s, bool advance_step_base, int list_every,
-                    bool binned, bool filter = true);
+                    const FixDev &fix, float rc2, float rs2, int multi, hipStream_t s, bool advance_step_base,
+                    int list_every, bool binned, bool filter = true);
 // Sets the skin flag so that the next rebuild rebuilds the skin.
 void launch_force_skin(const DevBufs &b, hipStream_t s);
-// Clears the cells and bins every residue at its current position.
-void launch_bin_all(const DevBufs &b, int cur, int n_res, const GridDev &g, hipStream_t s);
+// Clears the cells, bins every residue at its current position and writes
+// the fixed-point copies of the layer.
+void launch_bin_all(const DevBufs &b, int cur, int n_res, const GridDev &g, const FixDev &fix, hipStream_t s);
 // mode: 0 = step, 1 = forces only.  check_thr2 > 0: after the update, a
 // residue that moved more than sqrt(check_thr2) from its position at the
 // last skin build sets the skin flag.
@@ -157,7 +191,7 @@ void launch_bin_all(const DevBufs &b, int cur, int n_res, const GridDev &g, hipS
 // which filters the skin rows at filter_rc2 itself, then clears the
 // n_cells cell counts and the skin flag.
 void launch_step(const DevBufs &b, int cur, int n_res, int cap, int tile, const StepConsts &c,
-                 const TipDev &tip, int has_pull, bool energy, int mode,
+                 const FixDev &fix, const TipDev &tip, int has_pull, bool energy, int mode,
                  const long long *step_base, long long step_off, float check_thr2, hipStream_t s,
                  int force_mode = 0, float ud_kick = 0.0f, const GridDev *bin_grid = nullptr,
                  float filter_rc2 = 0.0f, int n_cells = 0);
@@ -180,9 +214,48 @@ void launch_set_step(long long *dst, long long value, hipStream_t s);
 void launch_noise(const DevBufs &b, int cur, int n, const StepConsts &c, long long step, uint4 *words,
                   float4 *g, hipStream_t s);
 
-// Plain schedule: entry k of residue r's row (a slot of its tile), and the
-// slots a tile of `tile` residues can stage.
-inline size_t list16_index_host(long long r, int k, int cap) { return (size_t)r * cap + (size_t)k; }
+// Plain schedule, lane order.  A workgroup of 256 lanes serves 256 / nl
+// residues, nl adjacent lanes each; a tile of T residues takes W = T nl / 256
+// workgroups, and the residue of rank r in skin_ord belongs to group r / W of
+// workgroup tile W + r % W.  A residue's partners are dealt to its lanes by
+// their id modulo nl, in ascending order, so which lane sums a partner, and in
+// which order, depends on the list alone; a row that would give one lane more
+// than its share of the capacity and 16 is dealt in turn instead.  A lane's
+// entries (4 * slot, 16 bits) lie four to a chunk of 8 bytes, chunk k of a
+// workgroup's 256 lanes side by side: a wave reads its chunks as one
+// contiguous piece at an address that needs no row length, and a lane filters
+// its own entries without its neighbours.  Bonded and native entries lie the
+// same way, one {partner, r0} a round.
+#define SOP_HD __host__ __device__ __forceinline__
+// Lanes per residue.  A 64-residue tile in one workgroup (4 lanes) keeps the
+// redundant staging lowest and is best once the tiles fill the 256 compute
+// units about three times over; below that a step is as long as one wave's
+// chain of instructions, and 8 or 16 lanes shorten it.  us a step, 4 / 8 / 16
+// lanes: 16 tiles (1,000 residues) 10.7 / 8.5 / 7.4; 76 (4,800 at protein
+// density) 19.0 / 14.1 / 12.1; 160 10.0 / 8.3 / 7.8; 320 10.9 / 9.1 / 10.6;
+// 640 13.6 / 13.3 / 16.9; 1,200 18.9 / 21.8 / 27.7.
+inline int lanes_for(int tile, int n_tiles)
+{
+    if (tile == 64)
+        return n_tiles <= 200 ? 16 : (n_tiles <= 640 ? 8 : 4);
+    return 256 / tile;
+}
+// Chunks of a lane's entries (even: the skin rows are read two at a time).
+SOP_HD int lane_chunks(int cap, int nl) { return ((cap + nl - 1) / nl + 16 + 7) / 8 * 2; }
+SOP_HD size_t chunk_index(int wg, int k, int lane, int chunks) { return ((size_t)wg * chunks + k) * 256 + lane; }
+// Rounds of bonded, then of native entries: for the most of each that a
+// residue of the topology has.  TOP_MIN of them, and STAGE_MIN slots of a
+// staging set, are there for any tile (if only as the residue itself and the
+// lowest id): the steps load them untested.
+constexpr int TOP_MIN = 4, STAGE_MIN = 1024;
+inline int top_rounds(int max_bonds, int max_natives, int nl)
+{
+    const int r = (max_bonds + nl - 1) / nl + (max_natives + nl - 1) / nl;
+    return r > TOP_MIN ? r : TOP_MIN;
+}
+SOP_HD size_t top_index(int wg, int round, int lane, int rounds) { return ((size_t)wg * rounds + round) * 256 + lane; }
+
+// The slots a tile of `tile` residues can stage.
 inline int stage_max_host(int) { return 4096; }
 inline int tile_index(int tile) { return tile == 64 ? 0 : (tile == 128 ? 1 : 2); }
 

@@ -72,6 +72,27 @@ __device__ __forceinline__ int cell_index(const float4 &p, const int4 &off, cons
     return cx + g.gx * (cy + g.gy * cz);
 }
 
+// Fixed-point copy of a position: hi + lo as a whole number of units of 2^-k
+// (StepConsts), modulo 2^32.  The difference of two copies, taken in 32-bit
+// integers, is exact whatever the distance of the residues from the origin,
+// as long as they are less than 2^31 units apart.  x - P rint(x / P) (P =
+// 2^32 units) is exact in double; adding 1.5 * 2^52 rounds it to a whole
+// number in the low word.
+__device__ __forceinline__ int fix_axis(float hi, float lo, const FixDev &f)
+{
+    const double x = (double)hi + (double)lo;
+    const double r = __builtin_fma(-f.period, __builtin_rint(x * f.inv_period), x);
+    return __double2loint(__builtin_fma(r, f.scale, 0x1.8p52));
+}
+
+__device__ __forceinline__ int4 fix_pos(const float4 &hi, const float4 &lo, const FixDev &f)
+{
+    return make_int4(fix_axis(hi.x, lo.x, f), fix_axis(hi.y, lo.y, f), fix_axis(hi.z, lo.z, f), 0);
+}
+
+// Difference of two fixed-point coordinates, modulo 2^32.
+__device__ __forceinline__ int fix_diff(int a, int b) { return (int)((unsigned)a - (unsigned)b); }
+
 // Bin one residue at high part p into the grid of the next skin search:
 // its cell, a slot in that cell, and a copy of p there.
 __device__ __forceinline__ void bin_one(const float4 &p, int i, int traj, const GridDev &g,
@@ -95,13 +116,14 @@ __global__ void k_clear(int *__restrict__ a, int n)
         a[i] = 0;
 }
 
-// Every residue binned at its current position.  The last step kernel of
-// each list period bins the positions it writes; this kernel serves the
-// rebuilds that do not follow such a step (after new coordinates, a new
-// step count or a new tile size), after k_clear.
+// Every residue binned at its current position, and its fixed-point copy.
+// The last step kernel of each list period bins the positions it writes (and
+// every step kernel writes the copies); this kernel serves the rebuilds that
+// do not follow such a step (after new coordinates, a new step count or a
+// new tile size), after k_clear.
 __global__ void k_bin_all(const float4 *__restrict__ pos, int n, GridDev g, const int4 *__restrict__ traj_cell,
                           int *__restrict__ count, float4 *__restrict__ cells, int *__restrict__ cell_of,
-                          unsigned *__restrict__ err)
+                          unsigned *__restrict__ err, int4 *__restrict__ fix, FixDev f)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
@@ -109,7 +131,9 @@ __global__ void k_bin_all(const float4 *__restrict__ pos, int n, GridDev g, cons
     const float4 p = pos[2 * i];
     if (!isfinite(p.x) || !isfinite(p.y) || !isfinite(p.z))
         atomicOr(err, ERR_NONFINITE);
-    bin_one(p, i, __float_as_int(pos[2 * i + 1].w), g, traj_cell, count, cells, cell_of, err);
+    const float4 l = pos[2 * i + 1];
+    fix[i] = fix_pos(p, l, f);
+    bin_one(p, i, __float_as_int(l.w), g, traj_cell, count, cells, cell_of, err);
 }
 
 // ---------------------------------------------------------------------------
@@ -182,14 +206,32 @@ __device__ __forceinline__ void add_fene_d(Acc &A, const float3 &d, float r0, co
 }
 
 // Native contact: eps_h [(r0/r)^12 - 2 (r0/r)^6].
-__device__ __forceinline__ void add_native_d(Acc &A, const float3 &d, float r0, const PairConsts &k, bool rec)
+__device__ __forceinline__ void add_native_d(Acc &A, const float3 &d, float r02, const PairConsts &k, bool rec)
 {
 #pragma clang fp contract(off)
     const float ir2 = fast_rcp(len2(d));
-    const float s = r0 * r0 * ir2;
+    const float s = r02 * ir2;
     const float q = s * s * s;
     const float w = __builtin_fmaf(q, q, -q);  // q^2 - q
     acc_force(A, k.eh12 * w * ir2, d);
+    if (rec) {
+        A.e_n += (double)(k.eh * __builtin_fmaf(q, q, -2.0f * q));
+        A.vir += (double)(k.eh12 * w);
+    }
+}
+
+// The same from a difference d in fixed-point units: r02 = r0^2 in the
+// caller's units, s2 = 1 / unit^2, eu = 12 eps_h unit (so the force needs no
+// scaled difference).
+__device__ __forceinline__ void add_native_q(Acc &A, const float3 &d, float r02, float s2, float eu,
+                                             const PairConsts &k, bool rec)
+{
+#pragma clang fp contract(off)
+    const float ir2 = fast_rcp(len2(d)) * s2;
+    const float s = r02 * ir2;
+    const float q = s * s * s;
+    const float w = __builtin_fmaf(q, q, -q);  // q^2 - q
+    acc_force(A, eu * w * ir2, d);
     if (rec) {
         A.e_n += (double)(k.eh * __builtin_fmaf(q, q, -2.0f * q));
         A.vir += (double)(k.eh12 * w);
@@ -226,6 +268,25 @@ __device__ __forceinline__ void add_repulsive_u(Acc &A, const float3 &d, const P
     }
 }
 
+// The same from the difference d of two fixed-point copies (whole numbers of
+// units, exact; rounded once by the conversion): accumulates d / r^8 with r
+// in the caller's units and d in fixed-point ones.  s2 = 1 / unit^2; `live`
+// false: no contribution, whatever q.
+__device__ __forceinline__ void add_repulsive_q(Acc &A, const int3 &q, float s2, const PairConsts &k, bool live,
+                                                bool rec)
+{
+#pragma clang fp contract(off)
+    const float3 d = make_float3((float)q.x, (float)q.y, (float)q.z);
+    const float ir2 = fast_rcp(len2(d)) * s2;
+    const float ir4 = ir2 * ir2;
+    acc_force(A, live ? ir4 * ir4 : 0.0f, d);
+    if (rec) {
+        const float q6 = live ? k.sg6 * ir4 * ir2 : 0.0f;
+        A.e_r += (double)(k.el * q6);
+        A.vir += (double)(k.el6 * q6);
+    }
+}
+
 // The same terms from compensated positions (hi, lo) of both residues.
 __device__ __forceinline__ void add_fene(Acc &A, const float4 &hi, const float4 &lo, const float4 &hj,
                                          const float4 &lj, float r0, const PairConsts &k, bool rec,
@@ -237,7 +298,7 @@ __device__ __forceinline__ void add_fene(Acc &A, const float4 &hi, const float4 
 __device__ __forceinline__ void add_native(Acc &A, const float4 &hi, const float4 &lo, const float4 &hj,
                                            const float4 &lj, float r0, const PairConsts &k, bool rec)
 {
-    add_native_d(A, pair_delta(hi, lo, hj, lj), r0, k, rec);
+    add_native_d(A, pair_delta(hi, lo, hj, lj), r0 * r0, k, rec);
 }
 
 // Cantilever `pull` (index or -1) and tip on one residue at t_n = step*h.
@@ -393,12 +454,17 @@ __device__ __forceinline__ void langevin_update(float4 &hi, float4 &lo, const Ac
 // ---------------------------------------------------------------------------
 template <int TILE>
 constexpr int stage_max() { return 4096; }
-// Slots held in LDS at once by the kernels that read the staging set; a
-// tile with more slots is taken in windows of this many.
-template <int TILE>
-constexpr int stage_win() { return TILE >= 256 ? 2048 : 1024; }
-// Row padding (and the slot of a bonded/native entry of a failed tile).
-constexpr unsigned short EMPTY_SLOT = 0xffffu;
+// Slots held in LDS at once by the kernels that read the staging set (12
+// bytes each: 21 KiB leave room for five workgroups a CU beside the rings of
+// the period's first step); a tile with more slots is taken in windows of
+// this many.
+template <int NL>
+constexpr int stage_win() { return NL == 1 ? 3072 : (NL >= 8 ? 2559 : 1792); }
+// Lane-ordered table of bonded/native entries: where there is none the
+// partner is the residue itself (so that every entry can be followed); this
+// bit beside the partner's id: the pair is out of the fixed-point copies'
+// reach until the next rebuild.
+constexpr unsigned FAR_ENTRY = 0x80000000u;
 
 // Candidate residues (the residues of the cells around a tile) held in LDS
 // at once during a rebuild; more are taken in windows of whole cells.  Small
@@ -410,7 +476,6 @@ template <int TILE>
 constexpr int cells_max() { return TILE >= 256 ? 512 : (TILE >= 128 ? 1024 : 640); }
 template <int TILE>
 constexpr int chash_bits() { return TILE == 128 ? 11 : 10; }
-constexpr int EXTRA_MAX = 128;  // bonded/native partners outside the tile's cells
 constexpr int TREG = 8;  // bonded/native entries per residue kept in registers during a search (more: global)
 
 struct BuildArgs {
@@ -426,7 +491,6 @@ struct BuildArgs {
     const float2 *tent;
     int *list_cnt;
     unsigned short *list16;
-    uint2 *topo2;
     int *stage;
     int *stage_cnt;
     unsigned *err;
@@ -476,11 +540,6 @@ __device__ __forceinline__ unsigned wave_or(unsigned v)
     return v;
 }
 
-// Bonded/native entry codes while a tile is built.
-constexpr unsigned CODE_NONE = 0xffffffffu;     // partner not found yet
-constexpr unsigned CODE_WINDOW = 0x80000000u;   // | candidate index in the current window
-constexpr unsigned CODE_EXTRA = 0x40000000u;    // | index among the extra slots
-
 // One workgroup of 256 lanes per tile of TILE consecutive residues; lane t
 // serves residue t % TILE and part q = t / TILE of its work (NLB = 256/TILE
 // parts).
@@ -493,10 +552,9 @@ constexpr unsigned CODE_EXTRA = 0x40000000u;    // | index among the extra slots
 //     Algorithm 3, one bit per candidate, part q taking a contiguous range
 //     of the 32-candidate words (words outside every neighbourhood of a wave
 //     are skipped).  Self, bonded and native partners are cleared; the
-//     candidates some row or entry uses get the next staging slots in sorted
-//     order; each part appends its words' partners to the row at the offset
-//     the lower parts leave.
-//  3. Bonded/native partners outside the cells take extra slots at the end.
+//     candidates some row uses get the next staging slots in sorted order;
+//     each part appends its words' partners to the row at the offset the
+//     lower parts leave.
 // A row lists its partners in (cell, residue index) order whatever the tile
 // size or the order in which residues were binned.
 template <int TILE, bool MULTI>
@@ -524,9 +582,8 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
     __shared__ short wlo[NW], whi[NW];    // sorted cells spanned by each word
     __shared__ short pcnt[NT];            // partners of (part, residue) in this window
     __shared__ int rowbase[TILE];         // partners of the residue in earlier windows
-    __shared__ int extra[EXTRA_MAX];
     __shared__ int part[NT];
-    __shared__ int n_cu, n_extra, bad_cells, n_used_w;
+    __shared__ int n_cu, bad_cells, n_used_w;
 
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         // every rebuild starts here (the kernels after it do not read these)
@@ -545,7 +602,7 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
     const int first = a.tile_first[tile], tcnt = a.tile_first[tile + 1] - first;
     const int i = first + rho;
     const bool act = rho < tcnt;
-    const bool lead = act && q == 0;  // writes the residue's count and padding
+    const bool lead = act && q == 0;  // writes the residue's count
     const GridDev g = a.g;
     if (tile == 0 && t == 0)
         ++a.stats[1];
@@ -557,7 +614,6 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         rowbase[t] = 0;
     if (t == 0) {
         n_cu = 0;
-        n_extra = 0;
         bad_cells = 0;
     }
     __syncthreads();
@@ -580,14 +636,11 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
     // entry e = v * NLB + q of the first TREG is this part's v-th
     constexpr int TPP = TREG / NLB;
     int tj[TPP], tm[TPP];
-    unsigned tr0[TPP], tcode[TPP];
 #pragma unroll
     for (int v = 0; v < TPP; ++v) {
         const int e = v * NLB + q;
         const float2 te = e < ntop ? a.tent[row.x + e] : make_float2(0.0f, 0.0f);
         tj[v] = __float_as_int(te.x);
-        tr0[v] = __float_as_uint(te.y);
-        tcode[v] = CODE_NONE;
     }
 #pragma unroll
     for (int v = 0; v < TPP; ++v)
@@ -621,18 +674,14 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         }
     }
     __syncthreads();
-    uint2 *trw = a.topo2 + (size_t)tile * TOPO_CAP * TILE + rho;
     auto fail_tile = [&]() {
-        // report; leave the tile pointing at the empty slot so steps stay in bounds
+        // report; leave the tile with no slots and no partners
         if (t == 0) {
             atomicOr(a.err, ERR_STAGE);
             a.stage_cnt[tile] = 0;
         }
-        if (lead) {
+        if (lead)
             a.list_cnt[i] = 0;
-            for (int e = 0; e < ntop; ++e)
-                trw[(size_t)e * TILE] = make_uint2((unsigned)EMPTY_SLOT, __float_as_uint(1.0f));
-        }
     };
     if (bad_cells) {
         fail_tile();
@@ -684,11 +733,6 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         if (t == 0)
             cbase[NC] = M;
     }
-    // entries beyond TREG live in the topology output meanwhile; entry
-    // e >= TREG belongs to part (e - TREG) mod NLB throughout
-    if (act)
-        for (int e = TREG + q; e < ntop; e += NLB)
-            trw[(size_t)e * TILE] = make_uint2(CODE_NONE, __float_as_uint(a.tent[row.x + e].y));
     __syncthreads();
     // partners' cells -> sorted cell numbers (or -1 outside the tile's cells)
 #pragma unroll
@@ -809,7 +853,6 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         }
         __syncthreads();
         // self, bonded and native partners in this window: clear their bits
-        // (their candidates are marked used: a partner's slot is needed anyway)
         auto find = [&](int j, int m) -> int {  // window candidate of residue j in sorted cell m, or -1
             if (m < mA || m >= mB)
                 return -1;
@@ -824,37 +867,21 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
             }
             return (lo < end && __float_as_int(cand[lo].w) == j) ? lo : -1;
         };
-        auto take = [&](int r) {
-            atomicAnd(&bits[(r >> 5) * TILE + rho], ~(1u << (r & 31)));
-            atomicOr(&used[r >> 5], 1u << (r & 31));
+        auto drop = [&](int r) {
+            if (r >= 0)
+                atomicAnd(&bits[(r >> 5) * TILE + rho], ~(1u << (r & 31)));
         };
-        if (lead) {
-            const int rs = find(i, own_m);
-            if (rs >= 0)
-                atomicAnd(&bits[(rs >> 5) * TILE + rho], ~(1u << (rs & 31)));
-        }
-        if (act) {
+        if (lead)
+            drop(find(i, own_m));
+        if (act)
             for (int e = TREG + q; e < ntop; e += NLB) {
-                if (trw[(size_t)e * TILE].x != CODE_NONE)
-                    continue;
                 const int j = __float_as_int(a.tent[row.x + e].x);
-                const int r = find(j, lookup(a.cell_of[j]));
-                if (r >= 0) {
-                    take(r);
-                    trw[(size_t)e * TILE].x = CODE_WINDOW | (unsigned)r;
-                }
+                drop(find(j, lookup(a.cell_of[j])));
             }
-        }
 #pragma unroll
-        for (int v = 0; v < TPP; ++v) {
-            if (v * NLB + q < ntop && tcode[v] == CODE_NONE) {
-                const int r = find(tj[v], tm[v]);
-                if (r >= 0) {
-                    take(r);
-                    tcode[v] = CODE_WINDOW | (unsigned)r;
-                }
-            }
-        }
+        for (int v = 0; v < TPP; ++v)
+            if (v * NLB + q < ntop)
+                drop(find(tj[v], tm[v]));
         __syncthreads();
         // slots of the used candidates: prefix over the window's words (<= 32);
         // row counts of each part
@@ -905,19 +932,6 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
                     row_store(k++, (unsigned short)(wb + __popc(uw & ((1u << kb) - 1u))));
                 }
             }
-            auto slot_of = [&](unsigned v) {
-                const int r = (int)(v & ~CODE_WINDOW), w = r >> 5;
-                return (unsigned)(wbase[w] + __popc(used[w] & ((1u << (r & 31)) - 1u)));
-            };
-#pragma unroll
-            for (int v = 0; v < TPP; ++v)
-                if (tcode[v] != CODE_NONE && (tcode[v] & CODE_WINDOW))
-                    tcode[v] = slot_of(tcode[v]);
-            for (int e = TREG + q; e < ntop; e += NLB) {
-                const unsigned v = trw[(size_t)e * TILE].x;
-                if (v != CODE_NONE && (v & CODE_WINDOW))
-                    trw[(size_t)e * TILE].x = slot_of(v);
-            }
         }
         slot_base += nu;
         mA = mB;
@@ -930,313 +944,350 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         }
     }
 
-    // ---- 3. partners outside the cells ----
-    if (act) {
-#pragma unroll
-        for (int v = 0; v < TPP; ++v)
-            if (v * NLB + q < ntop && tcode[v] == CODE_NONE) {
-                const int k = atomicAdd(&n_extra, 1);
-                if (k < EXTRA_MAX)
-                    extra[k] = tj[v];
-                tcode[v] = CODE_EXTRA | (unsigned)k;
-            }
-        for (int e = TREG + q; e < ntop; e += NLB)
-            if (trw[(size_t)e * TILE].x == CODE_NONE) {
-                const int k = atomicAdd(&n_extra, 1);
-                if (k < EXTRA_MAX)
-                    extra[k] = __float_as_int(a.tent[row.x + e].x);
-                trw[(size_t)e * TILE].x = CODE_EXTRA | (unsigned)k;
-            }
-    }
-    __syncthreads();
-    const int n_ex = n_extra;
-    const int S = slot_base + min(n_ex, EXTRA_MAX);
-    if (S > SM || n_ex > EXTRA_MAX) {
-        fail_tile();
-        return;  // uniform
-    }
-    for (int k = t; k < n_ex; k += NT)
-        st[slot_base + k] = extra[k];
     if (t == 0)
-        a.stage_cnt[tile] = S;
-    if (!act)
-        return;
-    auto final_slot = [&](unsigned v) {
-        return ((v & CODE_WINDOW) == 0 && (v & CODE_EXTRA)) ? (unsigned)slot_base + (v & ~CODE_EXTRA) : v;
-    };
-#pragma unroll
-    for (int v = 0; v < TPP; ++v)
-        if (v * NLB + q < ntop)
-            trw[(size_t)(v * NLB + q) * TILE] = make_uint2(final_slot(tcode[v]), tr0[v]);
-    for (int e = TREG + q; e < ntop; e += NLB)
-        trw[(size_t)e * TILE].x = final_slot(trw[(size_t)e * TILE].x);
+        a.stage_cnt[tile] = slot_base;
     if (!lead)
         return;
-    // count; the last chunk padded with the empty slot
     const int cnt = rowbase[rho];
-    for (int k = cnt; k < ((cnt + 3) & ~3); ++k)
-        row_store(k, EMPTY_SLOT);
     a.list_cnt[i] = cnt;
     if (cnt > a.cap)
         atomicOr(a.err, ERR_OVERFLOW);
 }
 
 // ---------------------------------------------------------------------------
-// List from the skin rows: every list_every steps each residue's skin row
-// (its partners within r_list + skin at the last skin build, in slot order)
-// is filtered with the single-precision predicate r < r_list of Algorithm 3
-// on the current positions.  The skin build runs again before the filter
-// whenever some residue has moved more than skin/2 since the last one, so
-// every pair within r_list is in the skin rows and the filtered rows equal a
-// rebuild from all pairs, entry for entry in the same order.
+// List from the skin rows: every list_every steps each lane's skin entries
+// (the partners of its residue within r_list + skin at the last skin build
+// that were dealt to it, in slot order) are filtered with the
+// single-precision predicate r < r_list of Algorithm 3 on the current
+// positions.  The skin build runs again before the filter whenever some
+// residue has moved more than skin/2 since the last one, so every pair within
+// r_list is in the skin rows and the filtered rows equal a rebuild from all
+// pairs, entry for entry in the same order.
 // ---------------------------------------------------------------------------
 struct FilterArgs {
     const int *tile_first;
     const float4 *pos;
     const int *stage;
     const int *stage_cnt;
-    const unsigned short *skin16;
-    const int *skin_cnt;
-    unsigned short *list16;
-    int *list_cnt;
+    const uint4 *skin16;             // pieces of 8 entries, lane order
+    const unsigned short *skin_len;  // entries of each lane
+    const unsigned short *skin_ord;  // per tile: 1 + its residues by decreasing skin row length
+    uint2 *ltop;
+    const int4 *tile_top;
+    uint2 *list16;                   // chunks of 4 entries, lane order
+    unsigned short *llen;
+    unsigned char *grho;
+    WgRec *wg_rec;
     int *cell_count;
     unsigned *skin_flag;
-    unsigned char *tile_ord;  // per tile: its residues by decreasing list length
-    const unsigned short *skin_ord;  // per tile: 1 + its residues by decreasing skin row length
+    FixDev fix;
     float rc2;
-    int cap, n_cells;
+    int cap, n_cells, top_rounds;
 };
 
-template <int TILE>
-__global__ __launch_bounds__(256, TILE == 64 ? 5 : (TILE == 128 ? 3 : 2)) void k_filter(FilterArgs a)
+// Residues of a workgroup, workgroups of a tile and LDS of the kernels that
+// work in lane order (NL lanes a residue).
+template <int TILE, int NL>
+struct Rows {
+    static constexpr int RW = 256 / NL, W = TILE / RW;
+    static constexpr int SW = stage_win<NL>();
+    static constexpr int XS = SW + 1;   // stride of the axes; slot SW is far away
+    static constexpr int BYTES = XS * 12;
+    static constexpr int NPRE = 6;      // list chunks a lane keeps in registers
+    static constexpr int RING = 16;     // passing entries of a lane on their way to memory
+};
+
+// Residue of group r of a tile (r < tcnt): the order of the last skin search.
+__device__ __forceinline__ int ranked(const unsigned short *ord, size_t at, int r)
 {
-    constexpr int NL = 256 / TILE;  // lanes per residue, adjacent in the wave
+    const int o = ord[at];
+    return o > 0 ? o - 1 : r;
+}
+
+// What holds for a workgroup until the next rebuild: it has a FAR_ENTRY; the
+// tile's residues do not fit a cube of 2 NARROW_TILE.  Within NARROW_TILE of
+// the cube's centre (the origin) on every axis, list partners (within r_list
+// = 20 A at the rebuild) lie within about 64 A of it, so positions relative to
+// the origin rounded to single precision separate list pairs to about 8e-6 A
+// at most; other tiles subtract the copies themselves.  Origin and test
+// depend on the tile's own residues only, neither on which other residues
+// are staged nor on how the tile's are dealt to workgroups.
+constexpr int WG_FAR = 1, WG_WIDE = 2;
+constexpr int WG_IDS32 = 4;  // the tile's slot ids do not fit stage16
+constexpr float NARROW_TILE = 40.0f;
+
+// Filters the skin entries of every lane of a workgroup; returns the number
+// of list entries of this lane, and the workgroup's record.  Every lane of a
+// wave gets as many chunks as the wave's longest, padded with the far-away
+// slot (whose term is exactly zero), so the sums run without lane masks.  Each lane tests
+// its own entries and appends those that pass to its own list row, so nothing
+// crosses lanes: 13 vector instructions and 3 LDS accesses an entry, where
+// rows compacted across a residue's lanes took 40.  An entry goes to the
+// lane's ring in LDS whether it passes or not, and stays if it does; whole
+// chunks leave for memory.
+template <int TILE, int NL>
+__device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile, int t, int first, int tcnt, bool in,
+                                           int rho, unsigned char *region, unsigned short *ring, float *bb,
+                                           WgRec &wr)
+{
+    using R = Rows<TILE, NL>;
     constexpr int SM = stage_max<TILE>();
-    constexpr int SW = stage_win<TILE>();
-    // filtered entries of a residue gathered in LDS (a multiple of 8, so
-    // rows start 16-byte aligned); sized so that 64-residue tiles fit five
-    // workgroups per CU
-    constexpr int OUTW = TILE == 64 ? 184 : (TILE == 128 ? 96 : 48);
-    constexpr int PF = 6;      // row pieces per lane loaded up front
-    constexpr int MAXP = 128;  // pieces of 8 entries in a row (cap <= 1024)
-    // the staged positions (predicate) and the gathered rows (emit) share
-    // one region
-    constexpr int HS_B = SW * 16, OUT_B = TILE * OUTW * 2;
-    __shared__ __align__(16) unsigned char region[HS_B > OUT_B ? HS_B : OUT_B];
-    float4 *hs = reinterpret_cast<float4 *>(region);
-    unsigned short *out_s = reinterpret_cast<unsigned short *>(region);
-    __shared__ int lens[TILE];
-    __shared__ unsigned char pbits[TILE * MAXP];  // passing entries of each piece
-    const int tile = blockIdx.x, t = threadIdx.x;
-    const int q = t % NL;
-    // the cell counts are read only by the skin build, which is done: clear
-    // them for the next one; the flag is read only by the skin build too
-    for (int k = tile * 256 + t; k < a.n_cells; k += gridDim.x * 256)
-        a.cell_count[k] = 0;
-    if (tile == 0 && t == 0)
-        *a.skin_flag = 0u;
-    const int first = a.tile_first[tile], tcnt = a.tile_first[tile + 1] - first;
+    constexpr int SW = R::SW, XS = R::XS;
+    const int i = first + rho;
+    float *hx = reinterpret_cast<float *>(region);
     const int S = min(a.stage_cnt[tile], SM);
     const int *st = a.stage + (size_t)tile * SM;
-    // the residue of this lane group: rows longest first (the order of the
-    // last skin search)
-    const bool act = t / NL < tcnt;
-    const int ord = act ? (int)a.skin_ord[(size_t)tile * TILE + t / NL] : 0;
-    const int rho = act ? (ord > 0 ? ord - 1 : t / NL) : t / NL;
-    const int i = first + (act ? rho : 0);
-    const int len = act ? min(a.skin_cnt[i], a.cap) : 0;
-    // the row in 16-byte pieces of 8 entries, piece m NL + q to lane q, so
-    // a residue's lanes read 16 NL contiguous bytes per round; the first PF
-    // pieces of this lane are loaded before the staging
-    const uint4 *src = reinterpret_cast<const uint4 *>(a.skin16 + (size_t)i * a.cap);
-    const int npc = (len + 7) >> 3;
-    uint4 pre[PF];
-#pragma unroll
-    for (int m = 0; m < PF; ++m)
-        pre[m] = m * NL + q < npc ? src[m * NL + q] : make_uint4(0u, 0u, 0u, 0u);
+    const int4 top = a.tile_top[tile];
+    const int chunks = lane_chunks(a.cap, NL);
+    const uint4 *src = a.skin16 + (size_t)wg * (chunks / 2) * 256 + t;
+    uint2 *dst = a.list16 + (size_t)wg * chunks * 256 + t;
+    const int len = a.skin_len[wg * 256 + t];
+    const int np = (len + 7) >> 3;
+    uint4 next = src[0];
     const float4 pi = a.pos[2 * i];
-    unsigned char *pb = pbits + rho * MAXP;
-    // passing entries of this lane's first PF pieces, eight bits a piece, in
-    // registers; later pieces (rows longer than 8 PF NL entries) in LDS
-    unsigned pbr[(PF + 3) / 4] = {};
-    // the predicate, window by window of the staging set (one window for
-    // nearly every tile): each entry is tested in the window holding its slot
-    const bool one_win = S <= SW;
-    for (int w0 = 0; w0 < S || w0 == 0; w0 += SW) {
-        const int wn = min(SW, S - w0);
-        if (w0 > 0)
-            __syncthreads();  // the previous window's readers are done
-        for (int sl = t; sl < wn; sl += 256)
-            hs[sl] = a.pos[2 * st[w0 + sl]];
-        __syncthreads();
-        // branch-free: the eight staged positions are read, then all eight
-        // are tested and the results masked.  One window (nearly every
-        // tile): every entry of the row is a staged slot, and entries past
-        // the row's end (masked afterwards) are clamped into the window.
-        // Several windows: an entry outside the current one reads slot 0
-        // and is masked.
-        auto test = [&](const uint4 &w, int pc) -> unsigned {
-            const unsigned ws[4] = {w.x, w.y, w.z, w.w};
-            const int valid = len - pc * 8;
-            const unsigned tail = valid >= 8 ? 0xffu : (valid > 0 ? (1u << valid) - 1u : 0u);
-            unsigned ok = 0u, bits = 0u;
-#pragma unroll
-            for (int h = 0; h < 8; h += 4) {  // four reads in flight, then their tests
-                float4 pj[4];
-#pragma unroll
-                for (int u = h; u < h + 4; ++u) {
-                    const unsigned sl = (ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu;
-                    const int e = (int)sl - w0;
-                    const bool in = one_win || (unsigned)e < (unsigned)wn;
-                    ok |= (unsigned)in << u;
-                    pj[u - h] = hs[one_win ? min(sl, (unsigned)(SW - 1)) : (in ? (unsigned)e : 0u)];
-                }
-#pragma unroll
-                for (int u = h; u < h + 4; ++u)
-                    bits |= (unsigned)within_cutoff(pi, pj[u - h], a.rc2) << u;
-            }
-            return bits & ok & tail;
-        };
-#pragma unroll
-        for (int m = 0; m < PF; ++m)
-            if (m * NL + q < npc)
-                pbr[m >> 2] |= test(pre[m], m * NL + q) << (8 * (m & 3));
-        for (int pc = PF * NL + q; pc < npc; pc += NL) {
-            const unsigned bits = test(src[pc], pc);
-            pb[pc] = (unsigned char)(w0 == 0 ? bits : (bits | pb[pc]));
+    const float4 pb = a.pos[2 * (first + min(t, tcnt - 1))];
+    auto stage_window = [&](int w0, int wn) {
+        for (int sl = t; sl < wn; sl += 256) {
+            const float4 h = a.pos[2 * st[w0 + sl]];
+            hx[sl] = h.x;
+            hx[XS + sl] = h.y;
+            hx[2 * XS + sl] = h.z;
         }
-    }
-    // the row's passing entries, over the residue's lanes
-    int tot = 0;
-#pragma unroll
-    for (int k = 0; k < (PF + 3) / 4; ++k)
-        tot += __popc(pbr[k]);
-    for (int pc = PF * NL + q; pc < npc; pc += NL)
-        tot += __popc((unsigned)pb[pc]);
-#pragma unroll
-    for (int off = 1; off < NL; off <<= 1)
-        tot += __shfl_xor(tot, off, NL);
-    __syncthreads();  // the staged positions are dead: the region takes the rows
-    unsigned short *dst = a.list16 + (size_t)i * a.cap;
-    // rows that fit (padding included) are gathered in LDS and written out
-    // in 16-byte pieces
-    const bool in_lds = ((tot + 7) & ~7) <= OUTW;
-    unsigned short *ob_l = out_s + rho * OUTW;  // LDS
-    int rounds = (npc + NL - 1) / NL;
-#pragma unroll
-    for (int off = 1; off < NL; off <<= 1)
-        rounds = max(rounds, __shfl_xor(rounds, off, NL));  // uniform over the residue's lanes
-    int base = 0;
-    auto emit = [&](const uint4 &w, unsigned bits) {
-        const unsigned ws[4] = {w.x, w.y, w.z, w.w};
-        const int c = __popc(bits);
-        // passing entries before this lane's piece: scan over the residue's lanes
-        int v = c;
-#pragma unroll
-        for (int off = 1; off < NL; off <<= 1) {
-            const int y = __shfl_up(v, off, NL);
-            if (q >= off)
-                v += y;
-        }
-        const int o = base + v - c;
-        // passing entry u goes to o + (passing entries before it): unrolled
-        // stores, LDS for rows that fit, else straight to the list
-        if (in_lds) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if ((bits >> u) & 1u)
-                    ob_l[o + __popc(bits & ((1u << u) - 1u))] =
-                        (unsigned short)((ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu);
-        } else {
-            for (int k = o; bits; ++k) {
-                const int u = __ffs(bits) - 1;
-                bits &= bits - 1u;
-                dst[k] = (unsigned short)((ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu);
-            }
-        }
-        base += __shfl(v, NL - 1, NL);
     };
-#pragma unroll
-    for (int m = 0; m < PF; ++m)
-        if (m < rounds)
-            emit(pre[m], (pbr[m >> 2] >> (8 * (m & 3))) & 0xffu);
-    for (int m = PF; m < rounds; ++m) {
-        const int pc = m * NL + q;
-        emit(pc < npc ? src[pc] : make_uint4(0u, 0u, 0u, 0u), pc < npc ? (unsigned)pb[pc] : 0u);
-    }
-    if (act && q == NL - 1) {
-        // pad the row to a multiple of 8 entries: with the LDS slot of the
-        // far-away position when the tile fits one window, else the empty slot
-        const unsigned short pad = S <= SW ? (unsigned short)SW : EMPTY_SLOT;
-        for (int k = base; k < ((base + 7) & ~7); ++k) {
-            if (in_lds)
-                ob_l[k] = pad;
-            else
-                dst[k] = pad;
+    stage_window(0, min(SW, S));
+    if (t < 3)
+        hx[t * XS + SW] = 1.0e18f;
+    // bonded and native partners beyond the reach of the fixed-point copies
+    bool far = false;
+    int rounds = 0;  // that this wave has entries in
+    for (int r = 0; r < top.x + top.y; ++r) {
+        unsigned &e = a.ltop[top_index(wg, r, t, a.top_rounds)].x;
+        const unsigned j = e;
+        if (j != (unsigned)i) {
+            const float4 h = a.pos[2 * (j & ~FAR_ENTRY)];
+            const bool out = !(fmaxf(fabsf(h.x - pi.x), fmaxf(fabsf(h.y - pi.y), fabsf(h.z - pi.z))) <= a.fix.reach);
+            far |= out;
+            if (out != (j >= FAR_ENTRY))
+                e = j ^ FAR_ENTRY;
         }
-        a.list_cnt[i] = base;
-        lens[rho] = base;
+        if (__any(j != (unsigned)i))
+            rounds = r + 1;
     }
-    __syncthreads();
-    if (act && in_lds) {
-        const uint4 *sp = reinterpret_cast<const uint4 *>(out_s + rho * OUTW);
-        uint4 *dp = reinterpret_cast<uint4 *>(dst);
-        for (int pc = q; pc < ((base + 7) >> 3); pc += NL)
-            dp[pc] = sp[pc];
-    }
-    // the step kernel hands the rows to its waves longest first, so that the
-    // rows a wave sums have about the same length (ties in index order):
-    // the residue's rank, counted by its NL lanes over a share of the tile
-    int r = 0;
-    if (act)
-        for (int u = q * (TILE / NL); u < min(tcnt, (q + 1) * (TILE / NL)); ++u)
-            r += (lens[u] > base || (lens[u] == base && u < rho)) ? 1 : 0;
+    // the box of the tile's residues, 64 to a wave
+    if (t < TILE) {
 #pragma unroll
-    for (int off = 1; off < NL; off <<= 1)
-        r += __shfl_xor(r, off, NL);
-    if (act && q == 0)
-        a.tile_ord[(size_t)tile * TILE + r] = (unsigned char)rho;
+        for (int ax = 0; ax < 3; ++ax) {
+            float mn = comp(pb, ax), mx = mn;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                mn = fminf(mn, __shfl_xor(mn, off));
+                mx = fmaxf(mx, __shfl_xor(mx, off));
+            }
+            if ((t & 63) == 0) {
+                bb[(t >> 6) * 6 + ax] = mn;
+                bb[(t >> 6) * 6 + 3 + ax] = mx;
+            }
+        }
+    }
+    int flags = __syncthreads_or(far ? 1 : 0) ? WG_FAR : 0;
+    {
+        float o[3], half = 0.0f;
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            float lo = bb[ax], hi = bb[3 + ax];
+#pragma unroll
+            for (int w = 1; w < TILE / 64; ++w) {
+                lo = fminf(lo, bb[6 * w + ax]);
+                hi = fmaxf(hi, bb[6 * w + 3 + ax]);
+            }
+            o[ax] = 0.5f * lo + 0.5f * hi;
+            half = fmaxf(half, hi - o[ax]);
+        }
+        if (!(half < NARROW_TILE))
+            flags |= WG_WIDE;
+        if (!top.w)
+            flags |= WG_IDS32;
+        wr = WgRec{fix_axis(o[0], 0.0f, a.fix), fix_axis(o[1], 0.0f, a.fix), fix_axis(o[2], 0.0f, a.fix), flags,
+                   first, tcnt, S, top.z, {0, 0, 0, 0}, {0, 0, 0, 0}};
+    }
+    // counts of passing and of written entries, times 512: entry c of the
+    // lane's row is at ring[(c mod 16) 256 + t]
+    unsigned c9 = 0u, f9 = 0u;
+    const unsigned t2 = 2u * (unsigned)t;
+    char *rg = reinterpret_cast<char *>(ring);
+    auto at = [&](unsigned k9) -> unsigned short & {
+        return *reinterpret_cast<unsigned short *>(rg + ((k9 & (unsigned)(512 * (R::RING - 1))) | t2));
+    };
+    constexpr unsigned PAD = 4u * (unsigned)SW;
+    auto flush = [&]() {
+        const unsigned e0 = at(f9), e1 = at(f9 + 512u), e2 = at(f9 + 1024u), e3 = at(f9 + 1536u);
+        dst[(size_t)(f9 >> 11) * 256] = make_uint2(e0 | (e1 << 16), e2 | (e3 << 16));
+        f9 += 2048u;
+    };
+    // one piece: its entries that pass, and for which `ok` holds, are appended
+    auto piece = [&](const uint4 &w, auto ok) {
+        const unsigned ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int h = 0; h < 8; h += 4) {  // four reads in flight, then their tests
+            unsigned e[4];
+            float4 pj[4];
+            bool use[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                e[u] = (ws[(h + u) >> 1] >> ((u & 1) * 16)) & 0xffffu;
+                unsigned o = e[u];
+                use[u] = ok(h + u, o);
+                const float *p = reinterpret_cast<const float *>(region + o);
+                pj[u] = make_float4(p[0], p[XS], p[2 * XS], 0.0f);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                at(c9) = (unsigned short)e[u];
+                c9 += within_cutoff(pi, pj[u], a.rc2) && use[u] ? 512u : 0u;
+            }
+        }
+        while (c9 - f9 >= 2048u)
+            flush();
+    };
+    if (S <= SW) {
+        // one window (nearly every tile): entries past the row's end are the
+        // far-away slot
+        for (int p = 0; p < np; ++p) {
+            const uint4 w = next;
+            next = src[(size_t)min(p + 1, np - 1) * 256];
+            piece(w, [](int, unsigned &) { return true; });
+        }
+    } else {
+        // window by window: the entries ascend, so a lane goes on where the
+        // window before ended
+        int p = 0;
+        for (int w0 = 0; w0 < S; w0 += SW) {
+            const int wn = min(SW, S - w0);
+            if (w0 > 0) {
+                __syncthreads();  // the previous window's readers are done
+                stage_window(w0, wn);
+                __syncthreads();
+            }
+            while (p < np) {
+                const uint4 w = src[(size_t)p * 256];
+                const int valid = len - 8 * p;
+                unsigned last = 0u;
+                piece(w, [&](int u, unsigned &o) {
+                    if (u < valid)
+                        last = o;
+                    o -= 4u * (unsigned)w0;
+                    const bool ok = u < valid && o < 4u * (unsigned)wn;
+                    o = ok ? o : 0u;
+                    return ok;
+                });
+                if (last >= 4u * (unsigned)(w0 + wn))
+                    break;  // the rest of the piece is in a later window
+                ++p;
+            }
+        }
+    }
+    const int m = (int)(c9 >> 9);
+    int nk = (m + 3) >> 2;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+        nk = max(nk, __shfl_xor(nk, off));
+    while ((int)(f9 >> 11) < nk) {
+        while (c9 < f9 + 2048u) {
+            at(c9) = (unsigned short)PAD;
+            c9 += 512u;
+        }
+        flush();
+    }
+    a.llen[wg * 256 + t] = (unsigned short)m;
+    if (t % NL == 0)
+        a.grho[wg * R::RW + t / NL] = (unsigned char)rho;
+    const int wave = nk | (min(top.x, rounds) << 16) | (rounds << 24);
+    int *wv = reinterpret_cast<int *>(bb);
+    __syncthreads();  // the box has been read, the staged positions too
+    if ((t & 63) == 0)
+        wv[t >> 6] = wave;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        wr.waves[k] = wv[k];
+    if (t == 0)
+        a.wg_rec[wg] = wr;
+    return m;
+}
+
+template <int TILE, int NL>
+__global__ __launch_bounds__(256, NL == 1 ? 2 : 5) void k_filter(FilterArgs a)
+{
+    using R = Rows<TILE, NL>;
+    __shared__ __align__(16) unsigned char region[R::BYTES];
+    __shared__ unsigned short ring[R::RING * 256];
+    __shared__ float bb[24];
+    const int wg = blockIdx.x, t = threadIdx.x;
+    const int tile = wg / R::W, part = wg % R::W;
+    // the cell counts are read only by the skin build, which is done: clear
+    // them for the next one; the flag is read only by the skin build too
+    for (int k = wg * 256 + t; k < a.n_cells; k += gridDim.x * 256)
+        a.cell_count[k] = 0;
+    if (wg == 0 && t == 0)
+        *a.skin_flag = 0u;
+    const int first = a.tile_first[tile], tcnt = a.tile_first[tile + 1] - first;
+    // the residue of this lane group: rows longest first
+    const int r = t / NL * R::W + part;
+    const bool in = r < tcnt;
+    const int rho = in ? ranked(a.skin_ord, (size_t)tile * TILE + r, r) : 0;
+    WgRec wr;
+    filter_rows<TILE, NL>(a, wg, tile, t, first, tcnt, in, rho, region, ring, bb, wr);
 }
 
 // ---------------------------------------------------------------------------
 // Canonical order after a skin search: a tile's slots are renumbered in the
-// order of their residues' global ids, and every skin row is rewritten in
-// ascending slot order, so each row lists its partners by ascending residue
-// id whatever the cell grid.  The list rows the filter derives keep that
-// order, so the order in which a residue's pair terms are summed depends on
-// its list alone, not on when or with which skin the last search ran.
+// order of their residues' global ids, and every skin row is dealt to its
+// residue's lanes by partner id, in ascending order, whatever the cell grid.
+// The list rows the filter derives keep that order, so the order in which a
+// residue's pair terms are summed depends on its list alone, not on when or
+// with which skin the last search ran.
 // ---------------------------------------------------------------------------
 struct CanonArgs {
     const int *tile_first;
     const int2 *trow;
     int *stage;
     const int *stage_cnt;
-    unsigned short *skin16;
+    const unsigned short *rows;  // the search's rows, by residue
     const int *skin_cnt;
-    uint2 *topo2;
+    const float2 *tent;
     const unsigned *skin_flag;
+    uint4 *skin16;
+    unsigned short *skin_len;
     unsigned short *skin_ord;
-    int cap;
+    uint2 *ltop;
+    int4 *tile_top;
+    unsigned short *stage16;
+    int cap, top_rounds;
 };
 
-template <int TILE>
+template <int TILE, int NL>
 __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
 {
+    using R = Rows<TILE, NL>;
+    constexpr int RW = R::RW, W = R::W;
     constexpr int SM = stage_max<TILE>();
-    constexpr int G = 32;           // residues per pass
-    constexpr int NLG = 256 / G;    // lanes per residue in a pass
-    constexpr int MW = SM / 32;     // mask words per residue
-    constexpr int MWP = MW + 1;     // their stride: a residue's word w in another bank than its neighbour's
+    constexpr int G = RW < 32 ? RW : 32;  // rows per pass
+    constexpr int NLG = 8;          // lanes reading one row
+    constexpr int MW = SM / 32;     // mask words per row
+    constexpr int MWP = MW + 1;     // their stride: a row's word w in another bank than its neighbour's
     constexpr int BW = 2048;        // bitmap words: ids spanning up to 65,536 values
     // the ranks (ids, bitmap, word prefixes) and the row masks use one
     // region in turn, so that three workgroups fit a CU
-    constexpr int P1 = (SM + 2 * BW) * 4, P2 = G * MWP * 4;
+    constexpr int P1 = (SM + 2 * BW) * 4, P2 = (G * MWP + NL * MW) * 4;
     __shared__ __align__(16) unsigned char region[P1 > P2 ? P1 : P2];
     int *sid = reinterpret_cast<int *>(region);
     unsigned *bmp = reinterpret_cast<unsigned *>(region + SM * 4);
     int *wpre = reinterpret_cast<int *>(region + (SM + BW) * 4);
     unsigned *mask = reinterpret_cast<unsigned *>(region);
+    unsigned *cmask = mask + G * MWP;
     __shared__ unsigned short nslot[SM];
+    __shared__ unsigned char cls[SM];
+    __shared__ short slen[TILE], sord[TILE];
     __shared__ int part[256];
     __shared__ int id_lo, id_hi;
     if (*a.skin_flag == 0u)
@@ -1306,209 +1357,614 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
         }
     }
     __syncthreads();
-    for (int k = t; k < S; k += 256)
+    for (int k = t; k < S; k += 256) {
         st[nslot[k]] = sid[k];
-    __syncthreads();  // the ids are dead: the region takes the masks
-    for (int g0 = 0; g0 < tcnt; g0 += G) {
-        const int rho = g0 + t / NLG, q = t % NLG;
-        const bool act = rho < tcnt && t / NLG < G;
-        for (int w = t; w < G * MWP; w += 256)
-            mask[w] = 0u;
-        __syncthreads();
-        int len = 0;
-        unsigned short *row = nullptr;
-        if (act) {
-            const int i = first + rho;
-            len = min(a.skin_cnt[i], a.cap);
-            row = a.skin16 + (size_t)i * a.cap;
-            // the row in 16-byte pieces (8 entries), pieces q, q + NLG, ...;
-            // the first CPF of them loaded up front
-            constexpr int CPF = 8;
-            const uint4 *rp = reinterpret_cast<const uint4 *>(row);
-            const int npc = (len + 7) >> 3;
-            uint4 pre[CPF];
-#pragma unroll
-            for (int m = 0; m < CPF; ++m)
-                pre[m] = m * NLG + q < npc ? rp[m * NLG + q] : make_uint4(0u, 0u, 0u, 0u);
-            for (int m = 0; m * NLG + q < npc; ++m) {
-                const int pc = m * NLG + q;
-                uint4 w;
-                if (m < CPF) {
-#pragma unroll
-                    for (int mm = 0; mm < CPF; ++mm)
-                        if (mm == m)
-                            w = pre[mm];
-                } else {
-                    w = rp[pc];
-                }
-                const unsigned ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (pc * 8 + u < len) {
-                        const int ns = nslot[(ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu];
-                        atomicOr(&mask[(t / NLG) * MWP + (ns >> 5)], 1u << (ns & 31));
-                    }
-                }
-            }
-            // bonded and native entries: renumber in place
-            const int2 rw = a.trow[i];
-            const int ntop = (rw.y & 4095) + (rw.y >> 12);
-            uint2 *tp = a.topo2 + (size_t)tile * TOPO_CAP * TILE + rho;
-            for (int e = q; e < ntop; e += NLG) {
-                const unsigned v = tp[(size_t)e * TILE].x;
-                if (v < (unsigned)S)
-                    tp[(size_t)e * TILE].x = nslot[v];
-            }
-        }
-        __syncthreads();
-        // emit: lane q scans words [q MW/NLG, (q+1) MW/NLG) of its residue's mask
-        constexpr int WPL = MW / NLG;
-        int c = 0;
-        if (act)
-            for (int w = q * WPL; w < (q + 1) * WPL; ++w)
-                c += __popc(mask[(t / NLG) * MWP + w]);
-        // entries before this lane's words: scan over the residue's lanes (adjacent)
-        int v = c;
-#pragma unroll
-        for (int off = 1; off < NLG; off <<= 1) {
-            const int y = __shfl_up(v, off, NLG);
-            if (q >= off)
-                v += y;
-        }
-        if (act) {
-            int o = v - c;
-            for (int w = q * WPL; w < (q + 1) * WPL; ++w) {
-                unsigned b = mask[(t / NLG) * MWP + w];
-                while (b) {
-                    const int kb = __ffs(b) - 1;
-                    b &= b - 1u;
-                    row[o++] = (unsigned short)(32 * w + kb);
-                }
-            }
-        }
-        __syncthreads();  // the masks are reused by the next pass
+        a.stage16[(size_t)tile * SM + nslot[k]] = (unsigned short)(sid[k] - lo);
+        cls[nslot[k]] = (unsigned char)(sid[k] & (NL - 1));
     }
-    // the filter hands the skin rows to its waves longest first, so that the
-    // rows a wave tests have about the same length (ties in index order)
-    int *slen = sid;  // the ids are written out
+    for (int k = S + t; k < max((S + 255) & ~255, STAGE_MIN); k += 256) {
+        st[k] = S > 0 ? lo : first;
+        a.stage16[(size_t)tile * SM + k] = 0;
+    }
+    // the rows are handed to the waves longest first, so that the rows of a
+    // wave have about the same length (ties in index order)
+    if (t == 0)
+        id_lo = id_hi = 0;  // most bonded / native entries of a residue
     for (int u = t; u < tcnt; u += 256)
-        slen[u] = min(a.skin_cnt[first + u], a.cap);
-    __syncthreads();
+        slen[u] = (short)min(a.skin_cnt[first + u], a.cap);
+    __syncthreads();  // the ids are dead: the region takes the masks
     for (int u = t; u < tcnt; u += 256) {
         const int L = slen[u];
         int r = 0;
         for (int v = 0; v < tcnt; ++v)
             r += (slen[v] > L || (slen[v] == L && v < u)) ? 1 : 0;
         a.skin_ord[(size_t)tile * TILE + r] = (unsigned short)(u + 1);
+        sord[r] = (short)u;
+        const int2 rw = a.trow[first + u];
+        atomicMax(&id_lo, rw.y & 4095);
+        atomicMax(&id_hi, rw.y >> 12);
+    }
+    // slots of each class (id modulo NL), as masks
+    const int nw = (S + 31) >> 5;
+    for (int x = t; x < nw * NL; x += 256) {
+        const int w = x / NL, c = x % NL;
+        unsigned m = 0u;
+        for (int b = 0; b < 32; ++b)
+            m |= (32 * w + b < S && cls[32 * w + b] == c) ? 1u << b : 0u;
+        cmask[c * MW + w] = m;
+    }
+    __syncthreads();
+    const int chunks = lane_chunks(a.cap, NL);
+    const int g = t / NL, q = t % NL;
+    for (int w = 0; w < W; ++w) {
+        const int wg = tile * W + w;
+        for (int g0 = 0; g0 < RW; g0 += G) {
+            // each row's partners as a mask over the slots, eight lanes a row
+            for (int x = t; x < G * MWP; x += 256)
+                mask[x] = 0u;
+            __syncthreads();
+            const int hr = (g0 + t / NLG) * W + w;  // rank of the row this lane reads
+            if (t / NLG < G && hr < tcnt) {
+                const int rho = sord[hr];
+                const int len = slen[rho];
+                const uint4 *rp = reinterpret_cast<const uint4 *>(a.rows + (size_t)(first + rho) * a.cap);
+                for (int pc = t % NLG; 8 * pc < len; pc += NLG) {
+                    const uint4 v = rp[pc];
+                    const unsigned ws[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        if (pc * 8 + u < len) {
+                            const int ns = nslot[(ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu];
+                            atomicOr(&mask[(t / NLG) * MWP + (ns >> 5)], 1u << (ns & 31));
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+            // each lane takes its partners, in ascending order
+            if (g >= g0 && g < g0 + G) {
+                const bool in = g * W + w < tcnt;
+                const unsigned *mk = mask + (g - g0) * MWP;
+                int mine = 0;
+                if (in)
+                    for (int x = 0; x < nw; ++x)
+                        mine += __popc(mk[x] & cmask[q * MW + x]);
+                int most = mine;
+#pragma unroll
+                for (int off = 1; off < NL; off <<= 1)
+                    most = max(most, __shfl_xor(most, off, NL));
+                const bool in_turn = most > 4 * chunks;
+                uint4 *dst = a.skin16 + (size_t)wg * (chunks / 2) * 256 + t;
+                unsigned acc[4] = {0u, 0u, 0u, 0u};
+                int c = 0, pos = 0;
+                auto put = [&](unsigned e) {
+                    const unsigned v = e << ((c & 1) * 16);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        acc[k] |= ((c >> 1) & 3) == k ? v : 0u;
+                    if ((++c & 7) == 0) {
+                        dst[(size_t)((c >> 3) - 1) * 256] = make_uint4(acc[0], acc[1], acc[2], acc[3]);
+                        acc[0] = acc[1] = acc[2] = acc[3] = 0u;
+                    }
+                };
+                if (in)
+                    for (int x = 0; x < nw; ++x) {
+                        unsigned b = in_turn ? mk[x] : mk[x] & cmask[q * MW + x];
+                        while (b) {
+                            const int kb = __ffs(b) - 1;
+                            b &= b - 1u;
+                            if (!in_turn || pos % NL == q)
+                                put(4u * (unsigned)(32 * x + kb));
+                            ++pos;
+                        }
+                    }
+                a.skin_len[wg * 256 + t] = (unsigned short)c;
+                while (c & 7)
+                    put(4u * (unsigned)R::SW);  // the far-away slot
+            }
+            __syncthreads();  // the masks are reused by the next pass
+        }
+        // bonded and native entries: bonded rounds, then native ones
+        const int kb = (id_lo + NL - 1) / NL, kn = (id_hi + NL - 1) / NL;
+        const int r = g * W + w;
+        const int rho = r < tcnt ? sord[r] : 0;
+        const int2 rw = r < tcnt ? a.trow[first + rho] : make_int2(0, 0);
+        const int nb = rw.y & 4095, ntop = nb + (rw.y >> 12);
+        if (t == 0)
+            a.tile_top[tile] = make_int4(kb, kn, S > 0 ? lo : first, S > 0 && span > 65536 ? 0 : 1);
+        for (int k = 0; k < max(kb + kn, TOP_MIN); ++k) {
+            const int e = k < kb ? q + k * NL : nb + q + (k - kb) * NL;
+            const bool has = e < (k < kb ? nb : ntop);
+            const float2 en = has ? a.tent[rw.x + e] : make_float2(__int_as_float(first + rho), 0.f);
+            // bonded: r0; native: r0^2
+            a.ltop[top_index(wg, k, t, a.top_rounds)] =
+                make_uint2((unsigned)__float_as_int(en.x), __float_as_uint(k < kb ? en.y : en.y * en.y));
+        }
     }
 }
 
+// In the order of use: the scalar loads of a wave's first lines bring what its
+// first loads need.
 struct TileArgs {
-    const int *tile_first;  // first residue of each tile, then n
-    const float4 *pin;
-    float4 *pout;
-    const int2 *trow;
-    const float2 *tent;
-    const unsigned short *list16;
-    const uint2 *topo2;
-    const int *list_cnt;
-    const int *stage;
-    const int *stage_cnt;
-    const unsigned *stream_ids;
+    const unsigned short *stage16;
+    const uint2 *ltop;
+    const unsigned char *grho;
+    const WgRec *wg_rec;
+    const long long *step_base;
+    long long step_off;
     const uint2 *noise_key;  // per residue {tag, stream id}
+    const float4 *pin;
+    const int4 *qin;        // fixed-point copies of the positions
+    const uint2 *list16;
+    const int *stage;
+    int n_wg, chunks, top_rounds, has_pull, do_bin;
+    FixDev fix;
+    StepConsts c;
+    UdConsts ud;
+    float check_thr2;
+    float4 *pout;
+    int4 *qout;
+    unsigned *err;
+    float4 *vel;          // underdamped: per-residue velocity (NULL: overdamped)
+    const unsigned short *llen;
     const int *pull_slot;
     const PullDev *pulls;
     double *res_energy;
     float4 *fout;
-    unsigned *err;
-    const long long *step_base;
+    TipDev tip;
+    // the last step of a list period checks the displacements and bins its
+    // new positions for the next skin search (do_bin)
     const float4 *hi_skin;
     unsigned *skin_flag;
-    const unsigned char *tile_ord;
-    float4 *vel;          // underdamped: per-residue velocity (NULL: overdamped)
-    // the last step of a list period bins its new positions for the next
-    // skin search (do_bin)
     const int4 *traj_cell;
     int *cell_count;
     float4 *cells;
     int *cell_of;
     GridDev g;
-    int do_bin;
-    long long step_off;
-    float check_thr2;
-    int n, cap, has_pull, n_tiles;
-    StepConsts c;
-    UdConsts ud;
-    TipDev tip;
-    // the first step of a list period filters the skin rows itself (FIRST):
-    // it writes the list rows, their counts and the longest-first order the
-    // later steps read, clears the cell counts and the skin flag
-    const unsigned short *skin16;
-    const int *skin_cnt;
-    const unsigned short *skin_ord;
-    unsigned short *list16_out;
-    int *list_cnt_out;
-    unsigned char *tile_ord_out;
-    float rc2;
-    int n_cells;
+    FilterArgs f;           // FIRST: the filter's arguments
 };
 
-// Position relative to the tile's origin O as an unevaluated sum rh + rl:
-// (hi - O) + lo by two error-free TwoSum steps, so rh + rl carries the
-// compensated position to about 2^-44 relative.
-__device__ __forceinline__ void tile_frame(const float4 &hi, const float4 &lo, const float4 &O, float4 &rh,
-                                           float4 &rl)
+// The value of lane xor `off` (1, 2, 4 or 8, the lower ones already summed
+// over, so that a mirror reaches an equal partner) by DPP: no LDS round trip.
+__device__ __forceinline__ float lane_xor(float v, int off)
 {
-    float h[3], l[3];
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        const float x = comp(hi, ax), o = comp(O, ax), xl = comp(lo, ax);
-        const float s = x - o;  // TwoSum(x, -o)
-        const float bb = s - x;
-        const float e = (x - (s - bb)) + (-o - bb);
-        const float t = e + xl;
-        const float r = s + t;  // TwoSum(s, t)
-        const float bp = r - s;
-        h[ax] = r;
-        l[ax] = (s - (r - bp)) + (t - bp);
-    }
-    rh = make_float4(h[0], h[1], h[2], 0.0f);
-    rl = make_float4(l[0], l[1], l[2], 0.0f);
+    const int x = __float_as_int(v);
+    const int y = off == 1   ? __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xf, 0xf, false)   // quad_perm 1 0 3 2
+                  : off == 2 ? __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xf, 0xf, false)   // quad_perm 2 3 0 1
+                  : off == 4 ? __builtin_amdgcn_update_dpp(x, x, 0x141, 0xf, 0xf, false)  // row_half_mirror
+                             : __builtin_amdgcn_update_dpp(x, x, 0x140, 0xf, 0xf, false); // row_mirror
+    return __int_as_float(y);
 }
 
-// The low part of a tile coordinate is at most half an ulp of the high part;
-// a staged slot keeps it as a 10-bit multiple of ulp/1000 per axis in the
-// high part's w word, so one 16-byte LDS read brings both.
+// The plain step: one workgroup of 256 lanes per 256 / NL residues of a tile,
+// NL adjacent lanes per residue, the tile's residues handed to the lanes
+// longest skin row first.  What bounds it is the number of instructions its
+// waves issue, so the pair loop holds one form and what can be done once a
+// period or once a step is.
+//  1. Every load at an address that needs no other load is issued first:
+//     the tile's slot ids, the lane's list chunks (4 slots each) and its
+//     bonded and native entries, all in lane order and so contiguous over a
+//     wave; the positions follow.
+//  2. Positions are read as fixed-point copies (16 bytes against the 32 of
+//     the compensated pair); their differences are exact integers, near and
+//     far from the origin.  Each lane evaluates its bonded and native
+//     entries from the two copies and stages slots: the copy relative to the
+//     workgroup's origin, rounded once to single precision.
+//     The last RW lanes draw their residue's Gaussians (Philox and
+//     Box-Muller, from the counter words that do not depend on the position)
+//     and evaluate its cantilever and tip terms.
+//  3. After the barrier the list chunks are summed from LDS.  Where the
+//     residues do not fit around one origin (wide), or the slots one window,
+//     the copies themselves are staged and subtracted.  A workgroup with a bonded or native pair out of the
+//     copies' reach (far), and a list whose cutoff is (list_far), take the
+//     compensated positions from memory.
+//     The NL partial sums of a residue are added by butterfly shuffles,
+//     which give every lane the same bits.
+//  4. After a second barrier the last RW lanes add the external terms and
+//     the noise and take the compensated step (first-order, or BAOAB).
+// FIRST (the first step after a rebuild, which then needs no filter kernel):
+// the list rows are filtered from the skin rows first (filter_rows): the same
+// rows, sums and bits as a filter kernel followed by a plain step.
+// Against rows by residue, 32-byte positions rounded to the tile's frame by
+// every reader and partners gathered through the rows (us a launch): 250,000
+// residues 40.7 -> 34.4, 75,000 13.5 -> 13.6, 20,000 8.2 -> 6.5, 4,801 at
+// protein density 22.2 -> 8.3, 1,000 10.3 -> 4.6, 56 4.6 -> 3.9; the first
+// step of a period at 75,000 38.1 -> 34.
+template <int TILE, int NL, bool ENERGY, int MODE, bool FIRST>
+__global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_step(TileArgs a)
+{
+    using R = Rows<TILE, NL>;
+    constexpr int RW = R::RW, W = R::W;
+    constexpr int SM = stage_max<TILE>();
+    constexpr int SW = R::SW, XS = R::XS;
+    constexpr int PER = 4;           // staging slots per lane loaded together
+    constexpr int EPI = 256 - RW;    // first lane of the update lanes
+    constexpr int NPRE = R::NPRE;    // list chunks per lane loaded before the staging
+    constexpr int TPRE = NL >= 16 ? 2 : (NL >= 8 ? 3 : TOP_MIN);  // bonded/native rounds loaded before the staging
+    __shared__ __align__(16) unsigned char region[R::BYTES];  // the slots' positions by axis
+    __shared__ unsigned short ring[FIRST ? R::RING * 256 : 1];
+    __shared__ float bb[FIRST ? 24 : 1];
+    __shared__ float f_s[3][RW];     // list + bonded/native force of each residue
+    __shared__ double e_s[ENERGY ? 4 : 1][ENERGY ? RW : 1];
+    if (FIRST) {
+        // the cell counts were read by the skin search, which is done:
+        // cleared for the binning at the end of this period; the flag too
+        for (int k = blockIdx.x * 256 + threadIdx.x; k < a.f.n_cells; k += gridDim.x * 256)
+            a.f.cell_count[k] = 0;
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            *a.f.skin_flag = 0u;
+    }
+    // XCD-aware order: consecutive tiles stay on one XCD's L2.
+    const int per = gridDim.x >> 3;
+    const int wg = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (wg >= a.n_wg)
+        return;  // uniform over the workgroup
+    const int t = threadIdx.x;
+    const int tile = wg / W, part = wg % W;
+    const int q = t % NL, g = t / NL;
+    // ---- 1. loads: straight-line, in the order in which they are needed,
+    // so that each wait is for its own load alone ----
+    const unsigned short *st16 = a.stage16 + (size_t)tile * SM;
+    const uint2 *tp = a.ltop + top_index(wg, 0, t, a.top_rounds);
+    const uint2 *lp = a.list16 + (size_t)wg * a.chunks * 256 + t;
+    int ids[PER];
+    uint2 te[TPRE], lw[NPRE];
+    int rho = 0;  // this lane group's residue in the tile
+    WgRec wr{};
+    if (FIRST) {
+        const int r = g * W + part;  // rank of this lane group's residue
+        const int first = a.f.tile_first[tile], tcnt = a.f.tile_first[tile + 1] - first;
+        const bool in = r < tcnt;
+        rho = in ? ranked(a.f.skin_ord, (size_t)tile * TILE + r, r) : 0;
+        filter_rows<TILE, NL>(a.f, wg, tile, t, first, tcnt, in, rho, region, ring, bb, wr);
+    } else {
+        rho = a.grho[wg * RW + g];
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        ids[u] = st16[t + u * 256];
+#pragma unroll
+    for (int k = 0; k < TPRE; ++k)
+        te[k] = tp[k * 256];
+    // update lanes: residues in order when the workgroup holds a whole tile
+    const int ue = t - EPI;
+    const int ru = ue * W + part;
+    int rhou = ue;
+    if (W > 1 && !FIRST)
+        rhou = a.grho[wg * RW + max(ue, 0)];
+    if (!FIRST)
+        wr = a.wg_rec[wg];
+    const long long step = (a.step_base ? *a.step_base : 0) + a.step_off;
+    const int first = wr.first, tcnt = wr.count, S = wr.slots;
+    const bool upd = ue >= 0 && ru < tcnt;
+    if (W > 1 && FIRST)  // this launch writes the groups' residues
+        rhou = upd ? ranked(a.f.skin_ord, (size_t)tile * TILE + ru, ru) : 0;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wave = wv == 0 ? wr.waves[0] : (wv == 1 ? wr.waves[1] : (wv == 2 ? wr.waves[2] : wr.waves[3]));
+    // this wave's list chunks, bonded rounds, all rounds
+    const int nk = wave & 0xffff, kb = (wave >> 16) & 0xff, kall = (int)((unsigned)wave >> 24);
+    const int i = first + rho;
+    const int iu = first + (upd ? rhou : 0);
+    const uint2 key = a.noise_key[iu];
+    float4 hu = a.pin[2 * iu], lu = a.pin[2 * iu + 1];
+    const int4 qi = a.qin[i];
+    // ---- 2. positions, noise and external terms (update lanes), bonded/native ----
+    const bool fast = !a.fix.list_far && !(wr.flags & WG_WIDE) && S <= SW;
+    float *sr = reinterpret_cast<float *>(region);  // x, y, z of slot s at s, XS + s, 2 XS + s
+    const int *st = a.stage + (size_t)tile * SM;
+    if (wr.flags & WG_IDS32) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            ids[u] = st[t + u * 256] - wr.base;
+    }
+    auto copy_of = [&](unsigned j) { return *reinterpret_cast<const int4 *>(reinterpret_cast<const char *>(a.qin) + (size_t)(j * 16u)); };
+    int4 v[PER], pq[TPRE];
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        v[u] = copy_of((unsigned)(ids[u] + wr.base));
+#pragma unroll
+    for (int k = 0; k < TPRE; ++k)
+        pq[k] = copy_of(te[k].x & ~FAR_ENTRY);
+    // the list chunks last: nothing needs them before the barrier
+#pragma unroll
+    for (int k = 0; k < NPRE; ++k)
+        lw[k] = lp[k * 256];
+    __builtin_amdgcn_sched_barrier(0);
+    if (fast) {
+        auto put = [&](int sl, const int4 &w) {
+            sr[sl] = (float)fix_diff(w.x, wr.ox) * a.fix.unit;
+            sr[XS + sl] = (float)fix_diff(w.y, wr.oy) * a.fix.unit;
+            sr[2 * XS + sl] = (float)fix_diff(w.z, wr.oz) * a.fix.unit;
+        };
+        if (FIRST)
+            __syncthreads();  // the staged positions of the filter are read
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            put(t + u * 256, v[u]);
+        for (int sl = t + PER * 256; sl < S; sl += 256)
+            put(sl, a.qin[st[sl]]);
+        if (t < 3)
+            sr[t * XS + SW] = 1.0e18f;  // the far-away slot
+    }
+    float gn[3] = {0.0f, 0.0f, 0.0f};
+    Acc X;
+    double e_x = 0.0, f_rep = 0.0;
+    if (upd) {
+        if (MODE == 0 && !(key.x >> 31)) {
+            const uint4 w = noise_words(key.x, key.y, step, a.c);
+            const float2 gxy = gaussian_pair(w);
+            gn[0] = gxy.x;
+            gn[1] = gxy.y;
+            gn[2] = gaussian_axis(w, 2);
+        }
+        add_external(X, e_x, f_rep, hu, lu, step, a.c.h, a.has_pull ? a.pull_slot[iu] : -1, a.pulls,
+                     a.tip, ENERGY, a.err);
+    }
+    const PairConsts k = pair_consts(a.c);
+    Acc A;   // bonded and native terms
+    {
+        // in fixed-point units unless a pair is out of the copies' range
+        const bool far = a.fix.bond_far || (wr.flags & WG_FAR);
+        const float eu = k.eh12 * a.fix.unit;
+        bool broken = false;
+        auto diff = [&](const int4 &p) {
+            return make_float3((float)fix_diff(qi.x, p.x), (float)fix_diff(qi.y, p.y), (float)fix_diff(qi.z, p.z));
+        };
+        auto out_of_range = [&](unsigned x) { return far && (a.fix.bond_far || x >= FAR_ENTRY); };
+        auto delta = [&](unsigned x) {
+            const unsigned j = x & ~FAR_ENTRY;
+            return pair_delta(a.pin[2 * i], a.pin[2 * i + 1], a.pin[2 * j], a.pin[2 * j + 1]);
+        };
+        auto bond = [&](const uint2 &e, const int4 &p) {
+            if (e.x != (unsigned)i) {
+                const float3 d = diff(p);
+                add_fene_d(A, out_of_range(e.x) ? delta(e.x)
+                                                : make_float3(d.x * a.fix.unit, d.y * a.fix.unit, d.z * a.fix.unit),
+                           __uint_as_float(e.y), k, ENERGY, broken);
+            }
+        };
+        auto native = [&](const uint2 &e, const int4 &p) {
+            if (e.x != (unsigned)i) {
+                if (out_of_range(e.x))
+                    add_native_d(A, delta(e.x), __uint_as_float(e.y), k, ENERGY);
+                else
+                    add_native_q(A, diff(p), __uint_as_float(e.y), a.fix.s2, eu, k, ENERGY);
+            }
+        };
+        int rd = 0;
+        if (kb == 1) {  // as in every chain of two neighbours a residue
+            bond(te[0], pq[0]);
+#pragma unroll
+            for (int u = 1; u < TPRE; ++u)
+                if (u < kall)
+                    native(te[u], pq[u]);
+            rd = TPRE;
+        }
+        for (; rd < kall; ++rd) {
+            const uint2 e = tp[rd * 256];
+            const int4 p = copy_of(e.x & ~FAR_ENTRY);
+            if (rd < kb)
+                bond(e, p);
+            else
+                native(e, p);
+        }
+        if (broken)
+            atomicOr(a.err, ERR_FENE);
+    }
+    __syncthreads();
+    // the binning's slot and the displacement check's reference, requested
+    // now so that they arrive during the sums
+    float4 hsk = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (MODE == 0 && upd && a.check_thr2 > 0.0f)
+        hsk = a.hi_skin[iu];
+    // the last step of a list period bins the new positions for the next
+    // skin search; the cell slot is taken in the cell of the position before
+    // the update (nearly always the cell of the new one), so the atomic's
+    // round trip overlaps the step.  The lanes of a wave that bin into one
+    // cell take consecutive slots from one atomic, issued by the group's
+    // first lane (uniform branch: the whole wave takes part in the ballots).
+    // The first step of a period never bins (it clears the cell counts the
+    // binning at the period's end fills; a period's first step is not its last)
+    const bool do_bin = MODE == 0 && !FIRST && a.do_bin;
+    int bin_lead = 0, bin_rank = 0, bin_base = 0;
+    int bin_c0 = -1;           // the cell of the position before the update
+    int4 bin_off = {0, 0, 0, 0};  // the trajectory's cell offset, kept for after the update
+    if (do_bin) {
+        const bool binning = upd;
+        if (binning)
+            bin_off = a.traj_cell[__float_as_int(lu.w)];
+        const int c0 = binning ? cell_index(hu, bin_off, a.g) : -1;
+        bin_c0 = c0;
+        const int lane = (int)__lane_id();
+        const unsigned long long below = (1ull << lane) - 1ull;
+        unsigned long long todo = __ballot(binning);
+        unsigned long long mine = 0ull;
+        while (todo) {
+            const int lead = __ffsll((long long)todo) - 1;
+            const int cl = __shfl(c0, lead);
+            const unsigned long long same = __ballot(binning && c0 == cl) & todo;
+            if ((same >> lane) & 1ull) {
+                bin_lead = lead;
+                bin_rank = __popcll(same & below);
+            }
+            if (lane == lead)
+                mine = same;
+            todo &= ~same;
+        }
+        if (binning && lane == bin_lead)
+            bin_base = atomicAdd(&a.cell_count[c0], __popcll(mine));
+    }
+    // ---- 3. list partners ----
+    Acc L;   // sum of d / r^8 (scaled below)
+    float lscale = k.c6;
+    auto entry = [](const uint2 &w, int u) { return ((u < 2 ? w.x : w.y) >> ((u & 1) * 16)) & 0xffffu; };
+    if (fast) {
+        const float xi = (float)fix_diff(qi.x, wr.ox) * a.fix.unit, yi = (float)fix_diff(qi.y, wr.oy) * a.fix.unit,
+                    zi = (float)fix_diff(qi.z, wr.oz) * a.fix.unit;
+        auto chunk = [&](const uint2 &w) {
+            float3 d[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float *p = reinterpret_cast<const float *>(region + entry(w, u));
+                d[u] = make_float3(xi - p[0], yi - p[XS], zi - p[2 * XS]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                add_repulsive_u(L, d[u], k, ENERGY);
+        };
+#pragma unroll
+        for (int kk = 0; kk < NPRE; ++kk)
+            if (kk < nk)
+                chunk(lw[kk]);
+        if (nk > NPRE) {
+            uint2 next = lp[NPRE * 256];
+            for (int c = NPRE; c < nk; ++c) {
+                const uint2 w = next;
+                next = lp[min(c + 1, nk - 1) * 256];  // requested before this one is used
+                chunk(w);
+            }
+        }
+    } else if (!a.fix.list_far) {
+        // the copies, window by window: the entries ascend, so a lane goes
+        // on where the window before ended
+        lscale = k.c6 * a.fix.unit;
+        const int m = a.llen[wg * 256 + t];
+        int *sq = reinterpret_cast<int *>(region);
+        int c = 0;
+        for (int w0 = 0; w0 < S; w0 += SW) {
+            __syncthreads();  // the previous window's readers are done
+            for (int sl = t; sl < min(SW, S - w0); sl += 256) {
+                const int4 w = a.qin[st[w0 + sl]];
+                sq[sl] = w.x;
+                sq[XS + sl] = w.y;
+                sq[2 * XS + sl] = w.z;
+            }
+            __syncthreads();
+            while (4 * c < m) {
+                const uint2 w = lp[c * 256];
+                unsigned far_end = 0u;
+                int3 d[4];
+                bool live[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const unsigned o = entry(w, u) - 4u * (unsigned)w0;
+                    const bool has = 4 * c + u < m;
+                    far_end |= has && entry(w, u) >= 4u * (unsigned)(w0 + SW) ? 1u : 0u;
+                    live[u] = has && o < 4u * (unsigned)SW;
+                    const int *p = reinterpret_cast<const int *>(region + (live[u] ? o : 0u));
+                    d[u] = make_int3(fix_diff(qi.x, p[0]), fix_diff(qi.y, p[XS]), fix_diff(qi.z, p[2 * XS]));
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    add_repulsive_q(L, d[u], a.fix.s2, k, live[u], ENERGY);
+                if (far_end)
+                    break;  // the rest of the chunk is in a later window
+                ++c;
+            }
+        }
+    } else {
+        const float4 hi0 = a.pin[2 * i], lo0 = a.pin[2 * i + 1];
+        const int m = a.llen[wg * 256 + t];
+        for (int e = 0; e < m; ++e) {
+            const int j = st[entry(lp[(e >> 2) * 256], e & 3) >> 2];
+            add_repulsive_u(L, pair_delta(hi0, lo0, a.pin[2 * j], a.pin[2 * j + 1]), k, ENERGY);
+        }
+    }
+    // the residue's total over its NL lanes (butterfly: every lane gets the same bits)
+    float fx = lscale * L.fx + A.fx, fy = lscale * L.fy + A.fy, fz = lscale * L.fz + A.fz;
+    double eb = A.e_b, en = A.e_n, er = L.e_r, vir = A.vir + L.vir;
+#pragma unroll
+    for (int off = 1; off < NL; off <<= 1) {
+        fx += lane_xor(fx, off);
+        fy += lane_xor(fy, off);
+        fz += lane_xor(fz, off);
+        if (ENERGY) {
+            eb += __shfl_xor(eb, off, NL);
+            en += __shfl_xor(en, off, NL);
+            er += __shfl_xor(er, off, NL);
+            vir += __shfl_xor(vir, off, NL);
+        }
+    }
+    if (q == 0 && g * W + part < tcnt) {
+        const int fs = W > 1 ? g : rho;  // the update lane of this residue
+        f_s[0][fs] = fx;
+        f_s[1][fs] = fy;
+        f_s[2][fs] = fz;
+        if constexpr (ENERGY) {
+            e_s[0][fs] = eb;
+            e_s[1][fs] = en;
+            e_s[2][fs] = er;
+            e_s[3][fs] = vir;
+        }
+    }
+    // this residue's slot in its cell (the group's atomic has returned)
+    int bin_s0 = 0;
+    if (do_bin)
+        bin_s0 = __shfl(bin_base, bin_lead) + bin_rank;
+    __syncthreads();
+    if (!upd)
+        return;
+    // ---- 4. external terms, noise and the compensated update ----
+    Acc F;
+    F.fx = f_s[0][ue] + X.fx;
+    F.fy = f_s[1][ue] + X.fy;
+    F.fz = f_s[2][ue] + X.fz;
+    if constexpr (ENERGY) {
+        double *er_out = a.res_energy + (size_t)iu * RES_E;
+        // each internal pair appears in both partners' rows
+        er_out[0] = 0.5 * e_s[0][ue];
+        er_out[1] = 0.5 * e_s[1][ue];
+        er_out[2] = 0.5 * e_s[2][ue];
+        er_out[3] = e_x;
+        er_out[4] = 0.5 * e_s[3][ue];
+        er_out[5] = f_rep;
+    }
+    if (MODE == 1) {
+        a.fout[iu] = make_float4(F.fx, F.fy, F.fz, 0.0f);
+        return;
+    }
+    float4 hi = hu, lo = lu;
+    if (a.vel) {
+        float4 v = a.vel[iu];
+        underdamped_update(hi, lo, v, F, gn, a.ud, a.err);
+        a.vel[iu] = v;
+    } else {
+        update_with_noise(hi, lo, F, gn, a.c, a.err);
+    }
+    a.pout[2 * iu] = hi;
+    a.pout[2 * iu + 1] = lo;
+    a.qout[iu] = fix_pos(hi, lo, a.fix);
+    if (a.check_thr2 > 0.0f) {
+        // moved farther than skin/2 from the last skin build: the next
+        // rebuild rebuilds the skin
+        const float dx = hi.x - hsk.x, dy = hi.y - hsk.y, dz = hi.z - hsk.z;
+        if (!(dx * dx + dy * dy + dz * dz <= a.check_thr2))
+            atomicOr(a.skin_flag, 1u);
+    }
+    if (do_bin) {
+        const int traj = __float_as_int(lo.w);
+        const int c1 = cell_index(hi, bin_off, a.g);
+        if (c1 == bin_c0) {
+            a.cell_of[iu] = c1;
+            if (bin_s0 < CELL_CAP)
+                a.cells[(size_t)c1 * CELL_CAP + bin_s0] = make_float4(hi.x, hi.y, hi.z, __int_as_float(iu));
+            else
+                atomicOr(a.err, ERR_CELL);
+        } else {
+            // moved into another cell: the slot taken holds a far-away copy
+            // (no predicate passes it; the id keeps the cell's ids distinct)
+            // and the residue is binned again
+            if (bin_s0 < CELL_CAP)
+                a.cells[(size_t)bin_c0 * CELL_CAP + bin_s0] =
+                    make_float4(1.0e18f, 1.0e18f, 1.0e18f, __int_as_float(iu));
+            bin_one(hi, iu, traj, a.g, a.traj_cell, a.cell_count, a.cells, a.cell_of, a.err);
+        }
+    }
+}
+
 __device__ __forceinline__ float ulp_of(float x)
 {
     return __int_as_float(__float_as_int(x) & 0x7f800000) * 0x1p-23f;
-}
-
-__device__ __forceinline__ unsigned pack_low(const float4 &rh, const float4 &rl)
-{
-    unsigned bitsw = 0u;
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        // 1/ulp is a power of two: biased exponent 277 - E for exponent field E
-        const int E = (__float_as_int(comp(rh, ax)) >> 23) & 0xff;
-        const float inv_u = (E >= 24 && E <= 253) ? __int_as_float((277 - E) << 23) : 0.0f;
-        const float v = comp(rl, ax) * inv_u * 1000.0f;
-        const int qv = (int)rintf(fminf(fmaxf(v, -511.0f), 511.0f));
-        bitsw |= ((unsigned)qv & 0x3ffu) << (10 * ax);
-    }
-    return bitsw;
-}
-
-__device__ __forceinline__ float3 unpack_low(const float4 &s)
-{
-    const unsigned w = __float_as_uint(s.w);
-    float l[3];
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        const int qv = ((int)(w << (22 - 10 * ax))) >> 22;  // sign-extended 10-bit field
-        l[ax] = (float)qv * (ulp_of(comp(s, ax)) * 1.0e-3f);
-    }
-    return make_float3(l[0], l[1], l[2]);
 }
 
 // Batched schedule: each residue packs its low part in units of one quantum,
@@ -1547,563 +2003,6 @@ __device__ __forceinline__ float3 pair_delta_packed(const float4 &hi, const floa
     return make_float3(d[0], d[1], d[2]);
 }
 
-// A tile whose residues all lie within this distance of its origin has its
-// list partners (within r_list = 20 A of one of them at the rebuild, a few
-// tenths of an Angstrom more after ten steps) within about 64 A of it, so
-// list pairs use the high parts alone (separation error about 8e-6 A at most); other
-// tiles add the low parts.  The test reads the tile's own residues only, so
-// the arithmetic does not depend on which other residues are staged.
-constexpr float NARROW_TILE = 40.0f;
-
-// The plain step: one workgroup of 256 lanes per tile of TILE consecutive
-// residues, NL = 256/TILE adjacent lanes per residue, the tile's residues
-// handed to the lanes longest list row first.
-//  1. Every load that does not need the staging is issued first: the
-//     residue's own position and row, its first PRE list chunks (4 slots
-//     each: chunks q, q + NL, ... for lane q), its first bonded/native
-//     entries and their partners' compensated positions, and the tile's
-//     slot ids.
-//  2. The last TILE lanes draw their residue's Gaussians (Philox and
-//     Box-Muller, from the counter words that do not depend on the
-//     position) and evaluate its cantilever and tip terms; every lane stages
-//     slots (each position relative to the tile origin, its middle residue,
-//     as the exactly rounded high part of a TwoSum split) and evaluates its
-//     bonded and native entries from the compensated positions.
-//  3. After the barrier the list chunks are summed from the staged
-//     positions: high parts only when every residue of the tile lies within
-//     NARROW_TILE of the origin, else high and low parts (the low parts, a
-//     10-bit multiple of the high part's ulp per axis, are staged then).
-//     The NL partial sums of a residue are added by butterfly shuffles,
-//     which give every lane the same bits.
-//  4. After a second barrier the last TILE lanes add the external terms and
-//     the noise and take the compensated step (first-order, or BAOAB).
-// FIRST (the first step after a rebuild, which then needs no filter kernel):
-// the rows read are the skin rows, in the order of the last skin search
-// (longest first); the staging also keeps each slot's global high part, and
-// after the barrier each residue's lanes test their skin row pieces with the
-// list predicate and write the passing entries, in order, as its list row,
-// which the list sums then read back: the same rows, sums and bits as a
-// filter kernel followed by a plain step.
-template <int TILE, bool ENERGY, int MODE, bool FIRST>
-__global__ __launch_bounds__(256, ENERGY ? 2 : (TILE >= 256 ? 3 : 5)) void k_tile_step(TileArgs a)
-{
-    constexpr int NL = 256 / TILE;
-    constexpr int SM = stage_max<TILE>();
-    constexpr int SW = stage_win<TILE>();
-    constexpr int PER = SW / 256;    // staging slots per lane
-    constexpr int EPI = 256 - TILE;  // first lane of the update lanes
-    constexpr int PRE = 6;           // list chunks per lane loaded before the staging
-    constexpr int TPRE = 2;          // bonded/native entries per lane loaded before the staging
-    __shared__ float4 sl_s[SW + 1];  // {rh.xyz, packed rl}; slot SW: the far-away empty slot
-    // SOA: the same high parts by axis, read by the list sums of compact
-    // tiles: three 4-byte reads a partner spread over all banks, where
-    // 16-byte elements start on one bank in four (not in the first step or
-    // with 2,048-slot windows, short of LDS)
-    constexpr bool SOA = !FIRST && SW <= 1024;
-    __shared__ float sr_s[3][SOA ? SW + 1 : 1];
-    __shared__ float hg_s[3][FIRST ? SW : 1];  // FIRST: each slot's global high part, by axis
-    __shared__ int lens_s[FIRST ? TILE : 1];    // FIRST: list row lengths
-    __shared__ float f_s[3][TILE];   // list + bonded/native force of each residue
-    __shared__ double e_s[ENERGY ? 4 : 1][ENERGY ? TILE : 1];
-    if (FIRST) {
-        // the cell counts were read by the skin search, which is done:
-        // cleared for the binning at the end of this period; the flag too
-        for (int k = blockIdx.x * 256 + threadIdx.x; k < a.n_cells; k += gridDim.x * 256)
-            a.cell_count[k] = 0;
-        if (blockIdx.x == 0 && threadIdx.x == 0)
-            *a.skin_flag = 0u;
-    }
-    // XCD-aware order: consecutive tiles stay on one XCD's L2.
-    const int per = gridDim.x >> 3;
-    const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if (tile >= a.n_tiles)
-        return;  // uniform over the workgroup
-    const int t = threadIdx.x;
-    const int first = a.tile_first[tile], tcnt = a.tile_first[tile + 1] - first;
-    const int S = min(a.stage_cnt[tile], SM);
-    const int *st = a.stage + (size_t)tile * SM;
-    // rare: a staging set larger than one LDS window is taken window by window
-    const bool windowed = S > SW;
-    const int mid = first + tcnt / 2;
-    const long long step = (a.step_base ? *a.step_base : 0) + a.step_off;
-    const int q = t % NL;
-    const bool act = t / NL < tcnt;
-    int rho = 0;
-    if (FIRST) {
-        const int ord = act ? (int)a.skin_ord[(size_t)tile * TILE + t / NL] : 0;
-        rho = act ? (ord > 0 ? ord - 1 : t / NL) : 0;
-    } else {
-        rho = act ? (int)a.tile_ord[(size_t)tile * TILE + t / NL] : 0;
-    }
-    const int i = first + rho;
-    const int ue = t - EPI;
-    const bool upd = ue >= 0 && ue < tcnt;
-    const int iu = first + ue;
-    // ---- 1. loads ----
-    int ids[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u)
-        ids[u] = (!windowed && t + u * 256 < S) ? st[t + u * 256] : -1;
-    float4 hi0 = make_float4(0.f, 0.f, 0.f, 0.f), lo0 = hi0;
-    int2 row = make_int2(0, 0);
-    int cnt = 0;
-    int slen = 0;  // FIRST: the skin row's length
-    if (act) {
-        hi0 = a.pin[2 * i];
-        lo0 = a.pin[2 * i + 1];
-        row = a.trow[i];
-        if (FIRST)
-            slen = min(a.skin_cnt[i], a.cap);
-        else
-            cnt = min(a.list_cnt[i], a.cap);
-    }
-    const float4 O = a.pin[2 * mid];
-    int nch = (cnt + 3) >> 2;
-    const uint2 *lp = reinterpret_cast<const uint2 *>(a.list16 + (size_t)i * a.cap);
-    constexpr int NPRE = FIRST ? 3 : PRE;
-    uint2 lw[NPRE];
-    constexpr int SPF = 1;  // FIRST: skin row pieces (8 entries) loaded up front
-    uint4 spre[SPF];
-    const uint4 *sp = reinterpret_cast<const uint4 *>(FIRST ? a.skin16 + (size_t)i * a.cap : nullptr);
-    const int npc = (slen + 7) >> 3;
-    if (FIRST) {
-#pragma unroll
-        for (int m = 0; m < SPF; ++m)
-            spre[m] = m * NL + q < npc ? sp[m * NL + q] : make_uint4(0u, 0u, 0u, 0u);
-    } else {
-#pragma unroll
-        for (int k = 0; k < NPRE; ++k)
-            lw[k] = q + k * NL < nch ? lp[q + k * NL] : make_uint2(0u, 0u);
-    }
-    const int nb = row.y & 4095, ntop = nb + (row.y >> 12);
-    // bonded entries: lane q takes bonds q, q + NL, ... and natives nb + q,
-    // nb + q + NL, ..., in loops of their own so that a wave runs each
-    // term's code once a round; its first bond and first TPRE - 1 natives
-    // are loaded here
-    float2 te[TPRE];
-#pragma unroll
-    for (int k = 0; k < TPRE; ++k) {
-        const int e = k == 0 ? q : nb + q + (k - 1) * NL;
-        te[k] = (k == 0 ? e < nb : e < ntop) ? a.tent[row.x + e] : make_float2(0.f, 0.f);
-    }
-    float4 ph[TPRE], pl[TPRE];
-#pragma unroll
-    for (int k = 0; k < TPRE; ++k) {
-        const int e = k == 0 ? q : nb + q + (k - 1) * NL;
-        if (k == 0 ? e < nb : e < ntop) {
-            const int j = __float_as_int(te[k].x);
-            ph[k] = a.pin[2 * j];
-            pl[k] = a.pin[2 * j + 1];
-        }
-    }
-    // ---- 2. noise and external terms (update lanes), staging, bonded/native ----
-    float4 hu = make_float4(0.f, 0.f, 0.f, 0.f), lu = hu;
-    float g[3] = {0.0f, 0.0f, 0.0f};
-    Acc X;
-    double e_x = 0.0, f_rep = 0.0;
-    // the last step of a list period bins the new positions for the next
-    // skin search; the cell slot is taken in the cell of the position before
-    // the update (nearly always the cell of the new one), so the atomic's
-    // round trip overlaps the step
-    if (upd) {
-        hu = a.pin[2 * iu];
-        lu = a.pin[2 * iu + 1];
-        if (MODE == 0) {
-            const uint2 key = a.noise_key[iu];
-            if (!(key.x >> 31)) {
-                const uint4 w = noise_words(key.x, key.y, step, a.c);
-                const float2 gxy = gaussian_pair(w);
-                g[0] = gxy.x;
-                g[1] = gxy.y;
-                g[2] = gaussian_axis(w, 2);
-            }
-        }
-        add_external(X, e_x, f_rep, hu, lu, step, a.c.h, a.has_pull ? a.pull_slot[iu] : -1, a.pulls,
-                     a.tip, ENERGY, a.err);
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        if (ids[u] >= 0) {
-            const float4 gh = a.pin[2 * ids[u]];
-            float4 rh, rl;
-            tile_frame(gh, a.pin[2 * ids[u] + 1], O, rh, rl);
-            rh.w = 0.0f;
-            sl_s[t + u * 256] = rh;
-            if (SOA) {
-                sr_s[0][t + u * 256] = rh.x;
-                sr_s[1][t + u * 256] = rh.y;
-                sr_s[2][t + u * 256] = rh.z;
-            }
-            if (FIRST) {
-                hg_s[0][t + u * 256] = gh.x;
-                hg_s[1][t + u * 256] = gh.y;
-                hg_s[2][t + u * 256] = gh.z;
-            }
-        }
-    }
-    if (t == 0) {
-        sl_s[SW] = make_float4(1.0e18f, 1.0e18f, 1.0e18f, 0.0f);
-        if (SOA)
-            sr_s[0][SW] = sr_s[1][SW] = sr_s[2][SW] = 1.0e18f;
-    }
-
-    const PairConsts k = pair_consts(a.c);
-    Acc A;   // bonded and native terms
-    bool broken = false;
-    if (act) {
-        if (q < nb)
-            add_fene_d(A, pair_delta(hi0, lo0, ph[0], pl[0]), te[0].y, k, ENERGY, broken);
-        for (int e = q + NL; e < nb; e += NL) {
-            const float2 tv = a.tent[row.x + e];
-            const int j = __float_as_int(tv.x);
-            add_fene_d(A, pair_delta(hi0, lo0, a.pin[2 * j], a.pin[2 * j + 1]), tv.y, k, ENERGY, broken);
-        }
-#pragma unroll
-        for (int kk = 1; kk < TPRE; ++kk)
-            if (nb + q + (kk - 1) * NL < ntop)
-                add_native_d(A, pair_delta(hi0, lo0, ph[kk], pl[kk]), te[kk].y, k, ENERGY);
-        for (int e = nb + q + (TPRE - 1) * NL; e < ntop; e += NL) {
-            const float2 tv = a.tent[row.x + e];
-            const int j = __float_as_int(tv.x);
-            add_native_d(A, pair_delta(hi0, lo0, a.pin[2 * j], a.pin[2 * j + 1]), tv.y, k, ENERGY);
-        }
-        if (broken)
-            atomicOr(a.err, ERR_FENE);
-    }
-    float4 rh0, rl0;
-    tile_frame(hi0, lo0, O, rh0, rl0);
-    const bool far = windowed || (act && !(fmaxf(fabsf(rh0.x), fmaxf(fabsf(rh0.y), fabsf(rh0.z))) < NARROW_TILE));
-    const bool wide = __syncthreads_or(far ? 1 : 0) != 0;
-    if (wide && !windowed) {
-        // rare: the low parts of the staged positions, packed beside them
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            if (ids[u] >= 0) {
-                float4 rh, rl;
-                tile_frame(a.pin[2 * ids[u]], a.pin[2 * ids[u] + 1], O, rh, rl);
-                sl_s[t + u * 256].w = __uint_as_float(pack_low(rh, rl));
-            }
-        }
-        rh0.w = __uint_as_float(pack_low(rh0, rl0));
-        __syncthreads();
-    }
-    if (windowed)
-        rh0.w = __uint_as_float(pack_low(rh0, rl0));
-    // the binning's slot and the displacement check's reference, requested
-    // now so that they arrive during the list sums
-    float4 hsk = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (MODE == 0 && upd && a.check_thr2 > 0.0f)
-        hsk = a.hi_skin[iu];
-    // the lanes of a wave that bin into one cell take consecutive slots
-    // from one atomic, issued by the group's first lane (uniform branch:
-    // the whole wave takes part in the ballots)
-    // the first step of a period never bins (it clears the cell counts the
-    // binning at the period's end fills; a period's first step is not its last)
-    const bool do_bin = MODE == 0 && !FIRST && a.do_bin;
-    int bin_lead = 0, bin_rank = 0, bin_base = 0;
-    int bin_c0 = -1;           // the cell of the position before the update
-    int4 bin_off = {0, 0, 0, 0};  // the trajectory's cell offset, kept for after the update
-    if (do_bin) {
-        const bool binning = upd;
-        if (binning)
-            bin_off = a.traj_cell[__float_as_int(lu.w)];
-        const int c0 = binning ? cell_index(hu, bin_off, a.g) : -1;
-        bin_c0 = c0;
-        const int lane = (int)__lane_id();
-        const unsigned long long below = (1ull << lane) - 1ull;
-        unsigned long long todo = __ballot(binning);
-        unsigned long long mine = 0ull;
-        while (todo) {
-            const int lead = __ffsll((long long)todo) - 1;
-            const int cl = __shfl(c0, lead);
-            const unsigned long long same = __ballot(binning && c0 == cl) & todo;
-            if ((same >> lane) & 1ull) {
-                bin_lead = lead;
-                bin_rank = __popcll(same & below);
-            }
-            if (lane == lead)
-                mine = same;
-            todo &= ~same;
-        }
-        if (binning && lane == bin_lead)
-            bin_base = atomicAdd(&a.cell_count[c0], __popcll(mine));
-    }
-    if (FIRST) {
-        // ---- the list rows, filtered from the skin rows (Algorithm 3's
-        // predicate at r_list) and written in order ----
-        // ONE (compile time): the set fits one LDS window, as for nearly
-        // every tile; the round loop below is compiled once for each case
-        auto test = [&](const uint4 &w, int pc, auto one) -> unsigned {
-            constexpr bool ONE = decltype(one)::value;
-            const unsigned ws[4] = {w.x, w.y, w.z, w.w};
-            const int valid = slen - pc * 8;
-            const unsigned tail = valid >= 8 ? 0xffu : (valid > 0 ? (1u << valid) - 1u : 0u);
-            unsigned bits = 0u;
-#pragma unroll
-            for (int h = 0; h < 8; h += 4) {  // four reads in flight, then their tests
-                float4 pj[4];
-#pragma unroll
-                for (int u = h; u < h + 4; ++u) {
-                    const unsigned sl = (ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu;
-                    if constexpr (ONE) {
-                        // entries past the row's end (masked) clamped into the set
-                        const int e = (int)min(sl, (unsigned)(SW - 1));
-                        pj[u - h] = make_float4(hg_s[0][e], hg_s[1][e], hg_s[2][e], 0.0f);
-                    } else {
-                        // rare: a set larger than one window reads the positions themselves
-                        pj[u - h] = a.pin[2 * st[min(sl, (unsigned)(SM - 1))]];
-                    }
-                }
-#pragma unroll
-                for (int u = h; u < h + 4; ++u)
-                    bits |= (unsigned)within_cutoff(hi0, pj[u - h], a.rc2) << u;
-            }
-            return bits & tail;
-        };
-        unsigned short *dst = a.list16_out + (size_t)i * a.cap;
-        int rounds = (npc + NL - 1) / NL;
-#pragma unroll
-        for (int off = 1; off < NL; off <<= 1)
-            rounds = max(rounds, __shfl_xor(rounds, off, NL));  // uniform over the residue's lanes
-        int base = 0;
-        // lane q's piece of this round: its passing entries go after those
-        // of the residue's earlier pieces
-        auto emit = [&](const uint4 &w, unsigned bits) {
-            const unsigned ws[4] = {w.x, w.y, w.z, w.w};
-            const int c = __popc(bits);
-            int v = c;
-#pragma unroll
-            for (int off = 1; off < NL; off <<= 1) {
-                const int y = __shfl_up(v, off, NL);
-                if (q >= off)
-                    v += y;
-            }
-            // entry u goes after the passing entries below it: eight masked
-            // stores, not a loop as long as the wave's longest run
-            unsigned short *d = dst + (base + v - c);
-#pragma unroll 1
-            for (int h = 0; h < 2; ++h) {  // the piece's two halves, four entries each
-                const unsigned w0 = h ? ws[2] : ws[0], w1 = h ? ws[3] : ws[1];
-                const unsigned hb = bits >> (4 * h);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if ((hb >> u) & 1u)
-                        d[__popc(hb & ((1u << u) - 1u))] = (unsigned short)((u < 2 ? w0 : w1) >> ((u & 1) * 16));
-                d += __popc(hb & 0xfu);
-            }
-            base += __shfl(v, NL - 1, NL);
-        };
-        auto filter_rows = [&](auto one) {
-#pragma unroll
-            for (int m = 0; m < SPF; ++m)
-                if (m < rounds)
-                    emit(spre[m], m * NL + q < npc ? test(spre[m], m * NL + q, one) : 0u);
-            // later pieces: the next one requested before the current one is used
-            uint4 wn = SPF * NL + q < npc ? sp[SPF * NL + q] : make_uint4(0u, 0u, 0u, 0u);
-            for (int m = SPF; m < rounds; ++m) {
-                const int pc = m * NL + q;
-                const uint4 w = wn;
-                wn = pc + NL < npc ? sp[pc + NL] : make_uint4(0u, 0u, 0u, 0u);
-                emit(w, pc < npc ? test(w, pc, one) : 0u);
-            }
-        };
-        if (S <= SW)
-            filter_rows(std::true_type{});
-        else
-            filter_rows(std::false_type{});
-        if (act && q == NL - 1) {
-            // padded to a multiple of 8 entries: with the LDS slot of the
-            // far-away position when the set fits one window, else the empty slot
-            const unsigned short pad = S <= SW ? (unsigned short)SW : EMPTY_SLOT;
-            for (int k = base; k < ((base + 7) & ~7); ++k)
-                dst[k] = pad;
-            a.list_cnt_out[i] = base;
-            lens_s[rho] = base;
-        }
-        cnt = act ? base : 0;
-        nch = (cnt + 3) >> 2;
-        __syncthreads();  // the rows are written (read back below) and the lengths known
-        // the row's first chunks requested together, as the other steps do
-        // before their staging; they arrive while the rank is counted
-#pragma unroll
-        for (int k = 0; k < NPRE; ++k)
-            lw[k] = q + k * NL < nch ? lp[q + k * NL] : make_uint2(0u, 0u);
-        // the later steps hand the rows to their waves longest first (ties
-        // in index order): the residue's rank, counted by its NL lanes
-        int r = 0;
-        if (act)
-            for (int u = q * (TILE / NL); u < min(tcnt, (q + 1) * (TILE / NL)); ++u)
-                r += (lens_s[u] > base || (lens_s[u] == base && u < rho)) ? 1 : 0;
-#pragma unroll
-        for (int off = 1; off < NL; off <<= 1)
-            r += __shfl_xor(r, off, NL);
-        if (act && q == 0)
-            a.tile_ord_out[(size_t)tile * TILE + r] = (unsigned char)rho;
-    }
-    // ---- 3. list chunks of this lane ----
-    Acc L;   // list: sum of d / r^8 (scaled by 6 eps_l sigma^6 below)
-    const float3 pl0 = unpack_low(rh0);
-    // slot -> LDS index of the current window (identity for one window)
-    int w0 = 0, wn = S;
-    // FORM: 0 high parts, 1 high and low parts, 2 high and low parts of one
-    // window (compile-time copies of `wide` and `windowed`, so that each list
-    // loop holds one form)
-    auto pairs4 = [&](const uint2 &w, auto form) {
-        constexpr int FORM = decltype(form)::value;
-        constexpr bool WIDE = FORM > 0;
-        float4 pj[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int sl = (int)(((u < 2 ? w.x : w.y) >> ((u & 1) * 16)) & 0xffffu);
-            if constexpr (FORM == 2) {
-                const int e = sl - w0;
-                pj[u] = sl_s[(unsigned)e < (unsigned)wn ? e : SW];
-            } else {
-                if constexpr (FORM == 0 && SOA)
-                    pj[u] = make_float4(sr_s[0][sl], sr_s[1][sl], sr_s[2][sl], 0.0f);
-                else
-                    pj[u] = sl_s[sl];
-            }
-        }
-        if constexpr (!WIDE) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                add_repulsive_u(L, make_float3(rh0.x - pj[u].x, rh0.y - pj[u].y, rh0.z - pj[u].z), k,
-                                ENERGY);
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float3 lj = unpack_low(pj[u]);
-                add_repulsive_u(L,
-                                make_float3((rh0.x - pj[u].x) + (pl0.x - lj.x), (rh0.y - pj[u].y) + (pl0.y - lj.y),
-                                            (rh0.z - pj[u].z) + (pl0.z - lj.z)),
-                                k, ENERGY);
-            }
-        }
-    };
-    auto list_pass = [&](auto form) {
-        if (!act)
-            return;
-#pragma unroll
-        for (int kk = 0; kk < NPRE; ++kk)
-            if (q + kk * NL < nch)
-                pairs4(lw[kk], form);
-        for (int c = q + NPRE * NL; c < nch; c += NL)
-            pairs4(lp[c], form);
-    };
-    if (!windowed) {
-        if (wide)
-            list_pass(std::integral_constant<int, 1>{});
-        else
-            list_pass(std::integral_constant<int, 0>{});
-    } else {
-        // every window's slots staged with their low parts; each entry
-        // contributes in the window holding its slot (elsewhere it reads the
-        // far-away slot, whose term is exactly zero)
-        for (w0 = 0; w0 < S; w0 += SW) {
-            wn = min(SW, S - w0);
-            __syncthreads();  // the previous window's readers are done
-            for (int sl = t; sl < wn; sl += 256) {
-                const int id = st[w0 + sl];
-                float4 rh, rl;
-                tile_frame(a.pin[2 * id], a.pin[2 * id + 1], O, rh, rl);
-                rh.w = __uint_as_float(pack_low(rh, rl));
-                sl_s[sl] = rh;
-            }
-            __syncthreads();
-            list_pass(std::integral_constant<int, 2>{});
-        }
-    }
-    // the residue's total over its NL lanes (butterfly: every lane gets the same bits)
-    float fx = k.c6 * L.fx + A.fx, fy = k.c6 * L.fy + A.fy, fz = k.c6 * L.fz + A.fz;
-    double eb = A.e_b, en = A.e_n, er = L.e_r, vir = A.vir + L.vir;
-#pragma unroll
-    for (int off = 1; off < NL; off <<= 1) {
-        fx += __shfl_xor(fx, off, NL);
-        fy += __shfl_xor(fy, off, NL);
-        fz += __shfl_xor(fz, off, NL);
-        if (ENERGY) {
-            eb += __shfl_xor(eb, off, NL);
-            en += __shfl_xor(en, off, NL);
-            er += __shfl_xor(er, off, NL);
-            vir += __shfl_xor(vir, off, NL);
-        }
-    }
-    if (act && q == 0) {
-        f_s[0][rho] = fx;
-        f_s[1][rho] = fy;
-        f_s[2][rho] = fz;
-        if constexpr (ENERGY) {
-            e_s[0][rho] = eb;
-            e_s[1][rho] = en;
-            e_s[2][rho] = er;
-            e_s[3][rho] = vir;
-        }
-    }
-    // this residue's slot in its cell (the group's atomic has returned)
-    int bin_s0 = 0;
-    if (do_bin)
-        bin_s0 = __shfl(bin_base, bin_lead) + bin_rank;
-    __syncthreads();
-    if (!upd)
-        return;
-    // ---- 4. external terms, noise and the compensated update ----
-    Acc F;
-    F.fx = f_s[0][ue] + X.fx;
-    F.fy = f_s[1][ue] + X.fy;
-    F.fz = f_s[2][ue] + X.fz;
-    if constexpr (ENERGY) {
-        double *er_out = a.res_energy + (size_t)iu * RES_E;
-        // each internal pair appears in both partners' rows
-        er_out[0] = 0.5 * e_s[0][ue];
-        er_out[1] = 0.5 * e_s[1][ue];
-        er_out[2] = 0.5 * e_s[2][ue];
-        er_out[3] = e_x;
-        er_out[4] = 0.5 * e_s[3][ue];
-        er_out[5] = f_rep;
-    }
-    if (MODE == 1) {
-        a.fout[iu] = make_float4(F.fx, F.fy, F.fz, 0.0f);
-        return;
-    }
-    float4 hi = hu, lo = lu;
-    if (a.vel) {
-        float4 v = a.vel[iu];
-        underdamped_update(hi, lo, v, F, g, a.ud, a.err);
-        a.vel[iu] = v;
-    } else {
-        update_with_noise(hi, lo, F, g, a.c, a.err);
-    }
-    a.pout[2 * iu] = hi;
-    a.pout[2 * iu + 1] = lo;
-    if (a.check_thr2 > 0.0f) {
-        // moved farther than skin/2 from the last skin build: the next
-        // rebuild rebuilds the skin
-        const float dx = hi.x - hsk.x, dy = hi.y - hsk.y, dz = hi.z - hsk.z;
-        if (!(dx * dx + dy * dy + dz * dz <= a.check_thr2))
-            atomicOr(a.skin_flag, 1u);
-    }
-    if (do_bin) {
-        const int traj = __float_as_int(lo.w);
-        const int c1 = cell_index(hi, bin_off, a.g);
-        if (c1 == bin_c0) {
-            a.cell_of[iu] = c1;
-            if (bin_s0 < CELL_CAP)
-                a.cells[(size_t)c1 * CELL_CAP + bin_s0] = make_float4(hi.x, hi.y, hi.z, __int_as_float(iu));
-            else
-                atomicOr(a.err, ERR_CELL);
-        } else {
-            // moved into another cell: the slot taken holds a far-away copy
-            // (no predicate passes it; the id keeps the cell's ids distinct)
-            // and the residue is binned again
-            if (bin_s0 < CELL_CAP)
-                a.cells[(size_t)bin_c0 * CELL_CAP + bin_s0] =
-                    make_float4(1.0e18f, 1.0e18f, 1.0e18f, __int_as_float(iu));
-            bin_one(hi, iu, traj, a.g, a.traj_cell, a.cell_count, a.cells, a.cell_of, a.err);
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Pair-based forces (Algorithm 4 with the atomic additions its text proposes
 // for GPUs that have them, Algorithm 5's gathering folded into the update
@@ -2114,18 +2013,19 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (TILE >= 256 ? 3 : 5)) void k_til
 // trajectories are reproducible only to rounding.
 // ---------------------------------------------------------------------------
 struct PairArgs {
+    const unsigned short *llen;
+    const unsigned char *grho;
     const int *tile_first;
     const float4 *pin;
     const int2 *trow;
     const float2 *tent;
-    const unsigned short *list16;
-    const int *list_cnt;
+    const uint2 *list16;
     const int *stage;
     const int *stage_cnt;
     float4 *facc;   // per residue: accumulated force
     double4 *eacc;  // per residue: accumulated {FENE, native, repulsive, virial} halves
     unsigned *err;
-    int cap, n_tiles;
+    int cap;
     StepConsts c;
 };
 
@@ -2135,15 +2035,15 @@ struct PairArgs {
 // residue's sum and each slot's sum are added to the device-wide
 // accumulators with one hardware float atomic per component.  Bonded and
 // native partners, which need no slot, take device-wide atomics directly.
-template <int TILE, bool ENERGY>
+template <int TILE, int NL, bool ENERGY>
 __global__ __launch_bounds__(256) void k_pair_forces(PairArgs a)
 {
-    constexpr int NL = 256 / TILE;
+    using R = Rows<TILE, NL>;
     constexpr int SM = stage_max<TILE>();
-    constexpr int SW = stage_win<TILE>();
+    constexpr int SW = R::SW;
     __shared__ float acc_s[3][SW];  // slots beyond SW take device-wide atomics
-    const int tile = blockIdx.x, t = threadIdx.x;
-    const int rho = t / NL, q = t % NL;
+    const int wg = blockIdx.x, t = threadIdx.x;
+    const int tile = wg / R::W, r = t / NL * R::W + wg % R::W, q = t % NL;
     const int first = a.tile_first[tile], tcnt = a.tile_first[tile + 1] - first;
     const int S = min(a.stage_cnt[tile], SM);
     const int *st = a.stage + (size_t)tile * SM;
@@ -2153,16 +2053,17 @@ __global__ __launch_bounds__(256) void k_pair_forces(PairArgs a)
         acc_s[2][sl] = 0.0f;
     }
     __syncthreads();
-    const bool act = rho < tcnt;
-    const int i = first + (act ? rho : 0);
+    const bool act = r < tcnt;
+    const int i = first + a.grho[wg * R::RW + t / NL];
     const PairConsts k = pair_consts(a.c);
     Acc own;  // residue i's share of its pairs
     if (act) {
         const float4 hi = a.pin[2 * i], lo = a.pin[2 * i + 1];
-        const int cnt = min(a.list_cnt[i], a.cap);
-        const unsigned short *row = a.list16 + (size_t)i * a.cap;
-        for (int e = q; e < cnt; e += NL) {
-            const int sl = row[e];
+        const int m = a.llen[wg * 256 + t];
+        const unsigned short *row = reinterpret_cast<const unsigned short *>(
+            a.list16 + chunk_index(wg, 0, t, lane_chunks(a.cap, NL)));
+        for (int e = 0; e < m; ++e) {
+            const int sl = row[(e >> 2) * 1024 + (e & 3)] >> 2;
             const int j = st[sl];
             if (j <= i)
                 continue;  // the pair belongs to the lower residue's row
@@ -2201,7 +2102,7 @@ __global__ __launch_bounds__(256) void k_pair_forces(PairArgs a)
             if (e < nb)
                 add_fene_d(d, dd, te.y, k, ENERGY, broken);
             else
-                add_native_d(d, dd, te.y, k, ENERGY);
+                add_native_d(d, dd, te.y * te.y, k, ENERGY);
             own.fx += d.fx;
             own.fy += d.fy;
             own.fz += d.fz;
@@ -2261,6 +2162,8 @@ __global__ __launch_bounds__(256) void k_pair_forces(PairArgs a)
 struct PairUpdArgs {
     const float4 *pin;
     float4 *pout;
+    int4 *qout;
+    FixDev fix;
     float4 *facc;
     double4 *eacc;
     const uint2 *noise_key;
@@ -2340,6 +2243,7 @@ __global__ __launch_bounds__(256) void k_pair_update(PairUpdArgs a)
     }
     a.pout[2 * i] = hi;
     a.pout[2 * i + 1] = lo;
+    a.qout[i] = fix_pos(hi, lo, a.fix);
     if (a.check_thr2 > 0.0f) {
         const float4 hs = a.hi_skin[i];
         const float dx = hi.x - hs.x, dy = hi.y - hs.y, dz = hi.z - hs.z;
@@ -2903,7 +2807,7 @@ __global__ void k_set_step(long long *dst, long long v)
 
 inline int blocks_for(long long n, int per) { return (int)((n + per - 1) / per); }
 
-template <int TILE>
+template <int TILE, int NL>
 void canon_tile(const DevBufs &b, int cap, hipStream_t s)
 {
     CanonArgs a{};
@@ -2911,35 +2815,69 @@ void canon_tile(const DevBufs &b, int cap, hipStream_t s)
     a.trow = b.trow;
     a.stage = b.stage;
     a.stage_cnt = b.stage_cnt;
-    a.skin16 = b.list16;
+    a.rows = b.flist16;
     a.skin_cnt = b.list_cnt;
-    a.topo2 = b.topo2;
+    a.tent = b.tent;
     a.skin_flag = b.skin_flag;
+    a.skin16 = reinterpret_cast<uint4 *>(b.list16);
+    a.skin_len = b.skin_len;
     a.skin_ord = b.skin_ord;
+    a.ltop = b.ltop;
+    a.tile_top = b.tile_top;
+    a.stage16 = b.stage16;
     a.cap = cap;
-    hipLaunchKernelGGL((k_canon<TILE>), dim3(b.n_tiles[tile_index(TILE)]), dim3(256), 0, s, a);
+    a.top_rounds = top_rounds(b.max_bonds, b.max_natives, NL);
+    hipLaunchKernelGGL((k_canon<TILE, NL>), dim3(b.n_tiles[tile_index(TILE)]), dim3(256), 0, s, a);
 }
 
-template <int TILE>
-void filter_tile(const DevBufs &b, int cur, int cap, const GridDev &g, float rc2, hipStream_t s)
+FilterArgs filter_args(const DevBufs &b, int cur, int cap, int tile, int n_cells, const FixDev &fix, float rc2)
 {
     FilterArgs a{};
-    a.tile_first = b.tile_first[tile_index(TILE)];
+    a.tile_first = b.tile_first[tile_index(tile)];
     a.pos = b.pos[cur];
     a.stage = b.stage;
     a.stage_cnt = b.stage_cnt;
-    a.skin16 = b.list16;
-    a.skin_cnt = b.list_cnt;
-    a.list16 = b.flist16;
-    a.list_cnt = b.fcnt;
+    a.skin16 = reinterpret_cast<const uint4 *>(b.list16);
+    a.skin_len = b.skin_len;
+    a.skin_ord = b.skin_ord;
+    a.ltop = b.ltop;
+    a.tile_top = b.tile_top;
+    a.list16 = reinterpret_cast<uint2 *>(b.flist16);
+    a.llen = b.llen;
+    a.grho = b.grho;
+    a.wg_rec = b.wg_rec;
     a.cell_count = b.cell_count;
     a.skin_flag = b.skin_flag;
-    a.tile_ord = b.tile_ord;
-    a.skin_ord = b.skin_ord;
     a.rc2 = rc2;
+    a.fix = fix;
     a.cap = cap;
-    a.n_cells = g.n_cells;
-    hipLaunchKernelGGL((k_filter<TILE>), dim3(b.n_tiles[tile_index(TILE)]), dim3(256), 0, s, a);
+    a.n_cells = n_cells;
+    a.top_rounds = top_rounds(b.max_bonds, b.max_natives, lanes_for(tile, b.n_tiles[tile_index(tile)]));
+    return a;
+}
+
+// Calls f with the tile size and the lanes per residue as compile-time constants.
+template <class F>
+void with_rows(int tile, int n_tiles, F &&f)
+{
+    using std::integral_constant;
+    switch (tile) {
+    case 64:
+        switch (lanes_for(64, n_tiles)) {
+        case 16: f(integral_constant<int, 64>{}, integral_constant<int, 16>{}); break;
+        case 8: f(integral_constant<int, 64>{}, integral_constant<int, 8>{}); break;
+        default: f(integral_constant<int, 64>{}, integral_constant<int, 4>{}); break;
+        }
+        break;
+    case 128: f(integral_constant<int, 128>{}, integral_constant<int, 2>{}); break;
+    default: f(integral_constant<int, 256>{}, integral_constant<int, 1>{}); break;
+    }
+}
+
+int workgroups(const DevBufs &b, int tile)
+{
+    const int n = b.n_tiles[tile_index(tile)];
+    return n * (tile * lanes_for(tile, n) / 256);
 }
 
 template <int TILE>
@@ -2961,8 +2899,7 @@ void rebuild_tile(const DevBufs &b, int cur, int n, int cap, const GridDev &g, f
     a.trow = b.trow;
     a.tent = b.tent;
     a.list_cnt = b.list_cnt;
-    a.list16 = b.list16;
-    a.topo2 = b.topo2;
+    a.list16 = b.flist16;
     a.stage = b.stage;
     a.stage_cnt = b.stage_cnt;
     a.err = b.err;
@@ -2980,59 +2917,39 @@ void rebuild_tile(const DevBufs &b, int cur, int n, int cap, const GridDev &g, f
         hipLaunchKernelGGL((k_tile_build<TILE, false>), dim3(nt), dim3(256), 0, s, a);
 }
 
-template <int TILE, bool ENERGY, int MODE, bool FIRST>
-void tile_step(const TileArgs &a, hipStream_t s)
-{
-    const int blocks = ((a.n_tiles + 7) / 8) * 8;
-    const TileArgs &x = a;
-    hipLaunchKernelGGL((k_tile_step<TILE, ENERGY, MODE, FIRST>), dim3(blocks), dim3(256), 0, s, x);
-}
-
 template <bool ENERGY, int MODE, bool FIRST = false>
-void tile_dispatch(int tile, const TileArgs &a, hipStream_t s)
+void tile_dispatch(const DevBufs &b, int tile, const TileArgs &a, hipStream_t s)
 {
-    switch (tile) {
-    case 64: tile_step<64, ENERGY, MODE, FIRST>(a, s); break;
-    case 128: tile_step<128, ENERGY, MODE, FIRST>(a, s); break;
-    default: tile_step<256, ENERGY, MODE, FIRST>(a, s); break;
-    }
+    const int blocks = ((a.n_wg + 7) / 8) * 8;
+    with_rows(tile, b.n_tiles[tile_index(tile)], [&](auto T, auto NL) {
+        hipLaunchKernelGGL((k_tile_step<decltype(T)::value, decltype(NL)::value, ENERGY, MODE, FIRST>), dim3(blocks),
+                           dim3(256), 0, s, a);
+    });
 }
 
 }  // namespace
 
-void launch_rebuild(const DevBufs &b, int cur, int n, int cap, int tile, const GridDev &g, float rc2,
-                    float rs2, int multi, hipStream_t s, bool advance_step_base, int list_every, bool binned,
-                    bool filter)
+void launch_rebuild(const DevBufs &b, int cur, int n, int cap, int tile, const GridDev &g, const FixDev &fix,
+                    float rc2, float rs2, int multi, hipStream_t s, bool advance_step_base, int list_every,
+                    bool binned, bool filter)
 {
     if (!binned)
-        launch_bin_all(b, cur, n, g, s);  // not binned by a period's last step kernel
-    switch (tile) {
-    case 64:
-        rebuild_tile<64>(b, cur, n, cap, g, rs2, multi, s, advance_step_base, list_every);
-        canon_tile<64>(b, cap, s);
+        launch_bin_all(b, cur, n, g, fix, s);  // not binned by a period's last step kernel
+    with_rows(tile, b.n_tiles[tile_index(tile)], [&](auto T, auto NL) {
+        constexpr int TILE = decltype(T)::value;
+        rebuild_tile<TILE>(b, cur, n, cap, g, rs2, multi, s, advance_step_base, list_every);
+        canon_tile<TILE, decltype(NL)::value>(b, cap, s);
         if (filter)
-            filter_tile<64>(b, cur, cap, g, rc2, s);
-        break;
-    case 128:
-        rebuild_tile<128>(b, cur, n, cap, g, rs2, multi, s, advance_step_base, list_every);
-        canon_tile<128>(b, cap, s);
-        if (filter)
-            filter_tile<128>(b, cur, cap, g, rc2, s);
-        break;
-    default:
-        rebuild_tile<256>(b, cur, n, cap, g, rs2, multi, s, advance_step_base, list_every);
-        canon_tile<256>(b, cap, s);
-        if (filter)
-            filter_tile<256>(b, cur, cap, g, rc2, s);
-        break;
-    }
+            hipLaunchKernelGGL((k_filter<TILE, decltype(NL)::value>), dim3(workgroups(b, tile)), dim3(256), 0, s,
+                               filter_args(b, cur, cap, tile, g.n_cells, fix, rc2));
+    });
 }
 
-void launch_bin_all(const DevBufs &b, int cur, int n, const GridDev &g, hipStream_t s)
+void launch_bin_all(const DevBufs &b, int cur, int n, const GridDev &g, const FixDev &fix, hipStream_t s)
 {
     hipLaunchKernelGGL(k_clear, dim3(blocks_for(g.n_cells, WG)), dim3(WG), 0, s, b.cell_count, g.n_cells);
     hipLaunchKernelGGL(k_bin_all, dim3(blocks_for(n, WG)), dim3(WG), 0, s, b.pos[cur], n, g, b.traj_cell,
-                       b.cell_count, b.cells, b.cell_of, b.err);
+                       b.cell_count, b.cells, b.cell_of, b.err, b.fix[cur], fix);
 }
 
 void launch_force_skin(const DevBufs &b, hipStream_t s)
@@ -3040,28 +2957,19 @@ void launch_force_skin(const DevBufs &b, hipStream_t s)
     hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(64), 0, s, b.skin_flag, 1u);
 }
 
-template <int TILE>
-void pair_forces(const PairArgs &a, bool energy, hipStream_t s)
-{
-    if (energy)
-        hipLaunchKernelGGL((k_pair_forces<TILE, true>), dim3(a.n_tiles), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_pair_forces<TILE, false>), dim3(a.n_tiles), dim3(256), 0, s, a);
-}
-
 void launch_pair_step(const DevBufs &b, int cur, int n, int cap, int tile, const StepConsts &c,
-                      const TipDev &tip, int has_pull, bool energy, int mode, const long long *step_base,
+                      const FixDev &fix, const TipDev &tip, int has_pull, bool energy, int mode, const long long *step_base,
                       long long step_off, float check_thr2, hipStream_t s, const float4 *vel,
                       const UdConsts &ud, const GridDev *bin_grid)
 {
     PairArgs a{};
     a.tile_first = b.tile_first[tile_index(tile)];
-    a.n_tiles = b.n_tiles[tile_index(tile)];
     a.pin = b.pos[cur];
     a.trow = b.trow;
     a.tent = b.tent;
-    a.list16 = b.flist16;
-    a.list_cnt = b.fcnt;
+    a.llen = b.llen;
+    a.grho = b.grho;
+    a.list16 = reinterpret_cast<const uint2 *>(b.flist16);
     a.stage = b.stage;
     a.stage_cnt = b.stage_cnt;
     a.facc = b.facc;
@@ -3069,14 +2977,18 @@ void launch_pair_step(const DevBufs &b, int cur, int n, int cap, int tile, const
     a.err = b.err;
     a.cap = cap;
     a.c = c;
-    switch (tile) {
-    case 64: pair_forces<64>(a, energy, s); break;
-    case 128: pair_forces<128>(a, energy, s); break;
-    default: pair_forces<256>(a, energy, s); break;
-    }
+    with_rows(tile, b.n_tiles[tile_index(tile)], [&](auto T, auto NL) {
+        const dim3 grid(workgroups(b, tile));
+        if (energy)
+            hipLaunchKernelGGL((k_pair_forces<decltype(T)::value, decltype(NL)::value, true>), grid, dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_pair_forces<decltype(T)::value, decltype(NL)::value, false>), grid, dim3(256), 0, s, a);
+    });
     PairUpdArgs u{};
     u.pin = b.pos[cur];
     u.pout = b.pos[cur ^ 1];
+    u.qout = b.fix[cur ^ 1];
+    u.fix = fix;
     u.facc = b.facc;
     u.eacc = b.eacc;
     u.noise_key = b.noise_key;
@@ -3118,7 +3030,7 @@ void launch_pair_step(const DevBufs &b, int cur, int n, int cap, int tile, const
 }
 
 void launch_step(const DevBufs &b, int cur, int n, int cap, int tile, const StepConsts &c,
-                 const TipDev &tip, int has_pull, bool energy, int mode, const long long *step_base,
+                 const FixDev &fix, const TipDev &tip, int has_pull, bool energy, int mode, const long long *step_base,
                  long long step_off, float check_thr2, hipStream_t s, int force_mode, float ud_kick,
                  const GridDev *bin_grid, float filter_rc2, int n_cells)
 {
@@ -3126,7 +3038,7 @@ void launch_step(const DevBufs &b, int cur, int n, int cap, int tile, const Step
     const float4 *vel = ud_kick > 0.0f ? b.vel : nullptr;
     UdConsts ud{ud_kick, c.ud_c1, c.ud_c2, (float)(0.5 * c.h)};
     if (force_mode == 1) {
-        launch_pair_step(b, cur, n, cap, tile, c, tip, has_pull, energy, mode, step_base, step_off,
+        launch_pair_step(b, cur, n, cap, tile, c, fix, tip, has_pull, energy, mode, step_base, step_off,
                          check_thr2, s, vel, ud, bin_grid);
         return;
     }
@@ -3140,22 +3052,22 @@ void launch_step(const DevBufs &b, int cur, int n, int cap, int tile, const Step
     a.cell_count = b.cell_count;
     a.cells = b.cells;
     a.cell_of = b.cell_of;
-    a.tile_ord = b.tile_ord;
     a.hi_skin = b.hi_skin;
     a.skin_flag = b.skin_flag;
     a.check_thr2 = mode == 0 ? check_thr2 : 0.0f;
-    a.tile_first = b.tile_first[tile_index(tile)];
-    a.n_tiles = b.n_tiles[tile_index(tile)];
+    a.n_wg = workgroups(b, tile);
     a.pin = b.pos[cur];
     a.pout = b.pos[cur ^ 1];
-    a.trow = b.trow;
-    a.tent = b.tent;
-    a.list16 = b.flist16;
-    a.topo2 = b.topo2;
-    a.list_cnt = b.fcnt;
+    a.qin = b.fix[cur];
+    a.qout = b.fix[cur ^ 1];
+    a.fix = fix;
+    a.list16 = reinterpret_cast<const uint2 *>(b.flist16);
+    a.llen = b.llen;
+    a.grho = b.grho;
+    a.wg_rec = b.wg_rec;
+    a.ltop = b.ltop;
     a.stage = b.stage;
-    a.stage_cnt = b.stage_cnt;
-    a.stream_ids = b.stream_ids;
+    a.stage16 = b.stage16;
     a.noise_key = b.noise_key;
     a.pull_slot = b.pull_slot;
     a.pulls = b.pulls;
@@ -3164,38 +3076,32 @@ void launch_step(const DevBufs &b, int cur, int n, int cap, int tile, const Step
     a.err = b.err;
     a.step_base = step_base;
     a.step_off = step_off;
-    a.n = n;
-    a.cap = cap;
+    const int nl = lanes_for(tile, b.n_tiles[tile_index(tile)]);
+    a.chunks = lane_chunks(cap, nl);
+    a.top_rounds = top_rounds(b.max_bonds, b.max_natives, nl);
     a.has_pull = has_pull;
     a.c = c;
     a.tip = tip;
     if (mode == 0 && filter_rc2 > 0.0f) {
         // the first step after a rebuild, which filters the skin rows itself
         // (never a binning step: the callers bin only at a period's end)
-        a.skin16 = b.list16;
-        a.skin_cnt = b.list_cnt;
-        a.skin_ord = b.skin_ord;
-        a.list16_out = b.flist16;
-        a.list_cnt_out = b.fcnt;
-        a.tile_ord_out = b.tile_ord;
-        a.rc2 = filter_rc2;
-        a.n_cells = n_cells;
+        a.f = filter_args(b, cur, cap, tile, n_cells, fix, filter_rc2);
         if (energy)
-            tile_dispatch<true, 0, true>(tile, a, s);
+            tile_dispatch<true, 0, true>(b, tile, a, s);
         else
-            tile_dispatch<false, 0, true>(tile, a, s);
+            tile_dispatch<false, 0, true>(b, tile, a, s);
         return;
     }
     if (mode == 1) {
         if (energy)
-            tile_dispatch<true, 1>(tile, a, s);
+            tile_dispatch<true, 1>(b, tile, a, s);
         else
-            tile_dispatch<false, 1>(tile, a, s);
+            tile_dispatch<false, 1>(b, tile, a, s);
     } else {
         if (energy)
-            tile_dispatch<true, 0>(tile, a, s);
+            tile_dispatch<true, 0>(b, tile, a, s);
         else
-            tile_dispatch<false, 0>(tile, a, s);
+            tile_dispatch<false, 0>(b, tile, a, s);
     }
 }
 
