@@ -7,6 +7,7 @@
 // are summed in double precision in a fixed order.
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "sop_internal.hpp"
 #include "sop_rng.hpp"
@@ -25,44 +26,124 @@ struct RampConsts {
     unsigned key0, key1, stream;
 };
 
+// One step: hi + lo advanced by c_det (ramp - K_sp X) plus the noise.
+template <bool COMP>
+__device__ __forceinline__ void ramp_step(float &hi, float &lo, float ramp, float noise, const RampConsts &c)
+{
+    const float f = (ramp - c.k_sp * hi) - c.k_sp * lo;
+    const float delta = __builtin_fmaf(c.c_det, f, noise);
+    if (COMP) {
+        // TwoSum(hi, delta + lo): hi + lo keeps the increments that fall
+        // below half an ulp of hi
+        const float y = delta + lo;
+        const float t = hi + y;
+        const float bp = t - hi;
+        const float ap = t - bp;
+        lo = (hi - ap) + (y - bp);
+        hi = t;
+    } else {
+        hi = hi + delta;
+    }
+}
+
+__device__ __forceinline__ float ramp_noise(long long m, long long k, const RampConsts &c)
+{
+    const uint4 w = philox10(make_uint4((unsigned)m, c.stream, (unsigned)k,
+                                        (unsigned)((unsigned long long)k >> 32)),
+                             c.key0, c.key1);
+    return c.c_noise * gaussian_pair(w).x;
+}
+
 // Both schemes step X by c_det (r_f t_k - K_sp X) plus the Gaussian
 // displacement: the order-2 correction of Eq. 5,
 // (X/(2 tau^2) - r_f t_k/(2 tau xi)) h^2, is -(h/(2 tau)) times the order-1
 // drift (r_f t_k/xi - X/tau) h, so it only rescales the drift coefficient.
-template <bool COMP, bool NOISE>
+// Without noise, one lane advances a particle; the ramp force is taken in
+// double (k reaches 1e9 and more), the rest in single precision.
+template <bool COMP>
 __global__ __launch_bounds__(RAMP_WG) void k_ramp(float2 *__restrict__ x, long long m_count,
                                                   long long step0, long long n_steps, RampConsts c)
 {
     const long long m = (long long)blockIdx.x * RAMP_WG + threadIdx.x;
     if (m >= m_count)
         return;
-    float2 v = x[m];
+    const float2 v = x[m];
     float hi = v.x, lo = COMP ? v.y : 0.0f;
-    for (long long k = step0; k < step0 + n_steps; ++k) {
-        // the ramp force in double (k reaches 1e9 and more), the rest single
-        const float ramp = (float)(c.rf_h * (double)k);
-        const float f = (ramp - c.k_sp * hi) - c.k_sp * lo;
-        float delta = c.c_det * f;
-        if (NOISE) {
-            const uint4 w = philox10(make_uint4((unsigned)m, c.stream, (unsigned)k,
-                                                (unsigned)((unsigned long long)k >> 32)),
-                                     c.key0, c.key1);
-            delta += c.c_noise * gaussian_pair(w).x;
-        }
-        if (COMP) {
-            // TwoSum(hi, delta + lo): hi + lo keeps the increments that fall
-            // below half an ulp of hi
-            const float y = delta + lo;
-            const float t = hi + y;
-            const float bp = t - hi;
-            const float ap = t - bp;
-            lo = (hi - ap) + (y - bp);
-            hi = t;
-        } else {
-            hi = hi + delta;
-        }
-    }
+    for (long long k = step0; k < step0 + n_steps; ++k)
+        ramp_step<COMP>(hi, lo, (float)(c.rf_h * (double)k), 0.0f, c);
     x[m] = make_float2(hi, lo);
+}
+
+// With noise, NOISE_WAVES waves advance 64 particles.  A particle's steps are
+// a chain, but nearly all of a step's work (about 85 of 100 instructions) is
+// its noise, which depends on the counter alone: seven waves make the noise
+// of the next chunk of steps, at most NOISE_STEPS each, while wave 0 advances the
+// particles through the current chunk from LDS.  Few particles are bound by
+// one wave's instruction chain, which this cuts to the update's; many by the
+// instruction rate of the chip, which their 64-lane groups now fill evenly
+// (1e5 particles, one lane each: two waves on half of the SIMDs, one on the
+// others).  1,000 steps and the moments, one lane a particle -> 4 waves -> 8:
+// 1e3 particles 230 -> 97 -> 83 us, 32e3 230 -> 125 -> 115, 1e5 330 -> 270 ->
+// 260, 1e6 2,030 -> 1,880 -> 1,850.
+constexpr int NOISE_WAVES = 8, NOISE_STEPS = 8;
+
+template <bool COMP>
+__global__ __launch_bounds__(64 * NOISE_WAVES) void k_ramp_noise(float2 *__restrict__ x, long long m_count,
+                                                                 long long step0, long long n_steps,
+                                                                 RampConsts c)
+{
+    constexpr int S = (NOISE_WAVES - 1) * NOISE_STEPS;  // steps of a chunk
+    __shared__ float g[2][S][64];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long m = (long long)blockIdx.x * 64 + lane;
+    const bool adv = w == 0 && m < m_count;
+    float hi = 0.0f, lo = 0.0f;
+    if (adv) {
+        const float2 v = x[m];
+        hi = v.x;
+        lo = COMP ? v.y : 0.0f;
+    }
+    const long long n_chunks = (n_steps + S - 1) / S;
+    for (long long ch = -1; ch < n_chunks; ++ch) {
+        if (w == 0 && ch >= 0) {
+            const long long k0 = step0 + ch * S;
+            const int n = (int)min((long long)S, n_steps - ch * S);
+            const float *gc = &g[ch & 1][0][lane];
+            double kd = (double)k0;  // whole numbers: exact
+#pragma unroll 4
+            for (int q = 0; q < n; ++q) {
+                ramp_step<COMP>(hi, lo, (float)(c.rf_h * kd), gc[64 * q], c);
+                kd += 1.0;
+            }
+        }
+        if (w > 0 && ch + 1 < n_chunks) {
+            const long long k0 = step0 + (ch + 1) * S;
+            const int n = (int)min((long long)S, n_steps - (ch + 1) * S);
+            float *gn = &g[(ch + 1) & 1][0][lane];
+#pragma unroll 2
+            for (int q = w - 1; q < n; q += NOISE_WAVES - 1)
+                gn[64 * q] = ramp_noise(m, k0 + q, c);
+        }
+        __syncthreads();
+    }
+    if (adv)
+        x[m] = make_float2(hi, lo);
+}
+
+// s1[0], s2[0]: the block's sums of a and b.
+__device__ __forceinline__ void block_sums(double a, double b, double *s1, double *s2)
+{
+    s1[threadIdx.x] = a;
+    s2[threadIdx.x] = b;
+    __syncthreads();
+    for (int off = RAMP_WG / 2; off > 0; off >>= 1) {
+        if ((int)threadIdx.x < off) {
+            s1[threadIdx.x] += s1[threadIdx.x + off];
+            s2[threadIdx.x] += s2[threadIdx.x + off];
+        }
+        __syncthreads();
+    }
 }
 
 // Per-block double sums of X = hi + lo and X^2 over a grid-stride range.
@@ -78,36 +159,31 @@ __global__ __launch_bounds__(RAMP_WG) void k_ramp_partial(const float2 *__restri
         a += X;
         b += X * X;
     }
-    s1[threadIdx.x] = a;
-    s2[threadIdx.x] = b;
-    __syncthreads();
-    for (int off = RAMP_WG / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            s1[threadIdx.x] += s1[threadIdx.x + off];
-            s2[threadIdx.x] += s2[threadIdx.x + off];
-        }
-        __syncthreads();
-    }
+    block_sums(a, b, s1, s2);
     if (threadIdx.x == 0) {
         part[2 * blockIdx.x] = s1[0];
         part[2 * blockIdx.x + 1] = s2[0];
     }
 }
 
-// Mean and population variance from the block sums, in block order.
-__global__ void k_ramp_final(const double *__restrict__ part, int n_part, long long m_count,
-                             double *__restrict__ moments)
+// Mean and population variance from the block sums, added in a fixed order
+// (thread by thread at a stride, then a tree; one thread in block order took
+// 30 us for 391 blocks).
+__global__ __launch_bounds__(RAMP_WG) void k_ramp_final(const double *__restrict__ part, int n_part,
+                                                        long long m_count, double *__restrict__ moments)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0)
-        return;
+    __shared__ double s1[RAMP_WG], s2[RAMP_WG];
     double a = 0.0, b = 0.0;
-    for (int k = 0; k < n_part; ++k) {
+    for (int k = threadIdx.x; k < n_part; k += RAMP_WG) {
         a += part[2 * k];
         b += part[2 * k + 1];
     }
-    const double mean = a / (double)m_count;
-    moments[0] = mean;
-    moments[1] = b / (double)m_count - mean * mean;
+    block_sums(a, b, s1, s2);
+    if (threadIdx.x == 0) {
+        const double mean = s1[0] / (double)m_count;
+        moments[0] = mean;
+        moments[1] = s2[0] / (double)m_count - mean * mean;
+    }
 }
 
 int ramp_blocks(long long m_count)
@@ -146,20 +222,24 @@ sop_status ramp_launch(const sop_ramp_params *rp, int64_t n_particles, float *x,
     c.stream = rp->stream;
     float2 *xv = reinterpret_cast<float2 *>(x);
     const long long M = n_particles;
-    const int grid = (int)((M + RAMP_WG - 1) / RAMP_WG);
     const bool noise = rp->kBT > 0.0;
+    auto run = [&](auto comp) {
+        constexpr bool COMP = decltype(comp)::value;
+        if (noise)
+            k_ramp_noise<COMP><<<(int)((M + 63) / 64), 64 * NOISE_WAVES, 0, s>>>(xv, M, step0, n_steps, c);
+        else
+            k_ramp<COMP><<<(int)((M + RAMP_WG - 1) / RAMP_WG), RAMP_WG, 0, s>>>(xv, M, step0, n_steps, c);
+    };
     if (n_steps > 0) {
         if (rp->compensated)
-            noise ? k_ramp<true, true><<<grid, RAMP_WG, 0, s>>>(xv, M, step0, n_steps, c)
-                  : k_ramp<true, false><<<grid, RAMP_WG, 0, s>>>(xv, M, step0, n_steps, c);
+            run(std::true_type{});
         else
-            noise ? k_ramp<false, true><<<grid, RAMP_WG, 0, s>>>(xv, M, step0, n_steps, c)
-                  : k_ramp<false, false><<<grid, RAMP_WG, 0, s>>>(xv, M, step0, n_steps, c);
+            run(std::false_type{});
     }
     if (moments) {
         const int nb = ramp_blocks(M);
         k_ramp_partial<<<nb, RAMP_WG, 0, s>>>(xv, M, part);
-        k_ramp_final<<<1, 64, 0, s>>>(part, nb, M, moments);
+        k_ramp_final<<<1, RAMP_WG, 0, s>>>(part, nb, M, moments);
     }
     return hipGetLastError() == hipSuccess ? SOP_OK : SOP_E_HIP;
 }

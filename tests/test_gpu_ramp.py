@@ -73,6 +73,27 @@ def test_resume_is_bit_exact(env):
     assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("M", [1, 64, 65])
+@pytest.mark.parametrize("n", [1, 55, 56, 57, 113])
+@pytest.mark.parametrize("compensated", [True, False])
+def test_chunk_edges(env, M, n, compensated):
+    """Step counts around the chunks of 56 steps whose noise is made ahead,
+    particle counts around the groups of 64: one call against single-step
+    calls bit for bit, and (compensated) the oracle."""
+    torch, orc, P = env
+    rp = P.ramp_params(RF, XI, KSP, KBT, 25.0, order=1, seed=SEED, stream=2, compensated=compensated)
+    a, b = particles(torch, np.zeros(M)), particles(torch, np.zeros(M))
+    P.ramp_run(rp, a, 5, n, moments=False)
+    for k in range(n):
+        P.ramp_run(rp, b, 5 + k, 1, moments=False)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    if compensated:
+        ref = orc.ramp_run(1, np.zeros(M), 5, n, RF, XI, KSP, KBT, 25.0, SEED, stream=2)
+        sig = math.sqrt(2.0 * KBT * 25.0 / XI)
+        assert np.abs(as_f64(a) - ref).max() <= 1e-5 * sig * math.sqrt(n)
+
+
 @pytest.mark.parametrize("order", [1, 2])
 def test_noise_free_follows_the_recursion(env, order):
     torch, orc, P = env
