@@ -364,6 +364,10 @@ FixDev fix_consts(const sop_ctx *c)
     const double drift = 16.0 * std::sqrt(2.0 * c->p.kBT * c->p.h / c->p.zeta * c->p.list_every);
     const double half = 2.5 * (c->p.r_list + drift);
     int k = 31 - (int)std::ceil(std::log2(std::min(std::max(half, 1e-9), 1e30)));
+    // batched: bonded and native terms have the copies alone, so the unit
+    // follows the shortest reference length where that asks for a finer one
+    if (c->schedule == SOP_SCHEDULE_BATCHED)
+        k = std::max(k, std::min(28, 24 - (int)std::floor(std::log2(std::min(std::max(c->min_r0, 1e-9), 1e30)))));
     k = std::max(-60, std::min(60, k));
     FixDev f{};
     f.scale = std::ldexp(1.0, k);
@@ -372,6 +376,7 @@ FixDev fix_consts(const sop_ctx *c)
     f.unit = (float)std::ldexp(1.0, -k);
     f.s2 = (float)std::ldexp(1.0, 2 * k);
     f.reach = (float)std::ldexp(1.0, 30 - k);
+    f.direct = (float)std::ldexp(1.0, 50 - k);
     f.list_far = (half > std::ldexp(1.0, 31 - k) || f.unit > 2e-6 * c->p.sigma) ? 1 : 0;
     f.bond_far = f.unit > std::ldexp(c->min_r0, -24) ? 1 : 0;
     return f;
@@ -543,7 +548,7 @@ void one_step(sop_ctx *c, hipStream_t s, const long long *base, long long off, b
 void batch_launch(sop_ctx *c, hipStream_t s, int n_steps, int stale, int mode, const long long *base,
                   long long off, bool records = false)
 {
-    launch_batch(c->b, c->cur, n_packs(c), c->batch_wg, c->cap, step_consts(c), c->tip,
+    launch_batch(c->b, c->cur, n_packs(c), c->batch_wg, c->cap, step_consts(c), fix_consts(c), c->tip,
                  c->pulls.empty() ? 0 : 1, list_rc2(c), c->p.list_every, c->energy_every, n_steps,
                  stale, mode == 1 ? 1 : (records ? 2 : 0), base, off, s,
                  c->re_rep > 0 ? c->b.re_tscale : nullptr);
@@ -1436,7 +1441,7 @@ sop_status sop_get_pairlist(sop_ctx *c, int64_t cap, int32_t *ij, int64_t *n_pai
             for (int t = 0; t < m; ++t) {
                 const int i = c->slot_res[off + t];
                 for (int k = 0; k < std::min(cnt[i], c->cap); ++k) {
-                    const int sl = list[(size_t)i * c->cap + k];
+                    const int sl = list[(size_t)i * c->cap + k] >> 4;
                     if (sl >= m)
                         return fail(c, SOP_E_LIST_OVERFLOW, "list entry outside its pack");
                     const int j = c->slot_res[off + sl];

@@ -64,15 +64,15 @@ constexpr int TOPO_CAP = 64;
 // the kernels hold 1,024 or 2,048 of them in LDS at once).
 constexpr int STAGE_MAX = 4096;
 
-// Fixed-point copies of the positions (plain schedule): whole numbers of
-// units of 2^-k, modulo 2^32 units.  `reach` is a quarter of the period, in
+// Fixed-point copies of the positions: whole numbers of units of 2^-k, modulo
+// 2^32 units.  `direct`: 2^50 units.  `reach` is a quarter of the period, in
 // the caller's units: a bonded or native pair within it on every axis at a
 // rebuild is taken from the copies until the next one, others (and every
 // such pair when `bond_far`, every list pair when `list_far`) from the
 // compensated positions.
 struct FixDev {
     double scale, period, inv_period;  // 2^k, 2^(32-k), 2^(k-32)
-    float unit, s2, reach;             // 2^-k, 2^2k, 2^(30-k)
+    float unit, s2, reach, direct;     // 2^-k, 2^2k, 2^(30-k), 2^(50-k)
     int list_far, bond_far;
 };
 
@@ -202,7 +202,7 @@ void launch_reduce_energy(const DevBufs &b, int n_traj, hipStream_t s);
 // steps without energy records; 2: steps that record at multiples of
 // energy_every; 1: one force evaluation with records, no update.
 void launch_batch(const DevBufs &b, int cur, int n_packs, int wg, int cap, const StepConsts &c,
-                  const TipDev &tip, int has_pull, float rc2, int list_every, long long energy_every,
+                  const FixDev &fix, const TipDev &tip, int has_pull, float rc2, int list_every, long long energy_every,
                   int n_steps, int stale, int mode, const long long *step_base, long long step_off,
                   hipStream_t s, const float *tscale = nullptr);
 // Replica exchange: the swaps of one round from the energies recorded in

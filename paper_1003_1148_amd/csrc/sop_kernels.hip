@@ -73,21 +73,50 @@ __device__ __forceinline__ int cell_index(const float4 &p, const int4 &off, cons
 }
 
 // Fixed-point copy of a position: hi + lo as a whole number of units of 2^-k
-// (StepConsts), modulo 2^32.  The difference of two copies, taken in 32-bit
-// integers, is exact whatever the distance of the residues from the origin,
-// as long as they are less than 2^31 units apart.  x - P rint(x / P) (P =
-// 2^32 units) is exact in double; adding 1.5 * 2^52 rounds it to a whole
-// number in the low word.
-__device__ __forceinline__ int fix_axis(float hi, float lo, const FixDev &f)
-{
-    const double x = (double)hi + (double)lo;
-    const double r = __builtin_fma(-f.period, __builtin_rint(x * f.inv_period), x);
-    return __double2loint(__builtin_fma(r, f.scale, 0x1.8p52));
-}
-
+// (FixDev), modulo 2^32, and in w ten bits an axis of the periods of 2^32
+// units below it.  The difference of two copies, taken in 32-bit integers, is
+// exact whatever the distance of the residues from the origin, as long as
+// they are less than 2^31 units apart.  x 2^k + 1.5 * 2^52, rounded once,
+// holds the whole number in its low word and the periods above it; farther
+// out than 2^50 units the periods are taken off first (x - P rint(x / P) is
+// exact), with the same bits.
 __device__ __forceinline__ int4 fix_pos(const float4 &hi, const float4 &lo, const FixDev &f)
 {
-    return make_int4(fix_axis(hi.x, lo.x, f), fix_axis(hi.y, lo.y, f), fix_axis(hi.z, lo.z, f), 0);
+    int q[3], n[3];
+    if (fmaxf(fmaxf(fabsf(hi.x), fabsf(hi.y)), fabsf(hi.z)) < f.direct) {
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            const double v = __builtin_fma((double)comp(hi, ax) + (double)comp(lo, ax), f.scale, 0x1.8p52);
+            q[ax] = __double2loint(v);
+            n[ax] = __double2hiint(v);
+        }
+    } else {
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            const double x = (double)comp(hi, ax) + (double)comp(lo, ax);
+            const double m = __builtin_rint(x * f.inv_period);
+            const double r = __builtin_fma(-f.period, m, x);
+            q[ax] = __double2loint(__builtin_fma(r, f.scale, 0x1.8p52));
+            n[ax] = __double2loint(m + 0x1.8p52) - (r < 0.0 && q[ax] < 0 ? 1 : 0);
+        }
+    }
+    return make_int4(q[0], q[1], q[2], (n[0] & 1023) | (n[1] & 1023) << 10 | (n[2] & 1023) << 20);
+}
+
+// Difference of two such positions up to 512 periods apart, exact before its
+// one rounding: the bits of the plain integer difference wherever that does
+// not wrap.
+__device__ __forceinline__ float3 fix_full_diff(const int4 &a, const int4 &b)
+{
+    const unsigned qa[3] = {(unsigned)a.x, (unsigned)a.y, (unsigned)a.z};
+    const unsigned qb[3] = {(unsigned)b.x, (unsigned)b.y, (unsigned)b.z};
+    float d[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        const int dn = (int)(((unsigned)(a.w >> (10 * ax)) - (unsigned)(b.w >> (10 * ax))) << 22) >> 22;
+        d[ax] = (float)__builtin_fma((double)dn, 4294967296.0, (double)qa[ax] - (double)qb[ax]);
+    }
+    return make_float3(d[0], d[1], d[2]);
 }
 
 // Difference of two fixed-point coordinates, modulo 2^32.
@@ -285,20 +314,6 @@ __device__ __forceinline__ void add_repulsive_q(Acc &A, const int3 &q, float s2,
         A.e_r += (double)(k.el * q6);
         A.vir += (double)(k.el6 * q6);
     }
-}
-
-// The same terms from compensated positions (hi, lo) of both residues.
-__device__ __forceinline__ void add_fene(Acc &A, const float4 &hi, const float4 &lo, const float4 &hj,
-                                         const float4 &lj, float r0, const PairConsts &k, bool rec,
-                                         bool &broken)
-{
-    add_fene_d(A, pair_delta(hi, lo, hj, lj), r0, k, rec, broken);
-}
-
-__device__ __forceinline__ void add_native(Acc &A, const float4 &hi, const float4 &lo, const float4 &hj,
-                                           const float4 &lj, float r0, const PairConsts &k, bool rec)
-{
-    add_native_d(A, pair_delta(hi, lo, hj, lj), r0 * r0, k, rec);
 }
 
 // Cantilever `pull` (index or -1) and tip on one residue at t_n = step*h.
@@ -1107,7 +1122,8 @@ __device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile
             flags |= WG_WIDE;
         if (!top.w)
             flags |= WG_IDS32;
-        wr = WgRec{fix_axis(o[0], 0.0f, a.fix), fix_axis(o[1], 0.0f, a.fix), fix_axis(o[2], 0.0f, a.fix), flags,
+        const int4 q = fix_pos(make_float4(o[0], o[1], o[2], 0.0f), make_float4(0.0f, 0.0f, 0.0f, 0.0f), a.fix);
+        wr = WgRec{q.x, q.y, q.z, flags,
                    first, tcnt, S, top.z, {0, 0, 0, 0}, {0, 0, 0, 0}};
     }
     // counts of passing and of written entries, times 512: entry c of the
@@ -1962,47 +1978,6 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
     }
 }
 
-__device__ __forceinline__ float ulp_of(float x)
-{
-    return __int_as_float(__float_as_int(x) & 0x7f800000) * 0x1p-23f;
-}
-
-// Batched schedule: each residue packs its low part in units of one quantum,
-// ulp/1000 of its largest high coordinate (no coarser than ulp/1000 of any
-// other), so that a partner's three fields take one exponent to unpack.
-__device__ __forceinline__ float res_quantum(const float4 &h)
-{
-    return ulp_of(fmaxf(fabsf(h.x), fmaxf(fabsf(h.y), fabsf(h.z)))) * 1.0e-3f;
-}
-
-__device__ __forceinline__ unsigned pack_low_res(const float4 &hi, const float4 &lo)
-{
-    const int E = (__float_as_int(fmaxf(fabsf(hi.x), fmaxf(fabsf(hi.y), fabsf(hi.z)))) >> 23) & 0xff;
-    // 1/quantum: a power of two (biased exponent 277 - E) times 1000
-    const float inv_q = (E >= 24 && E <= 253) ? __int_as_float((277 - E) << 23) * 1000.0f : 0.0f;
-    unsigned bitsw = 0u;
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        const int qv = (int)rintf(fminf(fmaxf(comp(lo, ax) * inv_q, -511.0f), 511.0f));
-        bitsw |= ((unsigned)qv & 0x3ffu) << (10 * ax);
-    }
-    return bitsw;
-}
-
-// hi_i + lo_i - (hj + its packed low part), per axis
-__device__ __forceinline__ float3 pair_delta_packed(const float4 &hi, const float4 &lo, const float4 &hj)
-{
-    const unsigned w = __float_as_uint(hj.w);
-    const float qm = res_quantum(hj);
-    float d[3];
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        const int qv = ((int)(w << (22 - 10 * ax))) >> 22;  // sign-extended 10-bit field
-        d[ax] = (comp(hi, ax) - comp(hj, ax)) + __builtin_fmaf(-(float)qv, qm, comp(lo, ax));
-    }
-    return make_float3(d[0], d[1], d[2]);
-}
-
 // ---------------------------------------------------------------------------
 // Pair-based forces (Algorithm 4 with the atomic additions its text proposes
 // for GPUs that have them, Algorithm 5's gathering folded into the update
@@ -2259,6 +2234,18 @@ __global__ __launch_bounds__(256) void k_pair_update(PairUpdArgs a)
 // resident in LDS for n_steps steps; the list of each residue is rebuilt in
 // LDS from all residues of its trajectory every list_every steps.
 // ---------------------------------------------------------------------------
+// The fixed-point position at byte offset `off` of the positions in LDS: one
+// 16-byte read, also where only the coordinates are used (the compiler makes
+// that a 12-byte one, which LDS serves no faster than two of 8 bytes: 4,096
+// chains 78.4 against 74.4 us a step).
+__device__ __forceinline__ int4 lds_pos(const char *base, unsigned off)
+{
+    typedef int vec4 __attribute__((ext_vector_type(4)));
+    const vec4 v = *reinterpret_cast<const vec4 *>(base + off);
+    asm volatile("" ::"v"(v));
+    return make_int4(v.x, v.y, v.z, v.w);
+}
+
 struct BatchArgs {
     const float4 *pin;
     float4 *pout;
@@ -2283,6 +2270,7 @@ struct BatchArgs {
     long long energy_every;
     int n_steps, list_every, stale, cap, has_pull;
     StepConsts c;
+    FixDev fix;
     TipDev tip;
     float rc2;
 };
@@ -2305,21 +2293,32 @@ __device__ __forceinline__ double traj_sum(double *red, int t, bool act, double 
 // pair by pair in row order, so the sum does not depend on the lane or on
 // the packing. Which lane sums which row is chosen at each list rebuild by a
 // counting sort on the row length (longest first), so the lanes of a wave
-// run loops of about the same length.
+// run loops of about the same length; which lane sums which bonded and native
+// entries, once a launch by their number.
+// Bound by vector instructions when the chip is full (their issue filled
+// 99.8% of the cycles before the following): integer differences of
+// fixed-point positions in place of float ones with packed low parts, rows
+// without padding, sorted native entries, and list entries shifted through
+// one word as they are found.  4,096 chains of 50-500 residues 75.6 -> 62.4 us
+// a step, 200 chains (111 packs: latency of one pack) 14.9 -> 11.5, 384 chains
+// of the exchange ladder 15.4 -> 12.3.
 constexpr int NBUCKET = 64;
 
 template <int WGS, int MODE>
 __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
 {
     constexpr int TCAP = 8 * WGS;  // bonded/native entries of a pack kept in LDS
-    __shared__ float4 shh[WGS + 1];     // {hi.xyz, packed lo} per residue; slot WGS: the far-away empty slot
-    __shared__ float4 shl[WGS + 1];     // lo per residue
+    // per residue: its fixed-point position and periods; its high part while
+    // the list is rebuilt
+    __shared__ int4 sq[WGS];
+    float4 *shh = reinterpret_cast<float4 *>(sq);
     __shared__ double red[WGS];         // trajectory sums
-    __shared__ unsigned short tpart[TCAP];  // bonded/native entries of the pack: local partner
+    __shared__ unsigned short tpart[TCAP];  // bonded/native entries of the pack: byte offset in sq
     __shared__ float tr0[TCAP];             // ... and r0 (CSR in slot order)
     __shared__ unsigned short tex[TCAP];    // the same partners in ascending order (list exclusions)
     __shared__ int perm[WGS];           // row summed by each lane: residue | chunks << 16
     __shared__ float lsum[3][WGS];      // list force of each residue
+    __shared__ float tsum[3][WGS];      // bonded and native force of each residue
     __shared__ int hist[NBUCKET];
     __shared__ int sres[WGS];           // residue of each local slot
     __shared__ float3 bblo[WGS / 32], bbhi[WGS / 32];  // list rebuild: boxes of 32-slot blocks
@@ -2343,14 +2342,10 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
         thi = a.traj_hi[i] + shift;
         row = a.trow[i];
         cnt = a.list_cnt[i];
-        shh[t] = make_float4(hi.x, hi.y, hi.z, __uint_as_float(pack_low_res(hi, lo)));
-        shl[t] = lo;
     }
+    int4 qi = fix_pos(hi, lo, a.fix);
+    sq[t] = qi;
     sres[t] = i;
-    if (t == 0) {
-        shh[WGS] = make_float4(1.0e18f, 1.0e18f, 1.0e18f, 0.0f);
-        shl[WGS] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
     const int nb = row.y & 4095, ntop = nb + (row.y >> 12);
     // the pack's bonded/native entries in LDS (entries past TCAP stay in
     // global memory); perm is the scan's workspace until the first assignment
@@ -2360,8 +2355,8 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
     for (int e = 0; e < ntop && toff + e < TCAP; ++e) {
         const float2 te = a.tent[row.x + e];
         const unsigned short j = (unsigned short)(__float_as_int(te.x) + shift);
-        tpart[toff + e] = j;
-        tr0[toff + e] = te.y;
+        tpart[toff + e] = (unsigned short)(j << 4);
+        tr0[toff + e] = e < nb ? te.y : te.y * te.y;  // natives: r0^2
         if (top_lds) {  // insertion into the ascending copy
             int k = e;
             while (k > 0 && tex[toff + k - 1] > j) {
@@ -2372,7 +2367,7 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
         }
     }
     auto partner = [&](int e) {
-        return toff + e < TCAP ? (int)tpart[toff + e] : __float_as_int(a.tent[row.x + e].x) + shift;
+        return toff + e < TCAP ? (int)tpart[toff + e] >> 4 : __float_as_int(a.tent[row.x + e].x) + shift;
     };
     // rows are residue-major: entry k (a local slot) of residue i at i cap + k
     unsigned short *lrow16 = a.list + (size_t)i * a.cap;
@@ -2385,18 +2380,15 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
         cn.c_noise *= a.tscale[traj];
     const unsigned stream = act ? a.stream_ids[traj] : 0u;
 
-    // lane -> row assignment: counting sort of the rows by chunk count,
-    // longest first (ties in any order; the sums do not depend on it)
-    int my = 0;   // local slot | chunks << 16 of the row this lane sums
-    int myg = 0;  // its residue
-    auto assign = [&]() {
-        const int nch = act ? (min(cnt, a.cap) + 3) >> 2 : 0;
-        const int key = NBUCKET - 1 - min(nch, NBUCKET - 1);
+    // Counting sort of the pack's slots by `key` (0 <= key < NBUCKET), largest
+    // first, ties in any order (no sum depends on which lane takes it): the
+    // packed value of the slot this lane takes.
+    auto sorted = [&](int key, int value) -> int {
         if (t < NBUCKET)
             hist[t] = 0;
         __syncthreads();
         if (act)
-            atomicAdd(&hist[key], 1);
+            atomicAdd(&hist[NBUCKET - 1 - key], 1);
         __syncthreads();
         if (t < 64) {  // one wave scans the buckets
             const int v = t < NBUCKET ? hist[t] : 0;
@@ -2412,18 +2404,73 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
         }
         __syncthreads();
         if (act)
-            perm[atomicAdd(&hist[key], 1)] = t | (nch << 16);
+            perm[atomicAdd(&hist[NBUCKET - 1 - key], 1)] = value;
         __syncthreads();
-        my = t < n ? perm[t] : 0;
+        return t < n ? perm[t] : 0;
+    };
+
+    // lane -> row assignment: by length in chunks, anew at each list rebuild
+    int my = 0;   // local slot | partners << 16 of the row this lane sums
+    int myg = 0;  // its residue
+    auto assign = [&]() {
+        const int c = act ? min(cnt, a.cap) : 0;
+        my = sorted(min((c + 3) >> 2, NBUCKET - 1), t | (c << 16));
         myg = sres[my & 0xffff];
     };
+
+    // lane -> bonded and native entries: by number, once a launch (the longest
+    // of 64 residues in slot order has about 8 natives where the mean is 3)
     __syncthreads();
-    if (!(a.stale || s0 % a.list_every == 0))
+    const int tr = sorted(min(ntop, NBUCKET - 1), t);  // the slot whose entries this lane sums
+    int *tq = reinterpret_cast<int *>(tsum[0]);
+    tq[t] = toff;
+    tq[WGS + t] = nb | (ntop << 12);
+    tq[2 * WGS + t] = row.x;
+    __syncthreads();
+    const int tr_off = tq[tr], tr_x = tq[2 * WGS + tr];
+    const int tr_nb = t < n ? tq[WGS + tr] & 4095 : 0, tr_ntop = t < n ? tq[WGS + tr] >> 12 : 0;
+    const int tr_shift = tr - sres[tr];
+    const bool tr_lds = tr_off + tr_ntop <= TCAP;
+    // entry e of residue `slot` (its entries at `x` and, in LDS, at `off0`)
+    auto entry = [&](int off0, int x, int sh, int nbond, int e, int &j, float &r0) {
+        if (off0 + e < TCAP) {
+            j = tpart[off0 + e];
+            r0 = tr0[off0 + e];
+        } else {
+            const float2 te = a.tent[x + e];
+            j = (__float_as_int(te.x) + sh) << 4;
+            r0 = e < nbond ? te.y : te.y * te.y;
+        }
+    };
+    const char *sqb = reinterpret_cast<const char *>(sq);
+
+    // one of tr's partners is out of reach of plain integer differences until
+    // the next rebuild (the full ones give the same bits within it)
+    bool far = false;
+    auto check_reach = [&]() {
+        far = false;
+        const float lim = a.fix.reach * (float)a.fix.scale;
+        const int4 p = sq[tr];
+        for (int e = 0; e < tr_ntop; ++e) {
+            int j;
+            float r0;
+            entry(tr_off, tr_x, tr_shift, tr_nb, e, j, r0);
+            const float3 d = fix_full_diff(p, lds_pos(sqb, j));
+            far |= !(fmaxf(fabsf(d.x), fmaxf(fabsf(d.y), fabsf(d.z))) <= lim);
+        }
+    };
+    __syncthreads();
+    if (!(a.stale || s0 % a.list_every == 0)) {
+        check_reach();
         assign();
+    }
 
     for (int q = 0; q < a.n_steps; ++q) {
         const long long step = s0 + q;
         if ((q == 0 && a.stale) || step % a.list_every == 0) {
+            check_reach();
+            __syncthreads();
+            shh[t] = hi;  // the high parts, until the rows are written
             {
                 // boxes of the 32-slot blocks (empty slots add nothing)
                 float3 bl = act ? make_float3(hi.x, hi.y, hi.z) : make_float3(3.0e38f, 3.0e38f, 3.0e38f);
@@ -2471,13 +2518,13 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                     unsigned m = 0u;
 #pragma unroll 1
                     for (int u0 = 0; u0 < 32; u0 += 8) {
-                        float4 q[8];
+                        float4 c8[8];
 #pragma unroll
                         for (int u = 0; u < 8; ++u)
-                            q[u] = shh[j0 + u0 + u];
+                            c8[u] = shh[j0 + u0 + u];
 #pragma unroll
                         for (int u = 0; u < 8; ++u)
-                            m = m + m + (within_cutoff(hi, q[u], a.rc2) ? 1u : 0u);
+                            m = m + m + (within_cutoff(hi, c8[u], a.rc2) ? 1u : 0u);
                     }
                     m &= 0xffffffffu >> max(tlo - j0, 0);
                     if (thi - j0 < 32)
@@ -2500,40 +2547,31 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                             drop(partner(e));
                     }
                     m &= ~x;
+                    // four entries pass through one 64-bit word, the newest on top
                     while (m) {
                         const int u = __builtin_clz(m);
-                        const unsigned v = (unsigned)(j0 + u);
-                        m ^= 0x80000000u >> u;
-                        const int sl = cnt & 3;
-                        if (sl == 0)
-                            w_lo = v;
-                        else if (sl == 1)
-                            w_lo |= v << 16;
-                        else if (sl == 2)
-                            w_hi = v;
-                        else
-                            w_hi |= v << 16;
+                        const unsigned v = (unsigned)(j0 + u) << 4;  // byte offset in sq (one workgroup holds 1,024)
+                        m &= 0x7fffffffu >> u;
+                        w_lo = __builtin_amdgcn_alignbit(w_hi, w_lo, 16);
+                        w_hi = __builtin_amdgcn_alignbit(v, w_hi, 16);
                         ++cnt;
                         if ((cnt & 3) == 0 && cnt <= a.cap)
                             rowp[(cnt >> 2) - 1] = make_uint2(w_lo, w_hi);
                     }
                 }
-                // pad the last chunk with the empty slot (its term is exactly zero)
-                const int sl = cnt & 3;
-                if (sl != 0 && cnt < a.cap) {
-                    const unsigned e2 = (unsigned)WGS | ((unsigned)WGS << 16);
-                    if (sl == 1)
-                        rowp[cnt >> 2] = make_uint2(w_lo | ((unsigned)WGS << 16), e2);
-                    else if (sl == 2)
-                        rowp[cnt >> 2] = make_uint2(w_lo, e2);
-                    else
-                        rowp[cnt >> 2] = make_uint2(w_lo, w_hi | ((unsigned)WGS << 16));
+                // the last chunk, if not whole
+                if ((cnt & 3) != 0 && cnt < a.cap) {
+                    const int sh = 16 * (4 - (cnt & 3));
+                    const unsigned long long w = ((unsigned long long)w_hi << 32 | w_lo) >> sh;
+                    rowp[cnt >> 2] = make_uint2((unsigned)w, (unsigned)(w >> 32));
                 }
                 if (cnt > a.cap)
                     atomicOr(a.err, ERR_OVERFLOW);
                 a.list_cnt[i] = cnt;
             }
             assign();  // its barriers also publish the rows written above
+            sq[t] = qi;
+            __syncthreads();
         }
         // mode 0 never records (no FP64 sums in its registers); mode 2
         // records at multiples of the energy interval, in a copy of the
@@ -2543,82 +2581,132 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
             constexpr bool rec = decltype(rec_tag)::value;
             {
                 // ---- list partners (forces) of the row this lane was given ----
-                const int r = my & 0xffff, nch = my >> 16;
-                const float4 ph = shh[r], pl = shl[r];
-                // rows are read two chunks (16 bytes) at a time, the next pair
-                // requested before the current one is used
+                const int r = my & 0xffff;
+                const int n8 = my >> 19;
+                const int4 pr = sq[r];
+                // rows are read eight entries (16 bytes) at a time, the next
+                // ones requested before the current ones are used
                 const uint4 *rp = reinterpret_cast<const uint4 *>(a.list + (size_t)myg * a.cap);
-                const int nc2 = (nch + 1) >> 1;
                 Acc L;  // the row's sum, pair by pair in row order
-                auto chunk = [&](unsigned wx, unsigned wy) {
-                    const unsigned idx[4] = {wx & 0xffffu, wx >> 16, wy & 0xffffu, wy >> 16};
-                    // one 16-byte read a partner: the high part and its packed
-                    // low part (10-bit multiples of the partner's quantum)
-                    float4 qh[4];
+                auto sweep = [&](auto list_far) {
+                    // four partners, `m` of them the row's (all of them: a constant)
+                    auto chunk = [&](unsigned wx, unsigned wy, auto m) {
+                        const unsigned off[4] = {wx & 0xffffu, wx >> 16, wy & 0xffffu, wy >> 16};
+                        int4 pj[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        qh[u] = shh[idx[u]];
+                        for (int u = 0; u < 4; ++u)
+                            pj[u] = lds_pos(sqb, u < m ? off[u] : 0u);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        add_repulsive_u(L, pair_delta_packed(ph, pl, qh[u]), kc, false);
+                        for (int u = 0; u < 4; ++u) {
+                            if (list_far()) {
+                                const float3 d = fix_full_diff(pr, pj[u]);
+                                if (u < m)
+                                    add_repulsive_u(L,
+                                                    make_float3(d.x * a.fix.unit, d.y * a.fix.unit, d.z * a.fix.unit),
+                                                    kc, false);
+                            } else {
+                                add_repulsive_q(L, make_int3(fix_diff(pr.x, pj[u].x), fix_diff(pr.y, pj[u].y),
+                                                             fix_diff(pr.z, pj[u].z)),
+                                                a.fix.s2, kc, u < m, false);
+                            }
+                        }
+                    };
+                    const int last = max((my >> 16) - 1, 0) >> 3;
+                    uint4 w = rp[0];
+                    for (int c = 0; c < n8; ++c) {
+                        const uint4 wn = rp[min(c + 1, last)];
+                        chunk(w.x, w.y, std::integral_constant<int, 4>{});
+                        chunk(w.z, w.w, std::integral_constant<int, 4>{});
+                        w = wn;
+                    }
+                    const int left = (my >> 16) & 7;
+                    if (left > 0)
+                        chunk(w.x, w.y, left);
+                    if (left > 4)
+                        chunk(w.z, w.w, left - 4);
                 };
-                uint4 w = rp[0];
-                for (int c2 = 0; c2 < nc2; ++c2) {
-                    const uint4 wn = rp[min(c2 + 1, nc2 - 1)];
-                    chunk(w.x, w.y);
-                    if (2 * c2 + 1 < nch)  // the second chunk of an odd row's last pair is not written
-                        chunk(w.z, w.w);
-                    w = wn;
-                }
+                if (a.fix.list_far)
+                    sweep(std::true_type{});
+                else
+                    sweep(std::false_type{});
                 if (t < n) {
-                    lsum[0][r] = kc.c6 * L.fx;
-                    lsum[1][r] = kc.c6 * L.fy;
-                    lsum[2][r] = kc.c6 * L.fz;
+                    const float ls = a.fix.list_far ? kc.c6 : kc.c6 * a.fix.unit;
+                    lsum[0][r] = ls * L.fx;
+                    lsum[1][r] = ls * L.fy;
+                    lsum[2][r] = ls * L.fz;
                 }
             }
             Acc A;  // energy sums are only accumulated on record steps
             bool broken = false;
             double e_x = 0.0, f_rep = 0.0;
-            if (act) {
-                // bonded, then native partners: two loops, so a wave whose
-                // residues have different bond counts (chain ends) runs each
-                // term's code alone
-                auto entry = [&](int e, int &j, float &r0) {
-                    if (toff + e < TCAP) {
-                        j = tpart[toff + e];
-                        r0 = tr0[toff + e];
-                    } else {
-                        const float2 te = a.tent[row.x + e];
-                        j = __float_as_int(te.x) + shift;
-                        r0 = te.y;
+            // ---- bonded, then native partners: two loops, so a wave whose
+            // residues have different bond counts (chain ends) runs each
+            // term's code alone.  Record steps take every lane's own residue
+            // (its energies belong there), others the slot sorted to the lane.
+            {
+                auto terms = [&](const int4 &p, int off0, int x, int sh, int nbond, int nall, auto general) {
+                    auto next = [&](int e, int &j, float &r0) -> float3 {
+                        if (general()) {
+                            entry(off0, x, sh, nbond, e, j, r0);
+                            return fix_full_diff(p, lds_pos(sqb, j));
+                        }
+                        j = tpart[off0 + e];
+                        r0 = tr0[off0 + e];
+                        const int4 o = lds_pos(sqb, j);
+                        return make_float3((float)fix_diff(p.x, o.x), (float)fix_diff(p.y, o.y),
+                                           (float)fix_diff(p.z, o.z));
+                    };
+                    for (int e = 0; e < nbond; ++e) {
+                        int j;
+                        float r0;
+                        const float3 d = next(e, j, r0);
+                        add_fene_d(A, make_float3(d.x * a.fix.unit, d.y * a.fix.unit, d.z * a.fix.unit), r0, kc, rec,
+                                   broken);
+                    }
+                    for (int e = nbond; e < nall; ++e) {
+                        int j;
+                        float r0;
+                        const float3 d = next(e, j, r0);
+                        add_native_q(A, d, r0, a.fix.s2, kc.eh12 * a.fix.unit, kc, rec);
                     }
                 };
-                for (int e = 0; e < nb; ++e) {
-                    int j;
-                    float r0;
-                    entry(e, j, r0);
-                    add_fene(A, hi, lo, shh[j], shl[j], r0, kc, rec, broken);
+                if (rec) {
+                    terms(qi, toff, row.x, shift, nb, ntop, std::true_type{});
+                } else {
+                    const int4 p = sq[tr];
+                    if (__any(far || !tr_lds))
+                        terms(p, tr_off, tr_x, tr_shift, tr_nb, tr_ntop, std::true_type{});
+                    else
+                        terms(p, tr_off, tr_x, tr_shift, tr_nb, tr_ntop, std::false_type{});
+                    if (t < n) {
+                        tsum[0][tr] = A.fx;
+                        tsum[1][tr] = A.fy;
+                        tsum[2][tr] = A.fz;
+                    }
+                    __syncthreads();
+                    A.fx = tsum[0][t];
+                    A.fy = tsum[1][t];
+                    A.fz = tsum[2][t];
                 }
-                for (int e = nb; e < ntop; ++e) {
-                    int j;
-                    float r0;
-                    entry(e, j, r0);
-                    add_native(A, hi, lo, shh[j], shl[j], r0, kc, rec);
-                }
+            }
+            if (broken)
+                atomicOr(a.err, ERR_FENE);
+            if (act) {
                 add_external(A, e_x, f_rep, hi, lo, step, a.c.h, a.has_pull ? a.pull_slot[i] : -1, a.pulls,
                              a.tip, rec, a.err);
-                if (broken)
-                    atomicOr(a.err, ERR_FENE);
                 if (rec) {
                     // record steps: the repulsive energy and virial over the own row
                     Acc E;
-                    for (int k = 0; k < min(cnt, a.cap); ++k)
-                        add_repulsive_d(E, pair_delta(hi, lo, shh[lrow16[k]], shl[lrow16[k]]), kc, true);
+                    for (int k = 0; k < min(cnt, a.cap); ++k) {
+                        const float3 d = fix_full_diff(qi, sq[lrow16[k] >> 4]);
+                        add_repulsive_d(E, make_float3(d.x * a.fix.unit, d.y * a.fix.unit, d.z * a.fix.unit), kc, true);
+                    }
                     A.e_r = E.e_r;
                     A.vir += E.vir;
                 }
             }
-            __syncthreads();
+            if (rec)
+                __syncthreads();
             if (act) {
                 A.fx += lsum[0][t];
                 A.fy += lsum[1][t];
@@ -2645,8 +2733,8 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
             }
             if (act) {
                 langevin_update(hi, lo, A, step, stream, cn, a.err);
-                shh[t] = make_float4(hi.x, hi.y, hi.z, __uint_as_float(pack_low_res(hi, lo)));
-                shl[t] = lo;
+                qi = fix_pos(hi, lo, a.fix);
+                sq[t] = qi;
             }
             __syncthreads();
         };
@@ -3106,7 +3194,7 @@ void launch_step(const DevBufs &b, int cur, int n, int cap, int tile, const Step
 }
 
 void launch_batch(const DevBufs &b, int cur, int n_packs, int wg, int cap, const StepConsts &c,
-                  const TipDev &tip, int has_pull, float rc2, int list_every, long long energy_every,
+                  const FixDev &fix, const TipDev &tip, int has_pull, float rc2, int list_every, long long energy_every,
                   int n_steps, int stale, int mode, const long long *step_base, long long step_off,
                   hipStream_t s, const float *tscale)
 {
@@ -3137,6 +3225,7 @@ void launch_batch(const DevBufs &b, int cur, int n_packs, int wg, int cap, const
     a.cap = cap;
     a.has_pull = has_pull;
     a.c = c;
+    a.fix = fix;
     a.tip = tip;
     a.rc2 = rc2;
     a.tscale = tscale;
