@@ -3,6 +3,7 @@
 // step driver with HIP-graph replays of whole list periods, and the
 // asynchronous device error word.
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -563,6 +564,23 @@ long long last_record(const sop_ctx *c, long long first, long long n)
     const long long last = first + n - 1;
     const long long r = last - last % E;
     return r >= first ? r : -1;
+}
+
+// Batched schedule: steps one launch may take from `step` on.  A record step
+// is a launch of its own where the interval is at least REC_SPLIT: the kernel
+// compiled for both kinds of steps takes 20% longer over the others than the
+// one without records, a launch more costs about two steps (4,096 chains, us a
+// step with launches of both kinds and split: 75.8 and 88.4 at an interval of
+// 8, 73.6 and 73.7 at 16, 71.7 and 61.2 at 100; 200 chains 14.8 and 16.5, 14.3
+// and 13.9, 14.2 and 11.8).
+constexpr long long REC_SPLIT = 16;
+
+long long record_span(const sop_ctx *c, long long step)
+{
+    const long long E = c->energy_every;
+    if (E < REC_SPLIT)
+        return INT_MAX;
+    return step % E == 0 ? 1 : E - step % E;
 }
 
 // Batched schedule: a graph of one persistent launch of batch_steps steps plus
@@ -1560,6 +1578,7 @@ sop_status sop_step(sop_ctx *c, int64_t n_steps)
             long long k = std::min<long long>(K, n_steps - q);
             if (X > 0)
                 k = std::min<long long>(k, X - c->step % X);  // stop at the next exchange
+            k = std::min<long long>(k, record_span(c, c->step));
             const long long rec = last_record(c, c->step, k);
             if (c->graph_steps > 0 && c->list_valid && k == K && X == 0) {
                 const int rg = rec >= 0 ? 1 : 0;

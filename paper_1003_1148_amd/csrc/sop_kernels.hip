@@ -2275,18 +2275,33 @@ struct BatchArgs {
     float rc2;
 };
 
-// Deterministic per-trajectory sum of one value per residue held in `red`;
-// the first residue of each trajectory adds its trajectory's values in order.
-__device__ __forceinline__ double traj_sum(double *red, int t, bool act, double v, int tlo, int thi)
+// Deterministic per-trajectory sums of three values per residue: a tree over
+// the residue's index in its trajectory, so the sums do not depend on where
+// the pack holds it.  `red` is three doubles a slot; the first residue of the
+// trajectory returns the sums.  (One lane that added a trajectory's values in
+// order, one value after the other, made a force evaluation of the 384 chains
+// of the exchange ladder 87 us; with the tree 57, and 46 with the list energies
+// taken in the force sweep.)
+template <int WGS>
+__device__ __forceinline__ void traj_sums(double *red, int t, double (&v)[3], int tlo, int thi)
 {
-    red[t] = act ? v : 0.0;
     __syncthreads();
-    double s = 0.0;
-    if (act && t == tlo)
-        for (int u = tlo; u < thi; ++u)
-            s += red[u];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        red[k * WGS + t] = v[k];
     __syncthreads();
-    return s;
+#pragma unroll 1
+    for (int o = WGS / 2; o > 0; o >>= 1) {
+        if (t - tlo < o && t + o < thi) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                red[k * WGS + t] += red[k * WGS + t + o];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        v[k] = red[k * WGS + t];
 }
 
 // Batched schedule: the list partners of a residue are summed by one lane,
@@ -2312,13 +2327,15 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
     // the list is rebuilt
     __shared__ int4 sq[WGS];
     float4 *shh = reinterpret_cast<float4 *>(sq);
-    __shared__ double red[WGS];         // trajectory sums
     __shared__ unsigned short tpart[TCAP];  // bonded/native entries of the pack: byte offset in sq
     __shared__ float tr0[TCAP];             // ... and r0 (CSR in slot order)
     __shared__ unsigned short tex[TCAP];    // the same partners in ascending order (list exclusions)
     __shared__ int perm[WGS];           // row summed by each lane: residue | chunks << 16
-    __shared__ float lsum[3][WGS];      // list force of each residue
-    __shared__ float tsum[3][WGS];      // bonded and native force of each residue
+    // list force, then bonded and native force of each residue; the
+    // trajectory sums of a record step
+    __shared__ __align__(8) float fsum[6][WGS];
+    float (*lsum)[WGS] = fsum, (*tsum)[WGS] = fsum + 3;
+    __shared__ double esum[2][MODE == 0 ? 1 : WGS];  // record steps: list energy and virial of each residue
     __shared__ int hist[NBUCKET];
     __shared__ int sres[WGS];           // residue of each local slot
     __shared__ float3 bblo[WGS / 32], bbhi[WGS / 32];  // list rebuild: boxes of 32-slot blocks
@@ -2370,7 +2387,7 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
         return toff + e < TCAP ? (int)tpart[toff + e] >> 4 : __float_as_int(a.tent[row.x + e].x) + shift;
     };
     // rows are residue-major: entry k (a local slot) of residue i at i cap + k
-    unsigned short *lrow16 = a.list + (size_t)i * a.cap;
+    uint2 *rowp = reinterpret_cast<uint2 *>(a.list + (size_t)i * a.cap);
     const long long s0 = (a.step_base ? *a.step_base : 0) + a.step_off;
     const PairConsts kc = pair_consts(a.c);
     const int traj = __float_as_int(lo.w);
@@ -2496,7 +2513,6 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                 // a bit word (blocks whose box is out of reach of every lane of
                 // the wave are skipped); the row is written four entries (one
                 // 8-byte chunk) at a time.
-                uint2 *rowp = reinterpret_cast<uint2 *>(lrow16);
                 unsigned w_lo = 0u, w_hi = 0u;
                 int ep = 0;  // next entry of the ascending exclusion list
                 cnt = 0;
@@ -2603,11 +2619,11 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                                 if (u < m)
                                     add_repulsive_u(L,
                                                     make_float3(d.x * a.fix.unit, d.y * a.fix.unit, d.z * a.fix.unit),
-                                                    kc, false);
+                                                    kc, rec);
                             } else {
                                 add_repulsive_q(L, make_int3(fix_diff(pr.x, pj[u].x), fix_diff(pr.y, pj[u].y),
                                                              fix_diff(pr.z, pj[u].z)),
-                                                a.fix.s2, kc, u < m, false);
+                                                a.fix.s2, kc, u < m, rec);
                             }
                         }
                     };
@@ -2634,6 +2650,10 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                     lsum[0][r] = ls * L.fx;
                     lsum[1][r] = ls * L.fy;
                     lsum[2][r] = ls * L.fz;
+                    if (rec) {
+                        esum[0][r] = L.e_r;
+                        esum[1][r] = L.vir;
+                    }
                 }
             }
             Acc A;  // energy sums are only accumulated on record steps
@@ -2694,16 +2714,6 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
             if (act) {
                 add_external(A, e_x, f_rep, hi, lo, step, a.c.h, a.has_pull ? a.pull_slot[i] : -1, a.pulls,
                              a.tip, rec, a.err);
-                if (rec) {
-                    // record steps: the repulsive energy and virial over the own row
-                    Acc E;
-                    for (int k = 0; k < min(cnt, a.cap); ++k) {
-                        const float3 d = fix_full_diff(qi, sq[lrow16[k] >> 4]);
-                        add_repulsive_d(E, make_float3(d.x * a.fix.unit, d.y * a.fix.unit, d.z * a.fix.unit), kc, true);
-                    }
-                    A.e_r = E.e_r;
-                    A.vir += E.vir;
-                }
             }
             if (rec)
                 __syncthreads();
@@ -2711,20 +2721,28 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                 A.fx += lsum[0][t];
                 A.fy += lsum[1][t];
                 A.fz += lsum[2][t];
+                if (rec) {
+                    A.e_r = esum[0][t];
+                    A.vir += esum[1][t];
+                }
             }
             if (rec) {
                 // each internal pair appears in both partners' rows
-                const double vals[RES_E] = {0.5 * A.e_b, 0.5 * A.e_n, 0.5 * A.e_r, e_x, 0.5 * A.vir, f_rep};
+                double *red = reinterpret_cast<double *>(fsum[0]);
+                double v0[3] = {0.5 * A.e_b, 0.5 * A.e_n, 0.5 * A.e_r}, v1[3] = {e_x, 0.5 * A.vir, f_rep};
+                traj_sums<WGS>(red, t, v0, tlo, thi);
+                traj_sums<WGS>(red, t, v1, tlo, thi);
+                if (act && t == tlo) {
+                    const double vals[RES_E] = {v0[0], v0[1], v0[2], v1[0], v1[1], v1[2]};
 #pragma unroll
-                for (int kk = 0; kk < RES_E; ++kk) {
-                    const double sum = traj_sum(red, t, act, vals[kk], tlo, thi);
-                    if (act && t == tlo) {
+                    for (int kk = 0; kk < RES_E; ++kk) {
                         if (kk < SOP_NTERMS)
-                            a.energy[(size_t)traj * SOP_NTERMS + kk] = sum;
+                            a.energy[(size_t)traj * SOP_NTERMS + kk] = vals[kk];
                         else
-                            a.f_ext[traj] = sum;
+                            a.f_ext[traj] = vals[kk];
                     }
                 }
+                __syncthreads();
             }
             if (MODE == 1) {
                 if (act)

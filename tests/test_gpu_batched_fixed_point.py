@@ -81,3 +81,22 @@ def test_beyond_the_direct_conversion(P, d):  # noqa: F811
         assert len(c.get_pairlist()) > 40
         c.close()
     assert np.array_equal(F[0], F[1])
+
+
+@pytest.mark.parametrize("wg", [256, 1024])
+@pytest.mark.parametrize("every", [15, 16, 17, 40])
+def test_record_launches(P, every, wg):  # noqa: F811
+    """Energy intervals around the one from which a record step is a launch of
+    its own: positions and the last record bit for bit those of one step a
+    call on the other workgroup size."""
+    w = saw_batch(np.array([170, 60, 33]), np.random.default_rng(11))
+    s = _system("records", [[v] for v in w])
+    got = []
+    for wg_, calls in ((wg, [7, 43, 6]), (1280 - wg, [1] * 56)):
+        c = P.from_system(s, RunParams(), schedule="batched", batch=(wg_, 20), energy_every=every)
+        for n in calls:
+            c.step(n)
+        got.append((c.get_coordinates(), *c.get_energies()))
+        c.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
