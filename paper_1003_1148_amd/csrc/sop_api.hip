@@ -204,6 +204,7 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
     d.re_stats = (unsigned long long *)take((plain ? 0 : 2 * T) * sizeof(unsigned long long));
     d.eacc = (double4 *)take((plain ? n : 0) * sizeof(double4));
     d.stage = (int *)take(stage_elems * sizeof(int));
+    d.stage_raw = (int *)take(stage_elems * sizeof(int));
     d.stage16 = (unsigned short *)take(stage_elems * sizeof(unsigned short));
     d.stage_cnt = (int *)take(n_tiles_max * sizeof(int));
     d.pack_off = (int *)take((T + 1) * sizeof(int));

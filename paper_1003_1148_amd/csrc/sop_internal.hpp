@@ -123,6 +123,7 @@ struct DevBufs {
     float4 *facc;            // plain, pair-based forces: per-residue force accumulator
     double4 *eacc;           // plain, pair-based forces: per-residue energy accumulator
     int *stage;       // plain: per tile, global ids of its slots (stage_max per tile)
+    int *stage_raw;   // the same in the search's order
     unsigned short *stage16;  // plain: the same less the tile's lowest id (tile_top), where all
                               // differences fit 16 bits: half the bytes of every step's ids
     int *stage_cnt;   // plain: slots per tile

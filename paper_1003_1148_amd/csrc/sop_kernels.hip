@@ -1266,6 +1266,7 @@ __global__ __launch_bounds__(256, NL == 1 ? 2 : 5) void k_filter(FilterArgs a)
 struct CanonArgs {
     const int *tile_first;
     const int2 *trow;
+    const int *stage_raw;
     int *stage;
     const int *stage_cnt;
     const unsigned short *rows;  // the search's rows, by residue
@@ -1287,20 +1288,16 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
     using R = Rows<TILE, NL>;
     constexpr int RW = R::RW, W = R::W;
     constexpr int SM = stage_max<TILE>();
-    constexpr int G = RW < 32 ? RW : 32;  // rows per pass
-    constexpr int NLG = 8;          // lanes reading one row
-    constexpr int MW = SM / 32;     // mask words per row
-    constexpr int MWP = MW + 1;     // their stride: a row's word w in another bank than its neighbour's
+    constexpr int MW = SM / 32;     // mask words per row, at most
     constexpr int BW = 2048;        // bitmap words: ids spanning up to 65,536 values
-    // the ranks (ids, bitmap, word prefixes) and the row masks use one
-    // region in turn, so that three workgroups fit a CU
-    constexpr int P1 = (SM + 2 * BW) * 4, P2 = (G * MWP + NL * MW) * 4;
-    __shared__ __align__(16) unsigned char region[P1 > P2 ? P1 : P2];
+    // the ranks (ids, bitmap, word prefixes) and the masks use one region in
+    // turn, so that three workgroups fit a CU
+    constexpr int P1 = SM + 2 * BW, P2 = NL * MW + 32 * (MW + 1);
+    constexpr int WORDS = P1 > P2 ? P1 : P2;
+    __shared__ unsigned region[WORDS];
     int *sid = reinterpret_cast<int *>(region);
-    unsigned *bmp = reinterpret_cast<unsigned *>(region + SM * 4);
-    int *wpre = reinterpret_cast<int *>(region + (SM + BW) * 4);
-    unsigned *mask = reinterpret_cast<unsigned *>(region);
-    unsigned *cmask = mask + G * MWP;
+    unsigned *bmp = region + SM;
+    int *wpre = reinterpret_cast<int *>(region + SM + BW);
     __shared__ unsigned short nslot[SM];
     __shared__ unsigned char cls[SM];
     __shared__ short slen[TILE], sord[TILE];
@@ -1308,9 +1305,10 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
     __shared__ int id_lo, id_hi;
     if (*a.skin_flag == 0u)
         return;  // no search ran (uniform over the grid)
-    const int tile = blockIdx.x, t = threadIdx.x;
+    const int wg = blockIdx.x, tile = wg / W, w = wg % W, t = threadIdx.x;
     const int first = a.tile_first[tile], tcnt = a.tile_first[tile + 1] - first;
     const int S = min(a.stage_cnt[tile], SM);
+    const int *raw = a.stage_raw + (size_t)tile * SM;
     int *st = a.stage + (size_t)tile * SM;
     if (t == 0) {
         id_lo = 0x7fffffff;
@@ -1320,7 +1318,7 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
     {
         int mn = 0x7fffffff, mx = -1;
         for (int k = t; k < S; k += 256) {
-            const int id = st[k];
+            const int id = raw[k];
             sid[k] = id;
             mn = min(mn, id);
             mx = max(mx, id);
@@ -1374,13 +1372,17 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
     }
     __syncthreads();
     for (int k = t; k < S; k += 256) {
-        st[nslot[k]] = sid[k];
-        a.stage16[(size_t)tile * SM + nslot[k]] = (unsigned short)(sid[k] - lo);
         cls[nslot[k]] = (unsigned char)(sid[k] & (NL - 1));
+        if (w == 0) {
+            st[nslot[k]] = sid[k];
+            a.stage16[(size_t)tile * SM + nslot[k]] = (unsigned short)(sid[k] - lo);
+        }
     }
-    for (int k = S + t; k < max((S + 255) & ~255, STAGE_MIN); k += 256) {
-        st[k] = S > 0 ? lo : first;
-        a.stage16[(size_t)tile * SM + k] = 0;
+    if (w == 0) {
+        for (int k = S + t; k < max((S + 255) & ~255, STAGE_MIN); k += 256) {
+            st[k] = S > 0 ? lo : first;
+            a.stage16[(size_t)tile * SM + k] = 0;
+        }
     }
     // the rows are handed to the waves longest first, so that the rows of a
     // wave have about the same length (ties in index order)
@@ -1394,108 +1396,122 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
         int r = 0;
         for (int v = 0; v < tcnt; ++v)
             r += (slen[v] > L || (slen[v] == L && v < u)) ? 1 : 0;
-        a.skin_ord[(size_t)tile * TILE + r] = (unsigned short)(u + 1);
+        if (w == 0)
+            a.skin_ord[(size_t)tile * TILE + r] = (unsigned short)(u + 1);
         sord[r] = (short)u;
         const int2 rw = a.trow[first + u];
         atomicMax(&id_lo, rw.y & 4095);
         atomicMax(&id_hi, rw.y >> 12);
     }
     // slots of each class (id modulo NL), as masks
-    const int nw = (S + 31) >> 5;
+    const int nw = (S + 31) >> 5, ms = nw | 1;  // mask words of a row, their stride (odd: neighbours in other banks)
+    unsigned *cmask = region, *mask = region + NL * nw;
     for (int x = t; x < nw * NL; x += 256) {
-        const int w = x / NL, c = x % NL;
+        const int v = x / NL, c = x % NL;
         unsigned m = 0u;
         for (int b = 0; b < 32; ++b)
-            m |= (32 * w + b < S && cls[32 * w + b] == c) ? 1u << b : 0u;
-        cmask[c * MW + w] = m;
+            m |= (32 * v + b < S && cls[32 * v + b] == c) ? 1u << b : 0u;
+        cmask[c * nw + v] = m;
     }
-    __syncthreads();
     const int chunks = lane_chunks(a.cap, NL);
+    const int cap_lane = 8 * (chunks / 2);  // entries of a lane that its chunks hold
     const int g = t / NL, q = t % NL;
-    for (int w = 0; w < W; ++w) {
-        const int wg = tile * W + w;
-        for (int g0 = 0; g0 < RW; g0 += G) {
-            // each row's partners as a mask over the slots, eight lanes a row
-            for (int x = t; x < G * MWP; x += 256)
-                mask[x] = 0u;
-            __syncthreads();
-            const int hr = (g0 + t / NLG) * W + w;  // rank of the row this lane reads
-            if (t / NLG < G && hr < tcnt) {
-                const int rho = sord[hr];
-                const int len = slen[rho];
-                const uint4 *rp = reinterpret_cast<const uint4 *>(a.rows + (size_t)(first + rho) * a.cap);
-                for (int pc = t % NLG; 8 * pc < len; pc += NLG) {
-                    const uint4 v = rp[pc];
-                    const unsigned ws[4] = {v.x, v.y, v.z, v.w};
+    // rows of this workgroup held as masks at a time (all of them, unless the
+    // tile stages nearly as many slots as it may)
+    const int G = min(RW, (WORDS - NL * nw) / ms);
+    for (int g0 = 0; g0 < RW; g0 += G) {
+        // each row's partners as a mask over the slots, several lanes a row
+        constexpr int NLG = 256 / RW < 4 ? 4 : 256 / RW;
+        __syncthreads();  // the ranks, then the last pass's masks, are read
+        for (int x = t; x < G * ms; x += 256)
+            mask[x] = 0u;
+        __syncthreads();
+        for (int hg = t / NLG; hg < G; hg += 256 / NLG) {
+            const int hr = (g0 + hg) * W + w;  // rank of the row this lane reads
+            if (g0 + hg >= RW || hr >= tcnt)
+                break;
+            const int rho = sord[hr];
+            const int len = slen[rho];
+            const uint4 *rp = reinterpret_cast<const uint4 *>(a.rows + (size_t)(first + rho) * a.cap);
+            unsigned *mk = mask + hg * ms;
+            for (int pc = t % NLG; 8 * pc < len; pc += NLG) {
+                const uint4 v = rp[pc];
+                const unsigned ws[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        if (pc * 8 + u < len) {
-                            const int ns = nslot[(ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu];
-                            atomicOr(&mask[(t / NLG) * MWP + (ns >> 5)], 1u << (ns & 31));
-                        }
+                for (int u = 0; u < 8; ++u) {
+                    if (pc * 8 + u < len) {
+                        const int ns = nslot[(ws[u >> 1] >> ((u & 1) * 16)) & 0xffffu];
+                        atomicOr(&mk[ns >> 5], 1u << (ns & 31));
                     }
                 }
             }
-            __syncthreads();
-            // each lane takes its partners, in ascending order
-            if (g >= g0 && g < g0 + G) {
-                const bool in = g * W + w < tcnt;
-                const unsigned *mk = mask + (g - g0) * MWP;
-                int mine = 0;
-                if (in)
-                    for (int x = 0; x < nw; ++x)
-                        mine += __popc(mk[x] & cmask[q * MW + x]);
-                int most = mine;
-#pragma unroll
-                for (int off = 1; off < NL; off <<= 1)
-                    most = max(most, __shfl_xor(most, off, NL));
-                const bool in_turn = most > 4 * chunks;
-                uint4 *dst = a.skin16 + (size_t)wg * (chunks / 2) * 256 + t;
-                unsigned acc[4] = {0u, 0u, 0u, 0u};
-                int c = 0, pos = 0;
-                auto put = [&](unsigned e) {
-                    const unsigned v = e << ((c & 1) * 16);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        acc[k] |= ((c >> 1) & 3) == k ? v : 0u;
-                    if ((++c & 7) == 0) {
-                        dst[(size_t)((c >> 3) - 1) * 256] = make_uint4(acc[0], acc[1], acc[2], acc[3]);
-                        acc[0] = acc[1] = acc[2] = acc[3] = 0u;
+        }
+        __syncthreads();
+        // each lane takes its partners, in ascending order
+        if (g >= g0 && g < g0 + G) {
+            const unsigned *mk = mask + (g - g0) * ms, *cm = cmask + q * nw;
+            const int words = g * W + w < tcnt ? nw : 0;
+            uint4 *dst = a.skin16 + (size_t)wg * (chunks / 2) * 256 + t;
+            unsigned a0 = 0u, a1 = 0u, a2 = 0u, a3 = 0u;  // the last eight entries, the newest on top
+            int c = 0;
+            auto put = [&](unsigned e) {
+                a0 = __builtin_amdgcn_alignbit(a1, a0, 16);
+                a1 = __builtin_amdgcn_alignbit(a2, a1, 16);
+                a2 = __builtin_amdgcn_alignbit(a3, a2, 16);
+                a3 = __builtin_amdgcn_alignbit(e, a3, 16);
+                if ((++c & 7) == 0 && c <= cap_lane)
+                    dst[(size_t)((c >> 3) - 1) * 256] = make_uint4(a0, a1, a2, a3);
+            };
+            // one partner, and a step to the next word when one is used up,
+            // each time round: lanes wait for the longest row, not for the
+            // fullest of every 64 words
+            {
+                unsigned b = words > 0 ? mk[0] & cm[0] : 0u, next = words > 1 ? mk[1] & cm[1] : 0u;
+                for (int x = 0; x < words;) {
+                    if (b) {
+                        put(4u * (unsigned)(32 * x + __ffs(b) - 1));
+                        b &= b - 1u;
                     }
-                };
-                if (in)
-                    for (int x = 0; x < nw; ++x) {
-                        unsigned b = in_turn ? mk[x] : mk[x] & cmask[q * MW + x];
-                        while (b) {
-                            const int kb = __ffs(b) - 1;
-                            b &= b - 1u;
-                            if (!in_turn || pos % NL == q)
-                                put(4u * (unsigned)(32 * x + kb));
-                            ++pos;
-                        }
+                    if (!b) {
+                        ++x;
+                        b = next;
+                        next = x + 1 < words ? mk[x + 1] & cm[x + 1] : 0u;
                     }
-                a.skin_len[wg * 256 + t] = (unsigned short)c;
-                while (c & 7)
-                    put(4u * (unsigned)R::SW);  // the far-away slot
+                }
             }
-            __syncthreads();  // the masks are reused by the next pass
+            int most = c;
+#pragma unroll
+            for (int off = 1; off < NL; off <<= 1)
+                most = max(most, __shfl_xor(most, off, NL));
+            if (most > cap_lane) {
+                // more of one class than a lane holds: the row is dealt in turn
+                c = 0;
+                int pos = 0;
+                for (int x = 0; x < words; ++x)
+                    for (unsigned b = mk[x]; b; b &= b - 1u, ++pos)
+                        if (pos % NL == q)
+                            put(4u * (unsigned)(32 * x + __ffs(b) - 1));
+            }
+            a.skin_len[wg * 256 + t] = (unsigned short)c;
+            while (c & 7)
+                put(4u * (unsigned)R::SW);  // the far-away slot
         }
-        // bonded and native entries: bonded rounds, then native ones
-        const int kb = (id_lo + NL - 1) / NL, kn = (id_hi + NL - 1) / NL;
-        const int r = g * W + w;
-        const int rho = r < tcnt ? sord[r] : 0;
-        const int2 rw = r < tcnt ? a.trow[first + rho] : make_int2(0, 0);
-        const int nb = rw.y & 4095, ntop = nb + (rw.y >> 12);
-        if (t == 0)
-            a.tile_top[tile] = make_int4(kb, kn, S > 0 ? lo : first, S > 0 && span > 65536 ? 0 : 1);
-        for (int k = 0; k < max(kb + kn, TOP_MIN); ++k) {
-            const int e = k < kb ? q + k * NL : nb + q + (k - kb) * NL;
-            const bool has = e < (k < kb ? nb : ntop);
-            const float2 en = has ? a.tent[rw.x + e] : make_float2(__int_as_float(first + rho), 0.f);
-            // bonded: r0; native: r0^2
-            a.ltop[top_index(wg, k, t, a.top_rounds)] =
-                make_uint2((unsigned)__float_as_int(en.x), __float_as_uint(k < kb ? en.y : en.y * en.y));
-        }
+    }
+    // bonded and native entries: bonded rounds, then native ones
+    const int kb = (id_lo + NL - 1) / NL, kn = (id_hi + NL - 1) / NL;
+    const int r = g * W + w;
+    const int rho = r < tcnt ? sord[r] : 0;
+    const int2 rw = r < tcnt ? a.trow[first + rho] : make_int2(0, 0);
+    const int nb = rw.y & 4095, ntop = nb + (rw.y >> 12);
+    if (w == 0 && t == 0)
+        a.tile_top[tile] = make_int4(kb, kn, S > 0 ? lo : first, S > 0 && span > 65536 ? 0 : 1);
+    for (int k = 0; k < max(kb + kn, TOP_MIN); ++k) {
+        const int e = k < kb ? q + k * NL : nb + q + (k - kb) * NL;
+        const bool has = e < (k < kb ? nb : ntop);
+        const float2 en = has ? a.tent[rw.x + e] : make_float2(__int_as_float(first + rho), 0.f);
+        // bonded: r0; native: r0^2
+        a.ltop[top_index(wg, k, t, a.top_rounds)] =
+            make_uint2((unsigned)__float_as_int(en.x), __float_as_uint(k < kb ? en.y : en.y * en.y));
     }
 }
 
@@ -2919,6 +2935,7 @@ void canon_tile(const DevBufs &b, int cap, hipStream_t s)
     CanonArgs a{};
     a.tile_first = b.tile_first[tile_index(TILE)];
     a.trow = b.trow;
+    a.stage_raw = b.stage_raw;
     a.stage = b.stage;
     a.stage_cnt = b.stage_cnt;
     a.rows = b.flist16;
@@ -2933,7 +2950,7 @@ void canon_tile(const DevBufs &b, int cap, hipStream_t s)
     a.stage16 = b.stage16;
     a.cap = cap;
     a.top_rounds = top_rounds(b.max_bonds, b.max_natives, NL);
-    hipLaunchKernelGGL((k_canon<TILE, NL>), dim3(b.n_tiles[tile_index(TILE)]), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_canon<TILE, NL>), dim3(b.n_tiles[tile_index(TILE)] * Rows<TILE, NL>::W), dim3(256), 0, s, a);
 }
 
 FilterArgs filter_args(const DevBufs &b, int cur, int cap, int tile, int n_cells, const FixDev &fix, float rc2)
@@ -3006,7 +3023,7 @@ void rebuild_tile(const DevBufs &b, int cur, int n, int cap, const GridDev &g, f
     a.tent = b.tent;
     a.list_cnt = b.list_cnt;
     a.list16 = b.flist16;
-    a.stage = b.stage;
+    a.stage = b.stage_raw;
     a.stage_cnt = b.stage_cnt;
     a.err = b.err;
     a.skin_flag = b.skin_flag;
