@@ -80,6 +80,8 @@ struct sop_ctx {
     // graphs over whole list periods, keyed by [layer parity][energy at first step]
     hipStream_t cap_stream = nullptr;
     hipGraphExec_t graphs[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+    hipGraphExec_t long_graphs[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // several of them in one
+    int graph_runs = 0;  // replays of `graphs`, up to LONG_AFTER
 };
 
 namespace {
@@ -250,12 +252,14 @@ int default_tile(long long) { return 64; }
 
 void destroy_graphs(sop_ctx *c)
 {
-    for (auto &row : c->graphs)
-        for (auto &g : row)
-            if (g) {
-                (void)hipGraphExecDestroy(g);
-                g = nullptr;
-            }
+    for (auto *set : {&c->graphs, &c->long_graphs})
+        for (auto &row : *set)
+            for (auto &g : row)
+                if (g) {
+                    (void)hipGraphExecDestroy(g);
+                    g = nullptr;
+                }
+    c->graph_runs = 0;
     for (auto &gp : c->bgraphs)
         for (auto &g : gp)
             if (g) {
@@ -610,9 +614,25 @@ sop_status capture_batch_graph(sop_ctx *c, int par, int records)
     return SOP_OK;
 }
 
+// Plain schedule: from one graph launch to the next the GPU idles about 8 us
+// (within a graph not at all), so a context that has replayed its graphs of
+// graph_steps list periods LONG_AFTER times makes one of LONG_PERIODS and
+// replays that wherever a call has the steps for it: 56 residues 5.85 -> 5.14
+// us a step, 4,801 at protein density 11.15 -> 10.17, 75,000 17.4 -> 16.75;
+// 25 periods give no more.  Making it (about 120 nodes) costs a context once
+// what the first 50 replays of it save, so a context that only runs a few
+// hundred steps does not.
+constexpr int LONG_PERIODS = 10, LONG_AFTER = 64;
+
+// Graphs of graph_steps list periods in one long graph.
+int long_factor(const sop_ctx *c)
+{
+    return c->graph_steps > 0 ? (LONG_PERIODS + c->graph_steps - 1) / c->graph_steps : 1;
+}
+
 // Capture `periods` list periods (rebuild + list_every steps each) starting at
 // layer parity `par`; energies are recorded at the first step when `energy`.
-sop_status capture_graph(sop_ctx *c, int par, int energy)
+sop_status capture_graph(sop_ctx *c, int par, int energy, int periods, hipGraphExec_t *out)
 {
     if (!c->cap_stream)
         HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
@@ -622,7 +642,7 @@ sop_status capture_graph(sop_ctx *c, int par, int energy)
     HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed));
     const bool half_saved = c->ud_half;
     c->ud_half = false;  // graphs start only after the first (half-kick) step
-    for (int q = 0; q < c->graph_steps; ++q) {
+    for (int q = 0; q < periods; ++q) {
         const bool fuse = fuses_filter(c, c->p.list_every == 1);
         rebuild(c, c->cap_stream, true, true, !fuse);
         for (int k = 0; k < c->p.list_every; ++k) {
@@ -641,7 +661,7 @@ sop_status capture_graph(sop_ctx *c, int par, int energy)
     (void)hipGraphDestroy(g);
     if (e != hipSuccess)
         return hip_fail(c, e, "hipGraphInstantiate");
-    c->graphs[par][energy] = ex;
+    *out = ex;
     return SOP_OK;
 }
 
@@ -1621,11 +1641,18 @@ sop_status sop_step(sop_ctx *c, int64_t n_steps)
         if (graphs_ok && c->step % align == 0 && n_steps - q >= span &&
             !(c->integrator == SOP_INTEGRATOR_UNDERDAMPED && c->ud_half)) {
             const int en = (E > 0 && c->step % E == 0) ? 1 : 0;
-            if (!c->graphs[c->cur][en]) {
-                st = capture_graph(c, c->cur, en);
+            const int m = long_factor(c);
+            const bool lng = m > 1 && c->graph_runs >= LONG_AFTER && n_steps - q >= m * span &&
+                             (E == 0 || E - c->step % E >= m * span);
+            const long long run = lng ? m * span : span;
+            hipGraphExec_t &ex = (lng ? c->long_graphs : c->graphs)[c->cur][en];
+            if (!ex) {
+                st = capture_graph(c, c->cur, en, (lng ? m : 1) * c->graph_steps, &ex);
                 if (st != SOP_OK)
                     return st;
             }
+            if (c->graph_runs < LONG_AFTER)
+                ++c->graph_runs;
             if (!base_set) {
                 launch_set_step(c->b.step_next, c->step, c->stream);
                 base_set = true;
@@ -1636,15 +1663,15 @@ sop_status sop_step(sop_ctx *c, int64_t n_steps)
                 launch_bin_all(c->b, c->cur, (int)c->n_res, c->grid, fix_consts(c), c->stream);
             if (c->skin_checked != c->step)
                 launch_force_skin(c->b, c->stream);
-            HIP_TRY(c, hipGraphLaunch(c->graphs[c->cur][en], c->stream));
+            HIP_TRY(c, hipGraphLaunch(ex, c->stream));
             if (en)
                 c->energy_step = c->step;
             c->list_valid = true;
-            c->step += span;
+            c->step += run;
             c->skin_checked = c->binned_at = c->step;
-            if (span & 1)
+            if (run & 1)
                 c->cur ^= 1;
-            q += span;
+            q += run;
             continue;
         }
         const bool en = E > 0 && c->step % E == 0;

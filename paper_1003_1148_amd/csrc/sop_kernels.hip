@@ -1697,10 +1697,12 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
 #pragma unroll
     for (int k = 0; k < TPRE; ++k)
         pq[k] = copy_of(te[k].x & ~FAR_ENTRY);
-    // the list chunks last: nothing needs them before the barrier
+    // the list chunks last: nothing needs them before the barrier (past the
+    // wave's chunks the first again, from L1: 20,000 residues 10.15 -> 9.9 us
+    // a step)
 #pragma unroll
     for (int k = 0; k < NPRE; ++k)
-        lw[k] = lp[k * 256];
+        lw[k] = lp[(k < nk ? k : 0) * 256];
     __builtin_amdgcn_sched_barrier(0);
     if (fast) {
         auto put = [&](int sl, const int4 &w) {
