@@ -447,18 +447,18 @@ __device__ __forceinline__ void underdamped_update(float4 &hi, float4 &lo, float
     v = make_float4(nv[0], nv[1], nv[2], 0.0f);
 }
 
-// Noise (Section III.C) and the first-order update (Eq. 2 / Algorithm 7)
-// with compensated positions.
-__device__ __forceinline__ void langevin_update(float4 &hi, float4 &lo, const Acc &A, long long step,
-                                                unsigned stream, const StepConsts &c, unsigned *err)
+// The Gaussians (Section III.C) of one residue's step; none if it is fixed.
+__device__ __forceinline__ void draw_noise(float (&g)[3], const float4 &hi, long long step, unsigned stream,
+                                           const StepConsts &c)
 {
     const unsigned tag = __float_as_uint(hi.w);
     if (tag >> 31)
-        return;  // fixed residue
+        return;
     const uint4 w = noise_words(tag, stream, step, c);
     const float2 gxy = gaussian_pair(w);
-    const float g[3] = {gxy.x, gxy.y, gaussian_axis(w, 2)};
-    update_with_noise(hi, lo, A, g, c, err);
+    g[0] = gxy.x;
+    g[1] = gxy.y;
+    g[2] = gaussian_axis(w, 2);
 }
 
 // ---------------------------------------------------------------------------
@@ -2356,24 +2356,30 @@ __device__ __forceinline__ void traj_sums(double *red, int t, double (&v)[3], in
         v[k] = red[k * WGS + t];
 }
 
-// Batched schedule: the list partners of a residue are summed by one lane,
-// pair by pair in row order, so the sum does not depend on the lane or on
-// the packing. Which lane sums which row is chosen at each list rebuild by a
+// Batched schedule: the list partners of a residue are summed in two partial
+// sums (the first and the second fours of its row's eights, each in row order)
+// by one lane or two, so the sum does not depend on the lanes or on the
+// packing.  Which lane sums which row is chosen at each list rebuild by a
 // counting sort on the row length (longest first), so the lanes of a wave
 // run loops of about the same length; which lane sums which bonded and native
 // entries, once a launch by their number.
 // Bound by vector instructions when the chip is full (their issue filled
-// 99.8% of the cycles before the following): integer differences of
-// fixed-point positions in place of float ones with packed low parts, rows
-// without padding, sorted native entries, and list entries shifted through
-// one word as they are found.  4,096 chains of 50-500 residues 75.6 -> 62.4 us
-// a step, 200 chains (111 packs: latency of one pack) 14.9 -> 11.5, 384 chains
-// of the exchange ladder 15.4 -> 12.3.
+// 99.8% of the cycles before the following), by the list rebuild (a third of
+// a step's time, every tenth step) and the wave with the longest rows when it
+// is not: integer differences of fixed-point positions in place of float ones
+// with packed low parts, rows without padding, sorted native entries, list
+// entries shifted through one word as they are found: 4,096 chains of 50-500
+// residues 75.6 -> 62.4 us a step, 200 chains (111 packs) 14.9 -> 11.5, 384
+// chains of the exchange ladder 15.4 -> 12.3.  Two partial sums, slots of
+// equal row length in slot order, and the fewest entries in the wave with the
+// longest rows: 54.5, 10.3 and 10.5; two lanes a residue (batch_split): 9.7.
 constexpr int NBUCKET = 64;
 
-template <int WGS, int MODE>
-__global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
+template <int WGS, int MODE, int SPLIT>
+__global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
 {
+    static_assert(SPLIT == 1 || (SPLIT == 2 && MODE == 0), "records are taken by one lane a residue");
+    constexpr int TH = WGS * SPLIT;
     constexpr int TCAP = 8 * WGS;  // bonded/native entries of a pack kept in LDS
     // per residue: its fixed-point position and periods; its high part while
     // the list is rebuilt
@@ -2385,16 +2391,22 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
     __shared__ int perm[WGS];           // row summed by each lane: residue | chunks << 16
     // list force, then bonded and native force of each residue; the
     // trajectory sums of a record step
-    __shared__ __align__(8) float fsum[6][WGS];
-    float (*lsum)[WGS] = fsum, (*tsum)[WGS] = fsum + 3;
+    __shared__ __align__(8) float fsum[3 * (SPLIT + 1)][WGS];
+    float (*tsum)[WGS] = fsum, (*lsum)[WGS] = fsum + 3;  // lsum: SPLIT triples
+    __shared__ unsigned words[SPLIT == 1 ? 1 : WGS / 32][SPLIT == 1 ? 1 : WGS];  // rebuild: the rows as masks
     __shared__ double esum[2][MODE == 0 ? 1 : WGS];  // record steps: list energy and virial of each residue
-    __shared__ int hist[NBUCKET];
+    __shared__ int hist[WGS / 64][NBUCKET];
     __shared__ int sres[WGS];           // residue of each local slot
     __shared__ float3 bblo[WGS / 32], bbhi[WGS / 32];  // list rebuild: boxes of 32-slot blocks
     const int p = blockIdx.x;
     const int off = a.pack_off[p];
     const int n = a.pack_off[p + 1] - off;
-    const int t = threadIdx.x;
+    // slot of this lane; SPLIT 2: lanes in the upper half of the workgroup
+    // serve the same slots as those in the lower
+    const int t = SPLIT == 1 ? (int)threadIdx.x : (int)(threadIdx.x % WGS);
+    const int half = SPLIT == 1 ? 0 : (int)(threadIdx.x / WGS);  // uniform over a wave
+    const bool own = half == 0;          // writes the slot's state
+    const bool topo = half == SPLIT - 1; // sums bonded and native entries
     const bool act = t < n;
     const int i = act ? a.slot_res[off + t] : 0;  // this lane's residue
     // local slot of a residue of the same trajectory: residue + shift
@@ -2413,15 +2425,19 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
         cnt = a.list_cnt[i];
     }
     int4 qi = fix_pos(hi, lo, a.fix);
-    sq[t] = qi;
-    sres[t] = i;
+    if (own) {
+        sq[t] = qi;
+        sres[t] = i;
+    }
     const int nb = row.y & 4095, ntop = nb + (row.y >> 12);
     // the pack's bonded/native entries in LDS (entries past TCAP stay in
-    // global memory); perm is the scan's workspace until the first assignment
+    // global memory)
     int tot_top = 0;
-    const int toff = block_exclusive_scan<WGS>(ntop, perm, tot_top);
+    int *scan = reinterpret_cast<int *>(fsum[0]);
+    block_exclusive_scan<TH>(own ? ntop : 0, scan, tot_top);
+    const int toff = scan[t] - ntop;
     const bool top_lds = toff + ntop <= TCAP;  // all of this residue's entries are in LDS
-    for (int e = 0; e < ntop && toff + e < TCAP; ++e) {
+    for (int e = 0; own && e < ntop && toff + e < TCAP; ++e) {
         const float2 te = a.tent[row.x + e];
         const unsigned short j = (unsigned short)(__float_as_int(te.x) + shift);
         tpart[toff + e] = (unsigned short)(j << 4);
@@ -2450,17 +2466,30 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
     const unsigned stream = act ? a.stream_ids[traj] : 0u;
 
     // Counting sort of the pack's slots by `key` (0 <= key < NBUCKET), largest
-    // first, ties in any order (no sum depends on which lane takes it): the
-    // packed value of the slot this lane takes.
-    auto sorted = [&](int key, int value) -> int {
-        if (t < NBUCKET)
-            hist[t] = 0;
+    // first, equal ones in slot order: neighbours have much the same partners,
+    // so their lanes read LDS with fewer bank conflicts (11.3 for 13.0 cycles a
+    // 16-byte read, counted over the rows of the 200 chains).  The packed value of
+    // the `k`-th slot goes to perm[k].
+    auto sort_slots = [&](int key, int value) {
+        const int wv = t >> 6, lane = t & 63;
+        unsigned long long same = __ballot(act);
+#pragma unroll
+        for (int b = 1; b < NBUCKET; b <<= 1) {
+            const unsigned long long set = __ballot((key & b) != 0);
+            same &= (key & b) ? set : ~set;
+        }
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
+        if (own)
+            hist[wv][lane] = 0;
         __syncthreads();
-        if (act)
-            atomicAdd(&hist[NBUCKET - 1 - key], 1);
+        if (own && act && rank == 0)
+            hist[wv][NBUCKET - 1 - key] = __popcll(same);
         __syncthreads();
-        if (t < 64) {  // one wave scans the buckets
-            const int v = t < NBUCKET ? hist[t] : 0;
+        if (own && t < 64) {  // one wave: a bucket a lane
+            int v = 0;
+#pragma unroll
+            for (int w = 0; w < WGS / 64; ++w)
+                v += hist[w][t];
             int x = v;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -2468,33 +2497,43 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                 if (t >= o)
                     x += y;
             }
-            if (t < NBUCKET)
-                hist[t] = x - v;
+            x -= v;
+#pragma unroll
+            for (int w = 0; w < WGS / 64; ++w) {
+                const int c = hist[w][t];
+                hist[w][t] = x;
+                x += c;
+            }
         }
         __syncthreads();
-        if (act)
-            perm[atomicAdd(&hist[NBUCKET - 1 - key], 1)] = value;
+        if (own && act)
+            perm[hist[wv][NBUCKET - 1 - key] + rank] = value;
         __syncthreads();
-        return t < n ? perm[t] : 0;
     };
+    static_assert(NBUCKET == 64, "a bucket a lane");
 
     // lane -> row assignment: by length in chunks, anew at each list rebuild
     int my = 0;   // local slot | partners << 16 of the row this lane sums
     int myg = 0;  // its residue
     auto assign = [&]() {
         const int c = act ? min(cnt, a.cap) : 0;
-        my = sorted(min((c + 3) >> 2, NBUCKET - 1), t | (c << 16));
+        sort_slots(min((c + 3) >> 2, NBUCKET - 1), t | (c << 16));
+        my = t < n ? perm[t] : 0;
         myg = sres[my & 0xffff];
     };
 
     // lane -> bonded and native entries: by number, once a launch (the longest
-    // of 64 residues in slot order has about 8 natives where the mean is 3)
+    // of 64 residues in slot order has about 8 natives where the mean is 3),
+    // fewest first: the wave with the longest rows has the fewest entries
     __syncthreads();
-    const int tr = sorted(min(ntop, NBUCKET - 1), t);  // the slot whose entries this lane sums
+    sort_slots(min(ntop, NBUCKET - 1), t);
+    const int tr = t < n ? perm[n - 1 - t] : 0;  // the slot whose entries this lane sums
     int *tq = reinterpret_cast<int *>(tsum[0]);
-    tq[t] = toff;
-    tq[WGS + t] = nb | (ntop << 12);
-    tq[2 * WGS + t] = row.x;
+    if (own) {
+        tq[t] = toff;
+        tq[WGS + t] = nb | (ntop << 12);
+        tq[2 * WGS + t] = row.x;
+    }
     __syncthreads();
     const int tr_off = tq[tr], tr_x = tq[2 * WGS + tr];
     const int tr_nb = t < n ? tq[WGS + tr] & 4095 : 0, tr_ntop = t < n ? tq[WGS + tr] >> 12 : 0;
@@ -2518,6 +2557,8 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
     bool far = false;
     auto check_reach = [&]() {
         far = false;
+        if (!topo)
+            return;
         const float lim = a.fix.reach * (float)a.fix.scale;
         const int4 p = sq[tr];
         for (int e = 0; e < tr_ntop; ++e) {
@@ -2539,7 +2580,8 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
         if ((q == 0 && a.stale) || step % a.list_every == 0) {
             check_reach();
             __syncthreads();
-            shh[t] = hi;  // the high parts, until the rows are written
+            if (own)
+                shh[t] = hi;  // the high parts, until the rows are written
             {
                 // boxes of the 32-slot blocks (empty slots add nothing)
                 float3 bl = act ? make_float3(hi.x, hi.y, hi.z) : make_float3(3.0e38f, 3.0e38f, 3.0e38f);
@@ -2553,92 +2595,137 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                     bh.y = fmaxf(bh.y, __shfl_xor(bh.y, o, 64));
                     bh.z = fmaxf(bh.z, __shfl_xor(bh.z, o, 64));
                 }
-                if ((t & 31) == 0) {
+                if (own && (t & 31) == 0) {
                     bblo[t >> 5] = bl;
                     bbhi[t >> 5] = bh;
                 }
                 __syncthreads();
             }
-            if (act) {
-                // Algorithm 3 over the trajectory: r < r_list, not bonded or
-                // native. Candidates are tested a 32-slot block at a time into
-                // a bit word (blocks whose box is out of reach of every lane of
-                // the wave are skipped); the row is written four entries (one
-                // 8-byte chunk) at a time.
-                unsigned w_lo = 0u, w_hi = 0u;
-                int ep = 0;  // next entry of the ascending exclusion list
-                cnt = 0;
-                for (int jb = tlo >> 5; jb <= (thi - 1) >> 5; ++jb) {
-                    const int j0 = jb << 5;
-                    {
-                        // the box test errs on the side of testing: a skipped
-                        // block is farther than r_list by a margin far above
-                        // the rounding of either distance
-                        const float3 bl = bblo[jb], bh = bbhi[jb];
-                        const float gx = fmaxf(fmaxf(bl.x - hi.x, hi.x - bh.x), 0.0f);
-                        const float gy = fmaxf(fmaxf(bl.y - hi.y, hi.y - bh.y), 0.0f);
-                        const float gz = fmaxf(fmaxf(bl.z - hi.z, hi.z - bh.z), 0.0f);
-                        if (!__any(gx * gx + gy * gy + gz * gz <= a.rc2 * 1.001f))
-                            continue;
-                    }
-                    // candidate j0 + u at bit 31 - u; slots of other
-                    // trajectories are masked
-                    unsigned m = 0u;
+            if (SPLIT == 2 && !own)
+                hi = shh[t];  // where its slot's own lane has moved it
+            // Algorithm 3 over the trajectory: r < r_list, not bonded or
+            // native. Candidates are tested a 32-slot block at a time into a
+            // bit word (blocks whose box is out of reach of every lane of the
+            // wave are skipped); the row is written four entries (one 8-byte
+            // chunk) at a time.  SPLIT 2: the blocks are halved between a
+            // slot's lanes, and so are the entries to write.
+            int ep = 0;  // next entry of the ascending exclusion list
+            const int b0 = tlo >> 5, b1 = act ? ((thi - 1) >> 5) + 1 : b0;
+            const int bm = SPLIT == 1 ? b1 : (b0 + b1 + 1) >> 1;
+            const int jb0 = half ? bm : b0, jb1 = half ? b1 : bm;  // this lane's blocks
+            // partners of this slot among those of block jb, at bit 31 - u
+            auto block_mask = [&](int jb) -> unsigned {
+                const int j0 = jb << 5;
+                {
+                    // the box test errs on the side of testing: a skipped
+                    // block is farther than r_list by a margin far above
+                    // the rounding of either distance
+                    const float3 bl = bblo[jb], bh = bbhi[jb];
+                    const float gx = fmaxf(fmaxf(bl.x - hi.x, hi.x - bh.x), 0.0f);
+                    const float gy = fmaxf(fmaxf(bl.y - hi.y, hi.y - bh.y), 0.0f);
+                    const float gz = fmaxf(fmaxf(bl.z - hi.z, hi.z - bh.z), 0.0f);
+                    if (!__any(gx * gx + gy * gy + gz * gz <= a.rc2 * 1.001f))
+                        return 0u;
+                }
+                // candidate j0 + u at bit 31 - u; slots of other
+                // trajectories are masked
+                unsigned m = 0u;
 #pragma unroll 1
-                    for (int u0 = 0; u0 < 32; u0 += 8) {
-                        float4 c8[8];
+                for (int u0 = 0; u0 < 32; u0 += 8) {
+                    float4 c8[8];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u)
-                            c8[u] = shh[j0 + u0 + u];
+                    for (int u = 0; u < 8; ++u)
+                        c8[u] = shh[j0 + u0 + u];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u)
-                            m = m + m + (within_cutoff(hi, c8[u], a.rc2) ? 1u : 0u);
+                    for (int u = 0; u < 8; ++u)
+                        m = m + m + (within_cutoff(hi, c8[u], a.rc2) ? 1u : 0u);
+                }
+                m &= 0xffffffffu >> max(tlo - j0, 0);
+                if (thi - j0 < 32)
+                    m &= ~(0xffffffffu >> (thi - j0));
+                unsigned x = 0u;  // the residue itself and its bonded/native partners
+                auto drop = [&](int j) {
+                    const unsigned d = (unsigned)(j - j0);
+                    x |= d < 32u ? (0x80000000u >> d) : 0u;
+                };
+                drop(t);
+                if (top_lds) {
+                    for (; ep < ntop; ++ep) {  // entries below this block were passed by skipped blocks
+                        const int j = tex[toff + ep];
+                        if (j >= j0 + 32)
+                            break;
+                        drop(j);
                     }
-                    m &= 0xffffffffu >> max(tlo - j0, 0);
-                    if (thi - j0 < 32)
-                        m &= ~(0xffffffffu >> (thi - j0));
-                    unsigned x = 0u;  // the residue itself and its bonded/native partners
-                    auto drop = [&](int j) {
-                        const unsigned d = (unsigned)(j - j0);
-                        x |= d < 32u ? (0x80000000u >> d) : 0u;
-                    };
-                    drop(t);
-                    if (top_lds) {
-                        for (; ep < ntop; ++ep) {  // entries below this block were passed by skipped blocks
-                            const int j = tex[toff + ep];
-                            if (j >= j0 + 32)
-                                break;
-                            drop(j);
-                        }
-                    } else {
-                        for (int e = 0; e < ntop; ++e)
-                            drop(partner(e));
-                    }
-                    m &= ~x;
-                    // four entries pass through one 64-bit word, the newest on top
-                    while (m) {
-                        const int u = __builtin_clz(m);
-                        const unsigned v = (unsigned)(j0 + u) << 4;  // byte offset in sq (one workgroup holds 1,024)
-                        m &= 0x7fffffffu >> u;
-                        w_lo = __builtin_amdgcn_alignbit(w_hi, w_lo, 16);
-                        w_hi = __builtin_amdgcn_alignbit(v, w_hi, 16);
-                        ++cnt;
-                        if ((cnt & 3) == 0 && cnt <= a.cap)
-                            rowp[(cnt >> 2) - 1] = make_uint2(w_lo, w_hi);
+                } else {
+                    for (int e = 0; e < ntop; ++e)
+                        drop(partner(e));
+                }
+                return m & ~x;
+            };
+            // entries [start, ...) of the row; those of the first and the last
+            // chunk, if not whole, one by one
+            unsigned w_lo = 0u, w_hi = 0u;  // the last four, the newest on top
+            int pos = 0, start = 0;
+            auto some = [&](int k) {  // the newest k < 4
+                const unsigned long long w = (unsigned long long)w_hi << 32 | w_lo;
+                unsigned short *row16 = reinterpret_cast<unsigned short *>(rowp);
+                for (int e = 0; e < k; ++e)
+                    if (pos - k + e < a.cap)
+                        row16[pos - k + e] = (unsigned short)(w >> (16 * (4 - k + e)));
+            };
+            auto put = [&](int jb, unsigned &m) {  // the first partner of m
+                const int u = __builtin_clz(m);
+                const unsigned v = (unsigned)((jb << 5) + u) << 4;  // byte offset in sq (one workgroup holds 1,024)
+                m &= 0x7fffffffu >> u;
+                w_lo = __builtin_amdgcn_alignbit(w_hi, w_lo, 16);
+                w_hi = __builtin_amdgcn_alignbit(v, w_hi, 16);
+                ++pos;
+                if ((pos & 3) == 0) {
+                    if (SPLIT == 2 && pos - start < 4)
+                        some(pos - start);
+                    else if (pos <= a.cap)
+                        rowp[(pos >> 2) - 1] = make_uint2(w_lo, w_hi);
+                }
+            };
+            if (SPLIT == 1) {
+                for (int jb = jb0; jb < jb1; ++jb) {
+                    unsigned m = block_mask(jb);
+                    while (m)
+                        put(jb, m);
+                }
+                cnt = pos;
+            } else {
+                for (int jb = jb0; jb < jb1; ++jb)
+                    words[jb][t] = block_mask(jb);
+                __syncthreads();
+                int c0 = 0, c1 = 0;
+                for (int jb = b0; jb < b1; ++jb)
+                    (jb < bm ? c0 : c1) += __popc(words[jb][t]);
+                pos = start = half ? c0 : 0;
+                // a partner, and a step to the next word when one is used up,
+                // each time round: lanes wait for the longest row alone
+                unsigned m = jb0 < jb1 ? words[jb0][t] : 0u, next = jb0 + 1 < jb1 ? words[jb0 + 1][t] : 0u;
+                for (int jb = jb0; jb < jb1;) {
+                    if (m)
+                        put(jb, m);
+                    if (!m) {
+                        ++jb;
+                        m = next;
+                        next = jb + 1 < jb1 ? words[jb + 1][t] : 0u;
                     }
                 }
-                // the last chunk, if not whole
-                if ((cnt & 3) != 0 && cnt < a.cap) {
-                    const int sh = 16 * (4 - (cnt & 3));
-                    const unsigned long long w = ((unsigned long long)w_hi << 32 | w_lo) >> sh;
-                    rowp[cnt >> 2] = make_uint2((unsigned)w, (unsigned)(w >> 32));
-                }
+                cnt = c0 + c1;
+            }
+            if ((pos & 3) != 0)
+                some(min(pos & 3, pos - start));
+            if (act && own) {
                 if (cnt > a.cap)
                     atomicOr(a.err, ERR_OVERFLOW);
                 a.list_cnt[i] = cnt;
             }
             assign();  // its barriers also publish the rows written above
-            sq[t] = qi;
+            if (own)
+                sq[t] = qi;
             __syncthreads();
         }
         // mode 0 never records (no FP64 sums in its registers); mode 2
@@ -2652,13 +2739,17 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                 const int r = my & 0xffff;
                 const int n8 = my >> 19;
                 const int4 pr = sq[r];
-                // rows are read eight entries (16 bytes) at a time, the next
-                // ones requested before the current ones are used
+                // rows are read in eights, the next one requested before the
+                // current one is used; the first fours of the eights and the
+                // second fours are summed apart, each pair by pair in row
+                // order: by one lane (SPLIT 1), or by one each
                 const uint4 *rp = reinterpret_cast<const uint4 *>(a.list + (size_t)myg * a.cap);
-                Acc L;  // the row's sum, pair by pair in row order
+                const uint2 *rh = reinterpret_cast<const uint2 *>(rp) + half;
+                const int last = max((my >> 16) - 1, 0) >> 3, left = (my >> 16) & 7;
+                Acc L, M;
                 auto sweep = [&](auto list_far) {
                     // four partners, `m` of them the row's (all of them: a constant)
-                    auto chunk = [&](unsigned wx, unsigned wy, auto m) {
+                    auto chunk = [&](Acc &L, unsigned wx, unsigned wy, auto m) {
                         const unsigned off[4] = {wx & 0xffffu, wx >> 16, wy & 0xffffu, wy >> 16};
                         int4 pj[4];
 #pragma unroll
@@ -2679,32 +2770,47 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                             }
                         }
                     };
-                    const int last = max((my >> 16) - 1, 0) >> 3;
-                    uint4 w = rp[0];
-                    for (int c = 0; c < n8; ++c) {
-                        const uint4 wn = rp[min(c + 1, last)];
-                        chunk(w.x, w.y, std::integral_constant<int, 4>{});
-                        chunk(w.z, w.w, std::integral_constant<int, 4>{});
-                        w = wn;
+                    constexpr std::integral_constant<int, 4> all{};
+                    if (SPLIT == 1) {
+                        uint4 w = rp[0];
+                        for (int c = 0; c < n8; ++c) {
+                            const uint4 wn = rp[min(c + 1, last)];
+                            chunk(L, w.x, w.y, all);
+                            chunk(M, w.z, w.w, all);
+                            w = wn;
+                        }
+                        if (left > 0)
+                            chunk(L, w.x, w.y, left);
+                        if (left > 4)
+                            chunk(M, w.z, w.w, left - 4);
+                    } else {
+                        uint2 w = rh[0];
+                        for (int c = 0; c < n8; ++c) {
+                            const uint2 wn = rh[2 * min(c + 1, last)];
+                            chunk(L, w.x, w.y, all);
+                            w = wn;
+                        }
+                        if (left > 4 * half)
+                            chunk(L, w.x, w.y, left - 4 * half);
                     }
-                    const int left = (my >> 16) & 7;
-                    if (left > 0)
-                        chunk(w.x, w.y, left);
-                    if (left > 4)
-                        chunk(w.z, w.w, left - 4);
                 };
                 if (a.fix.list_far)
                     sweep(std::true_type{});
                 else
                     sweep(std::false_type{});
                 if (t < n) {
-                    const float ls = a.fix.list_far ? kc.c6 : kc.c6 * a.fix.unit;
-                    lsum[0][r] = ls * L.fx;
-                    lsum[1][r] = ls * L.fy;
-                    lsum[2][r] = ls * L.fz;
+                    if (SPLIT == 2) {
+                        lsum[3 * half][r] = L.fx;
+                        lsum[3 * half + 1][r] = L.fy;
+                        lsum[3 * half + 2][r] = L.fz;
+                    } else {
+                        lsum[0][r] = L.fx + M.fx;
+                        lsum[1][r] = L.fy + M.fy;
+                        lsum[2][r] = L.fz + M.fz;
+                    }
                     if (rec) {
-                        esum[0][r] = L.e_r;
-                        esum[1][r] = L.vir;
+                        esum[0][r] = L.e_r + M.e_r;
+                        esum[1][r] = L.vir + M.vir;
                     }
                 }
             }
@@ -2744,7 +2850,7 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                 };
                 if (rec) {
                     terms(qi, toff, row.x, shift, nb, ntop, std::true_type{});
-                } else {
+                } else if (topo) {
                     const int4 p = sq[tr];
                     if (__any(far || !tr_lds))
                         terms(p, tr_off, tr_x, tr_shift, tr_nb, tr_ntop, std::true_type{});
@@ -2755,24 +2861,33 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                         tsum[1][tr] = A.fy;
                         tsum[2][tr] = A.fz;
                     }
-                    __syncthreads();
-                    A.fx = tsum[0][t];
-                    A.fy = tsum[1][t];
-                    A.fz = tsum[2][t];
                 }
             }
             if (broken)
                 atomicOr(a.err, ERR_FENE);
-            if (act) {
+            // SPLIT 2: the slot's own lane draws its noise meanwhile
+            float gn[3] = {0.0f, 0.0f, 0.0f};
+            if (SPLIT == 2 && own && act)
+                draw_noise(gn, hi, step, stream, cn);
+            __syncthreads();
+            if (!rec) {
+                A.fx = tsum[0][t];
+                A.fy = tsum[1][t];
+                A.fz = tsum[2][t];
+            }
+            if (act && own) {
                 add_external(A, e_x, f_rep, hi, lo, step, a.c.h, a.has_pull ? a.pull_slot[i] : -1, a.pulls,
                              a.tip, rec, a.err);
-            }
-            if (rec)
-                __syncthreads();
-            if (act) {
-                A.fx += lsum[0][t];
-                A.fy += lsum[1][t];
-                A.fz += lsum[2][t];
+                const float ls = a.fix.list_far ? kc.c6 : kc.c6 * a.fix.unit;
+                float l[3] = {lsum[0][t], lsum[1][t], lsum[2][t]};
+                if (SPLIT == 2) {
+#pragma unroll
+                    for (int ax = 0; ax < 3; ++ax)
+                        l[ax] += lsum[3 + ax][t];
+                }
+                A.fx = __builtin_fmaf(ls, l[0], A.fx);
+                A.fy = __builtin_fmaf(ls, l[1], A.fy);
+                A.fz = __builtin_fmaf(ls, l[2], A.fz);
                 if (rec) {
                     A.e_r = esum[0][t];
                     A.vir += esum[1][t];
@@ -2797,12 +2912,14 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                 __syncthreads();
             }
             if (MODE == 1) {
-                if (act)
+                if (act && own)
                     a.fout[i] = make_float4(A.fx, A.fy, A.fz, 0.0f);
                 return;
             }
-            if (act) {
-                langevin_update(hi, lo, A, step, stream, cn, a.err);
+            if (act && own) {
+                if (SPLIT == 1)
+                    draw_noise(gn, hi, step, stream, cn);
+                update_with_noise(hi, lo, A, gn, cn, a.err);
                 qi = fix_pos(hi, lo, a.fix);
                 sq[t] = qi;
             }
@@ -2820,7 +2937,7 @@ __global__ __launch_bounds__(WGS, 4) void k_batch(BatchArgs a)
                 forces_and_update(std::false_type{});
         }
     }
-    if (MODE != 1 && act) {
+    if (MODE != 1 && act && own) {
         a.pout[2 * i] = hi;
         a.pout[2 * i + 1] = lo;
     }
@@ -3264,6 +3381,15 @@ void launch_step(const DevBufs &b, int cur, int n, int cap, int tile, const Step
     }
 }
 
+// Two lanes a residue for packs of 256 as long as all of them are resident at
+// once so (two a CU): such packs leave most of a CU's issue slots idle.  us a
+// step with one lane and two: 60 chains of 137 residues 7.7 and 6.7, 384 8.7
+// and 8.2, 510 8.8 and 8.2; 250 of 250 9.4 and 8.0, 510 10.9 and 10.2; 1,000
+// of 60 6.3 and 5.8.  With packs of 512 the sums fill the CU already and the
+// rebuild's masks cost more than they bring (200 chains of 50-500 10.3 and
+// 11.0).
+bool batch_split(int n_packs, int wg) { return wg == 256 && n_packs <= 512; }
+
 void launch_batch(const DevBufs &b, int cur, int n_packs, int wg, int cap, const StepConsts &c,
                   const FixDev &fix, const TipDev &tip, int has_pull, float rc2, int list_every, long long energy_every,
                   int n_steps, int stale, int mode, const long long *step_base, long long step_off,
@@ -3301,24 +3427,23 @@ void launch_batch(const DevBufs &b, int cur, int n_packs, int wg, int cap, const
     a.rc2 = rc2;
     a.tscale = tscale;
     const dim3 grid(n_packs);
-    if (mode == 1) {
-        switch (wg) {
-        case 256: hipLaunchKernelGGL((k_batch<256, 1>), grid, dim3(256), 0, s, a); break;
-        case 512: hipLaunchKernelGGL((k_batch<512, 1>), grid, dim3(512), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_batch<1024, 1>), grid, dim3(1024), 0, s, a); break;
-        }
-    } else if (mode == 2) {
-        switch (wg) {
-        case 256: hipLaunchKernelGGL((k_batch<256, 2>), grid, dim3(256), 0, s, a); break;
-        case 512: hipLaunchKernelGGL((k_batch<512, 2>), grid, dim3(512), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_batch<1024, 2>), grid, dim3(1024), 0, s, a); break;
-        }
-    } else {
-        switch (wg) {
-        case 256: hipLaunchKernelGGL((k_batch<256, 0>), grid, dim3(256), 0, s, a); break;
-        case 512: hipLaunchKernelGGL((k_batch<512, 0>), grid, dim3(512), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_batch<1024, 0>), grid, dim3(1024), 0, s, a); break;
-        }
+    auto run = [&](auto W) {
+        constexpr int WGS = decltype(W)::value;
+        if (mode == 1)
+            hipLaunchKernelGGL((k_batch<WGS, 1, 1>), grid, dim3(WGS), 0, s, a);
+        else if (mode == 2)
+            hipLaunchKernelGGL((k_batch<WGS, 2, 1>), grid, dim3(WGS), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_batch<WGS, 0, 1>), grid, dim3(WGS), 0, s, a);
+    };
+    if (mode == 0 && batch_split(n_packs, wg)) {
+        hipLaunchKernelGGL((k_batch<256, 0, 2>), grid, dim3(512), 0, s, a);
+        return;
+    }
+    switch (wg) {
+    case 256: run(std::integral_constant<int, 256>{}); break;
+    case 512: run(std::integral_constant<int, 512>{}); break;
+    default: run(std::integral_constant<int, 1024>{}); break;
     }
 }
 

@@ -100,3 +100,20 @@ def test_record_launches(P, every, wg):  # noqa: F811
         c.close()
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("packs", [512, 513])
+def test_one_and_two_lanes_a_residue(P, packs):  # noqa: F811
+    """Packs of 256 on both sides of the count up to which two lanes serve a
+    residue, against the first 12 chains alone (two lanes) on packs of 512
+    (one): bit for bit."""
+    w = saw_batch(np.full(12, 150), np.random.default_rng(13))
+    got = []
+    for n, wg in ((packs, 256), (12, 256), (12, 512)):
+        s = _system("lanes", [[w[t % 12]] for t in range(n)])
+        c = P.from_system(s, RunParams(), schedule="batched", batch=(wg, 25))
+        c.step(25)
+        got.append(c.get_coordinates()[:12 * 150])
+        c.close()
+    assert np.array_equal(got[0], got[1])
+    assert np.array_equal(got[0], got[2])
