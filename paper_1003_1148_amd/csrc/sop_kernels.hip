@@ -555,8 +555,8 @@ __device__ __forceinline__ unsigned wave_or(unsigned v)
     return v;
 }
 
-// One workgroup of 256 lanes per tile of TILE consecutive residues; lane t
-// serves residue t % TILE and part q = t / TILE of its work (NLB = 256/TILE
+// One workgroup of NT lanes per tile of TILE consecutive residues; lane t
+// serves residue t % TILE and part q = t / TILE of its work (NLB = NT / TILE
 // parts).
 //  1. The cells around the tile's residues (each residue's own and adjacent
 //     cells) go into an LDS hash table and are sorted by cell index; their
@@ -564,18 +564,18 @@ __device__ __forceinline__ unsigned wave_or(unsigned v)
 //  2. Per window of whole cells (at most cand_win candidates, usually one
 //     window): candidates go to LDS; each residue is tested against them 32
 //     at a time with the single-precision predicate r < r_list of
-//     Algorithm 3, one bit per candidate, part q taking a contiguous range
-//     of the 32-candidate words (words outside every neighbourhood of a wave
-//     are skipped).  Self, bonded and native partners are cleared; the
+//     Algorithm 3, one bit per candidate, part q taking every NLB-th of the
+//     32-candidate words (words outside every neighbourhood of a wave are
+//     skipped).  Self, bonded and native partners are cleared; the
 //     candidates some row uses get the next staging slots in sorted order;
 //     each part appends its words' partners to the row at the offset the
 //     lower parts leave.
-// A row lists its partners in (cell, residue index) order whatever the tile
-// size or the order in which residues were binned.
-template <int TILE, bool MULTI>
-__global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArgs a)
+// The order of a row's partners here depends on the number of parts; the
+// canonical order that follows does not.
+template <int TILE, bool MULTI, int NT>
+__global__ __launch_bounds__(NT, NT > 256 ? 4 : (TILE == 64 ? 5 : 2)) void k_tile_build(BuildArgs a)
 {
-    constexpr int NT = 256, NLB = NT / TILE;
+    constexpr int NLB = NT / TILE;
     constexpr int SM = stage_max<TILE>();
     constexpr int CM = cand_win<TILE>();
     constexpr int NW = CM / 32;
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
 
     // ---- 1. cells around the tile ----
     // independent loads first; this part's bonded/native entries (u = q mod
-    // NLB, the first TREG kept in registers) and their partners' cells are
+    // NLB, the first ones kept in registers) and their partners' cells are
     // needed only in step 2
     float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
     int own = 0;
@@ -648,8 +648,8 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         row = a.trow[i];
     }
     const int ntop = (row.y & 4095) + (row.y >> 12);
-    // entry e = v * NLB + q of the first TREG is this part's v-th
-    constexpr int TPP = TREG / NLB;
+    // entry e = v * NLB + q, e < TPP * NLB, is this part's v-th
+    constexpr int TPP = TREG > NLB ? TREG / NLB : 1;
     int tj[TPP], tm[TPP];
 #pragma unroll
     for (int v = 0; v < TPP; ++v) {
@@ -663,7 +663,16 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
     const int tlo = (MULTI && act) ? a.traj_lo[i] : 0, thi = (MULTI && act) ? a.traj_hi[i] : 0;
     // own wrapped cell coordinates
     const int ux = own % g.gx, uy = (own / g.gx) % g.gy, uz = own / (g.gx * g.gy);
-    if (act) {
+    // one lane of those in one cell enters its neighbours: the lanes of a wave
+    // share a dozen cells, and LDS serves atomics on one address one by one
+    bool enters = act;
+    for (unsigned long long todo = __ballot(act); todo;) {
+        const int l = __ffsll((long long)todo) - 1;
+        const bool same = act && own == __shfl(own, l);
+        enters &= !(same && (int)__lane_id() != l);
+        todo &= ~__ballot(same);
+    }
+    if (enters) {
         for (int d = q; d < 27; d += NLB) {
             const int cx = ux + d % 3 - 1, cy = uy + (d / 3) % 3 - 1, cz = uz + d / 9 - 1;
             const int cid = (cx < 0 ? cx + g.gx : (cx >= g.gx ? cx - g.gx : cx)) +
@@ -825,10 +834,9 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
             whi[w] = (short)segment_of(base + min(32 * w + 31, Mw - 1));
         }
         __syncthreads();
-        // row bits; part q takes words [w0, w1) (uniform over a wave)
-        const int wpp = (NWm + NLB - 1) / NLB;
-        const int w0 = min(NWm, q * wpp), w1 = min(NWm, w0 + wpp);
-        for (int w = w0; w < w1; ++w) {
+        // row bits; part q (uniform over a wave) takes every NLB-th word, as
+        // partners lie in few neighbouring ones
+        for (int w = q; w < NWm; w += NLB) {
             bool reach = false;
             if (act)
                 for (int m = wlo[w]; m <= whi[w]; ++m) {
@@ -889,7 +897,7 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         if (lead)
             drop(find(i, own_m));
         if (act)
-            for (int e = TREG + q; e < ntop; e += NLB) {
+            for (int e = TPP * NLB + q; e < ntop; e += NLB) {
                 const int j = __float_as_int(a.tent[row.x + e].x);
                 drop(find(j, lookup(a.cell_of[j])));
             }
@@ -915,7 +923,7 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
         }
         {
             int c = 0;
-            for (int w = w0; w < w1; ++w)
+            for (int w = q; w < NWm; w += NLB)
                 c += __popc(bits[w * TILE + rho]);
             pcnt[t] = (short)c;
         }
@@ -937,7 +945,7 @@ __global__ __launch_bounds__(256, TILE == 64 ? 5 : 2) void k_tile_build(BuildArg
             int k = rowbase[rho];
             for (int pq = 0; pq < q; ++pq)
                 k += pcnt[pq * TILE + rho];
-            for (int w = w0; w < w1; ++w) {
+            for (int w = q; w < NWm; w += NLB) {
                 unsigned b = bits[w * TILE + rho];
                 const unsigned uw = used[w];
                 const int wb = wbase[w];
@@ -3156,6 +3164,14 @@ int workgroups(const DevBufs &b, int tile)
     return n * (tile * lanes_for(tile, n) / 256);
 }
 
+// Lanes of a search workgroup by the number of 64-residue tiles.  A tile's
+// search is a chain of short phases that four waves alone on a CU take 44 us
+// for, so while every tile has a CU to itself 16 waves share it, and up to a
+// few tiles a CU eight.  Whole search (with the order of its rows), us with
+// 256, 512 and 1,024 lanes: 16 tiles 109, 86, 77; 76 tiles at protein density
+// 247, 179, 147; 320 tiles 105, 91, 104; 1,200 tiles 206, 208, 251.
+constexpr int SEARCH_1024 = 256, SEARCH_512 = 640;
+
 template <int TILE>
 void rebuild_tile(const DevBufs &b, int cur, int n, int cap, const GridDev &g, float rc2, int multi,
                   hipStream_t s, bool advance, int period)
@@ -3187,10 +3203,20 @@ void rebuild_tile(const DevBufs &b, int cur, int n, int cap, const GridDev &g, f
     a.n = n;
     a.cap = cap;
     const int nt = b.n_tiles[tile_index(TILE)];
-    if (multi)
-        hipLaunchKernelGGL((k_tile_build<TILE, true>), dim3(nt), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_tile_build<TILE, false>), dim3(nt), dim3(256), 0, s, a);
+    auto run = [&](auto NT) {
+        constexpr int N = decltype(NT)::value;
+        if (multi)
+            hipLaunchKernelGGL((k_tile_build<TILE, true, N>), dim3(nt), dim3(N), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_tile_build<TILE, false, N>), dim3(nt), dim3(N), 0, s, a);
+    };
+    if constexpr (TILE == 64) {
+        if (nt <= SEARCH_1024)
+            return run(std::integral_constant<int, 1024>{});
+        if (nt <= SEARCH_512)
+            return run(std::integral_constant<int, 512>{});
+    }
+    run(std::integral_constant<int, 256>{});
 }
 
 template <bool ENERGY, int MODE, bool FIRST = false>
