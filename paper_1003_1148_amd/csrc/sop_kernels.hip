@@ -1690,7 +1690,20 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
         const int first = a.f.tile_first[tile], tcnt = a.f.tile_first[tile + 1] - first;
         const bool in = r < tcnt;
         rho = in ? ranked(a.f.skin_ord, (size_t)tile * TILE + r, r) : 0;
-        filter_rows<TILE, NL>(a.f, wg, tile, t, first, tcnt, in, rho, region, ring, bb, wr);
+        // what the step has as well by the step's own arguments: one set of
+        // registers, none in scratch (250,000 residues 47.1 -> 46.4 us a step,
+        // 75,000 16.75 -> 16.55)
+        FilterArgs f = a.f;
+        f.pos = a.pin;
+        f.stage = a.stage;
+        f.ltop = const_cast<uint2 *>(a.ltop);
+        f.list16 = const_cast<uint2 *>(a.list16);
+        f.llen = const_cast<unsigned short *>(a.llen);
+        f.grho = const_cast<unsigned char *>(a.grho);
+        f.wg_rec = const_cast<WgRec *>(a.wg_rec);
+        f.fix = a.fix;
+        f.top_rounds = a.top_rounds;
+        filter_rows<TILE, NL>(f, wg, tile, t, first, tcnt, in, rho, region, ring, bb, wr);
     } else {
         rho = a.grho[wg * RW + g];
     }
