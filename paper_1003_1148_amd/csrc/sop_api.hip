@@ -362,7 +362,7 @@ StepConsts step_consts(const sop_ctx *c)
     return k;
 }
 
-// Scale of the fixed-point copies (plain schedule): the coarsest power of two
+// Scale of the fixed-point copies: the coarsest power of two
 // that keeps 2.5 times the distance a listed pair can have (r_list, and 16
 // standard deviations of the thermal drift of a list period, eight for each
 // partner) inside half the period of 2^32 units, so that a listed pair would

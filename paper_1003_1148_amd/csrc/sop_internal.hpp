@@ -60,8 +60,8 @@ struct GridDev {
 constexpr int CELL_CAP = 256;
 // Bonded plus native partners per residue (larger is rejected at load).
 constexpr int TOPO_CAP = 64;
-// Largest staging set of a tile of the plain schedule (slots are 16-bit;
-// the kernels hold 1,024 or 2,048 of them in LDS at once).
+// Largest staging set of a tile of the plain schedule (slots are 16-bit; the
+// kernels hold some 1,800 to 3,000 of them in LDS at once).
 constexpr int STAGE_MAX = 4096;
 
 // Fixed-point copies of the positions: whole numbers of units of 2^-k, modulo
@@ -69,7 +69,9 @@ constexpr int STAGE_MAX = 4096;
 // the caller's units: a bonded or native pair within it on every axis at a
 // rebuild is taken from the copies until the next one, others (and every
 // such pair when `bond_far`, every list pair when `list_far`) from the
-// compensated positions.
+// compensated positions; the batched schedule, which has the copies alone,
+// keeps the periods below them beside them and takes such pairs (and the list
+// when `list_far`) over both.
 struct FixDev {
     double scale, period, inv_period;  // 2^k, 2^(32-k), 2^(k-32)
     float unit, s2, reach, direct;     // 2^-k, 2^2k, 2^(30-k), 2^(50-k)
@@ -99,8 +101,8 @@ struct DevBufs {
     float2 *tent;     // {partner id bits, r0}: bonds first, then natives
     int *list_cnt;    // partners per residue (plain: of the skin rows)
     unsigned short *list16;  // plain: skin rows (pairs within r_list + skin at the last skin build),
-                             // lane order; batched: the list, rows by residue (cap entries) of local
-                             // slots of its pack
+                             // lane order; batched: the list, rows by residue (cap entries) of 16
+                             // times the local slot of its pack
     unsigned short *skin_len;  // plain: skin entries of each lane (workgroup * 256 + lane)
     unsigned short *flist16; // plain: the list rows (the skin rows filtered at r_list), lane order;
                              // during a skin search its rows by residue (cap entries)
