@@ -123,7 +123,7 @@ struct DevBufs {
     float *re_tscale;        // batched, replica exchange: sqrt(kB T / kB T of the parameters)
     unsigned long long *re_stats;  // batched, replica exchange: {accepted, attempted} per ladder pair
     float4 *facc;            // plain, pair-based forces: per-residue force accumulator
-    double4 *eacc;           // plain, pair-based forces: per-residue energy accumulator
+    double4 *eacc;           // plain, pair-based forces: per-residue energies of the pairs in its row
     int *stage;       // plain: per tile, global ids of its slots (stage_max per tile)
     int *stage_raw;   // the same in the search's order
     unsigned short *stage16;  // plain: the same less the tile's lowest id (tile_top), where all
