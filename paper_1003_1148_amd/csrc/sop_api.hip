@@ -372,6 +372,13 @@ StepConsts step_consts(const sop_ctx *c)
 // use the copies only while a unit is below 2^-24 of the shortest reference
 // length (the rounding of that length in single precision), the list only
 // while it is below 2e-6 sigma.
+// `narrow`: copies relative to a tile's origin wrap at half a period H, and a
+// list partner lies up to r_list further out than the tile's residues, plus
+// what it moves until the next rebuild, for which the drift or H / 16 is left.
+// At 300 K and the time step of the reference workloads: 40 A from r_list =
+// 10.6 A (H = 64 A) to 20 A, 37 A at 23 A, 20 A at 10 A (H = 32 A).
+constexpr double NARROW_MAX = 40.0;
+
 FixDev fix_consts(const sop_ctx *c)
 {
     const double drift = 16.0 * std::sqrt(2.0 * c->p.kBT * c->p.h / c->p.zeta * c->p.list_every);
@@ -390,6 +397,8 @@ FixDev fix_consts(const sop_ctx *c)
     f.s2 = (float)std::ldexp(1.0, 2 * k);
     f.reach = (float)std::ldexp(1.0, 30 - k);
     f.direct = (float)std::ldexp(1.0, 50 - k);
+    const double H = std::ldexp(1.0, 31 - k);
+    f.narrow = (float)std::min(NARROW_MAX, H - c->p.r_list - std::max(drift, H / 16));
     f.list_far = (half > std::ldexp(1.0, 31 - k) || f.unit > 2e-6 * c->p.sigma) ? 1 : 0;
     f.bond_far = f.unit > std::ldexp(c->min_r0, -24) ? 1 : 0;
     return f;

@@ -75,6 +75,7 @@ constexpr int STAGE_MAX = 4096;
 struct FixDev {
     double scale, period, inv_period;  // 2^k, 2^(32-k), 2^(k-32)
     float unit, s2, reach, direct;     // 2^-k, 2^2k, 2^(30-k), 2^(50-k)
+    float narrow;                      // plain: largest half-width of a tile taken around one origin
     int list_far, bond_far;
 };
 

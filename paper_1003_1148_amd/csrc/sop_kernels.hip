@@ -1027,16 +1027,16 @@ __device__ __forceinline__ int ranked(const unsigned short *ord, size_t at, int 
 }
 
 // What holds for a workgroup until the next rebuild: it has a FAR_ENTRY; the
-// tile's residues do not fit a cube of 2 NARROW_TILE.  Within NARROW_TILE of
-// the cube's centre (the origin) on every axis, list partners (within r_list
-// = 20 A at the rebuild) lie within about 64 A of it, so positions relative to
-// the origin rounded to single precision separate list pairs to about 8e-6 A
-// at most; other tiles subtract the copies themselves.  Origin and test
-// depend on the tile's own residues only, neither on which other residues
-// are staged nor on how the tile's are dealt to workgroups.
+// tile's residues do not fit a cube of 2 FixDev::narrow.  Within `narrow` of
+// the cube's centre (the origin) on every axis, neither the tile's residues
+// nor their list partners wrap (fix_consts), and positions relative to the
+// origin, all within half a period, are rounded once to single precision: list
+// pairs are separated to half a unit in the last place of it (at r_list = 20 A
+// 64 A: about 8e-6 A at most).  Other tiles subtract the copies themselves.
+// Origin and test depend on the tile's own residues only, neither on which
+// other residues are staged nor on how the tile's are dealt to workgroups.
 constexpr int WG_FAR = 1, WG_WIDE = 2;
 constexpr int WG_IDS32 = 4;  // the tile's slot ids do not fit stage16
-constexpr float NARROW_TILE = 40.0f;
 
 // Filters the skin entries of every lane of a workgroup; returns the number
 // of list entries of this lane, and the workgroup's record.  Every lane of a
@@ -1156,7 +1156,7 @@ __device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile
             o[ax] = 0.5f * lo + 0.5f * hi;
             half = fmaxf(half, hi - o[ax]);
         }
-        if (!(half < NARROW_TILE))
+        if (!(half < a.fix.narrow))
             flags |= WG_WIDE;
         if (!top.w)
             flags |= WG_IDS32;
