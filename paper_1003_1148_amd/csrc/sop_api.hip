@@ -196,13 +196,17 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
     d.skin_len = (unsigned short *)take(wg_elems * 256 * sizeof(unsigned short));
     d.llen = (unsigned short *)take(wg_elems * 256 * sizeof(unsigned short));
     d.grho = (unsigned char *)take(wg_elems * 256);
-    d.wg_rec = (WgRec *)take(wg_elems * sizeof(WgRec));
+    d.wg_rec = (WgRec *)take((wg_elems + 1) * sizeof(WgRec)) + 1;
+    d.err = (unsigned *)d.wg_rec - MOVED - 2;
     d.tile_top = (int4 *)take(n_tiles_max * sizeof(int4));
     d.ltop = (uint2 *)take(ltop_elems * sizeof(uint2));
     for (auto &f : d.fix)
         f = (int4 *)take((plain ? n : 0) * sizeof(int4));
     d.hi_skin = (float4 *)take((plain ? n : 0) * sizeof(float4));
     d.skin_flag = (unsigned *)take(sizeof(unsigned));
+    d.place = (unsigned *)take(n * sizeof(unsigned));
+    d.pack_moved = (unsigned *)take((plain ? 0 : T) * sizeof(unsigned));
+    d.pack_done = (int *)take((plain ? 0 : T) * sizeof(int));
     d.list_stats = (unsigned long long *)take(2 * sizeof(unsigned long long));
     d.skin_ord = (unsigned short *)take((plain ? n_tiles_max * 256 : 0) * sizeof(unsigned short));
     d.vel = (float4 *)take((plain ? n : 0) * sizeof(float4));
@@ -245,7 +249,6 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
     d.words = (uint4 *)take(n * sizeof(uint4));
     d.step_base = (long long *)take(sizeof(long long));
     d.step_next = (long long *)take(sizeof(long long));
-    d.err = (unsigned *)take(sizeof(unsigned));
     if (b)
         *b = d;
     return off;
@@ -365,23 +368,39 @@ StepConsts step_consts(const sop_ctx *c)
 // Scale of the fixed-point copies: the coarsest power of two
 // that keeps 2.5 times the distance a listed pair can have (r_list, and 16
 // standard deviations of the thermal drift of a list period, eight for each
-// partner) inside half the period of 2^32 units, so that a listed pair would
-// have to move 3 list cutoffs further apart within a list period before its
-// difference wrapped to a wrong near one.  At r_list = 20 A: k = 25, half a
-// period 64 A, unit 3e-8 A.  Bonded and native terms, which are steep where the forces cancel,
+// partner) inside half the period of 2^32 units, H.  At r_list = 20 A: k = 25,
+// H 64 A, unit 3e-8 A.  Bonded and native terms, which are steep where the forces cancel,
 // use the copies only while a unit is below 2^-24 of the shortest reference
 // length (the rounding of that length in single precision), the list only
 // while it is below 2e-6 sigma.
-// `narrow`: copies relative to a tile's origin wrap at half a period H, and a
-// list partner lies up to r_list further out than the tile's residues, plus
-// what it moves until the next rebuild, for which the drift or H / 16 is left.
-// At 300 K and the time step of the reference workloads: 40 A from r_list =
-// 10.6 A (H = 64 A) to 20 A, 37 A at 23 A, 20 A at 10 A (H = 32 A).
+// `narrow`: copies relative to a tile's origin wrap at H, and a list partner
+// lies up to r_list further out than the tile's residues, plus what it moves
+// until the next rebuild, for which a margin is left.  At 300 K and the time
+// step of the reference workloads: 40 A from r_list = 10.6 A (H = 64 A) to
+// 20 A, 37 A at 23 A, 18 A at 10 A (H = 32 A).
+// The margin is also what a residue may move until the next rebuild, H / 4 at
+// most (pairs are H / 2 apart at most at the rebuild): 4 A at r_list = 20 A.
+// Thermal motion never exceeds it; whatever does (a clash that throws a
+// residue off, a fast anchor) makes the steps until the next rebuild take the
+// compensated positions.  `by_step`: no step may take more than its share of
+// the margin, which must be 8.5 standard deviations of a step's noise: one
+// comparison a step, for list periods up to some 100 steps (H / 8).  Longer ones
+// compare every residue with its place at the rebuild, to 10 bits an axis
+// (`move`, from below; a step of at most `jump`, four times it, cannot go
+// round).  us a step
+// kernel without a check, by step, by place: 56 residues 4.0, 4.1, 4.2; 4,801
+// 8.4, 8.8, 8.9; 75,000 13.5, 13.6, 13.9; 250,000 35.2, 35.7, 36.3.
+// Batched: H / 8, as a launch within a list period takes the reach of bonded and
+// native pairs anew; 128 periods where differences are taken over the periods,
+// of which the copies hold 1,024, and a trajectory may span 256.  500 steps of
+// 200 chains 6.04 -> 6.27 ms with the check and the launches behind (k_batch_exact),
+// of 4,096 31.6 -> 31.9.
 constexpr double NARROW_MAX = 40.0;
 
 FixDev fix_consts(const sop_ctx *c)
 {
-    const double drift = 16.0 * std::sqrt(2.0 * c->p.kBT * c->p.h / c->p.zeta * c->p.list_every);
+    const double noise = std::sqrt(2.0 * c->p.kBT * c->p.h / c->p.zeta), steps = c->p.list_every;
+    const double drift = 16.0 * noise * std::sqrt(steps);
     const double half = 2.5 * (c->p.r_list + drift);
     int k = 31 - (int)std::ceil(std::log2(std::min(std::max(half, 1e-9), 1e30)));
     // batched: bonded and native terms have the copies alone, so the unit
@@ -389,6 +408,7 @@ FixDev fix_consts(const sop_ctx *c)
     if (c->schedule == SOP_SCHEDULE_BATCHED)
         k = std::max(k, std::min(28, 24 - (int)std::floor(std::log2(std::min(std::max(c->min_r0, 1e-9), 1e30)))));
     k = std::max(-60, std::min(60, k));
+    const double H = std::ldexp(1.0, 31 - k);
     FixDev f{};
     f.scale = std::ldexp(1.0, k);
     f.period = std::ldexp(1.0, 32 - k);
@@ -397,10 +417,22 @@ FixDev fix_consts(const sop_ctx *c)
     f.s2 = (float)std::ldexp(1.0, 2 * k);
     f.reach = (float)std::ldexp(1.0, 30 - k);
     f.direct = (float)std::ldexp(1.0, 50 - k);
-    const double H = std::ldexp(1.0, 31 - k);
-    f.narrow = (float)std::min(NARROW_MAX, H - c->p.r_list - std::max(drift, H / 16));
-    f.list_far = (half > std::ldexp(1.0, 31 - k) || f.unit > 2e-6 * c->p.sigma) ? 1 : 0;
+    f.list_far = (half > H || f.unit > 2e-6 * c->p.sigma) ? 1 : 0;
     f.bond_far = f.unit > std::ldexp(c->min_r0, -24) ? 1 : 0;
+    const double share = 8.5 * noise * steps, periods = 256 * H;  // 128 of them
+    double move, grain = 1.0;
+    if (c->schedule == SOP_SCHEDULE_BATCHED) {
+        move = f.list_far ? periods : H / 8;
+        grain = f.list_far ? std::ldexp(1.0, -10) : 1.0;
+        f.by_step = share <= move ? 1 : 0;
+    } else {
+        f.by_step = share <= H / 8 ? 1 : 0;
+        f.narrow = (float)std::min(NARROW_MAX, H - c->p.r_list - std::max({drift, H / 16, f.by_step ? share : 0.0}));
+        move = f.list_far ? H / 4 : std::min(H / 4, H - f.narrow - c->p.r_list);
+    }
+    f.move = (unsigned)(move * f.scale * grain) - (1u << 22);
+    f.jump = (float)(f.by_step ? move / steps : 4 * move);
+    f.spread = (float)periods;
     return f;
 }
 
@@ -1467,6 +1499,7 @@ sop_status sop_bind_workspace(sop_ctx *c, void *dev, size_t bytes)
                                       hipMemcpyHostToDevice, s));
         }
         HIP_TRY(c, hipMemsetAsync(b.tile_top, 0, n_tiles_max * sizeof(int4), s));
+        HIP_TRY(c, hipMemsetAsync(b.err + MOVED, 0, 2 * sizeof(unsigned), s));
         HIP_TRY(c, hipMemsetAsync(b.cell_count, 0, (size_t)c->n_cells_cap * sizeof(int), s));
         HIP_TRY(c, hipMemsetAsync(b.facc, 0, n * sizeof(float4), s));
         HIP_TRY(c, hipMemsetAsync(b.vel, 0, n * sizeof(float4), s));
@@ -1935,9 +1968,14 @@ sop_status sop_step_timed(sop_ctx *c, int64_t n_steps, double *ms_out)
             out = hip_fail(c, e, "hipStreamBeginCapture");
             break;
         }
+        // the steps run on past the list's period: whatever they move, the
+        // kernel timed is the ordinary one
+        FixDev fix = fix_consts(c);
+        fix.move = 0x7fffffffu;
+        fix.jump = 3.0e38f;
         for (long long q = 0; q < K; ++q) {
             if (kind == 0) {
-                launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), fix_consts(c), c->tip,
+                launch_step(c->b, c->cur, (int)c->n_res, c->cap, c->tile, step_consts(c), fix, c->tip,
                             c->pulls.empty() ? 0 : 1, false, 0, nullptr, c->step + q, 0.0f,
                             c->cap_stream, c->force_mode, 0.0f);
                 c->cur ^= 1;

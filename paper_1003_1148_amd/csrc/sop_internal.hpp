@@ -70,13 +70,20 @@ constexpr int STAGE_MAX = 4096;
 // rebuild is taken from the copies until the next one, others (and every
 // such pair when `bond_far`, every list pair when `list_far`) from the
 // compensated positions; the batched schedule, which has the copies alone,
-// keeps the periods below them beside them and takes such pairs (and the list
-// when `list_far`) over both.
+// keeps the periods below them beside them and takes such pairs (and, when
+// `list_far`, all) over both.  That holds while no residue has moved too far
+// since the rebuild: more than `jump` in one step, or, unless `by_step`, more
+// than `move` units (batched and `list_far`: of 2^-22 periods) from its place
+// then; and, batched, while a trajectory's residues are within `spread` of its
+// first at the rebuild.
 struct FixDev {
     double scale, period, inv_period;  // 2^k, 2^(32-k), 2^(k-32)
     float unit, s2, reach, direct;     // 2^-k, 2^2k, 2^(30-k), 2^(50-k)
     float narrow;                      // plain: largest half-width of a tile taken around one origin
     int list_far, bond_far;
+    unsigned move;
+    float jump, spread;
+    int by_step;
 };
 
 // Plain schedule: what a workgroup's steps need to know of it, written at
@@ -115,6 +122,9 @@ struct DevBufs {
     uint2 *ltop;             // plain: bonded and native entries in lane order (top_index): {partner, r0 bits}
     float4 *hi_skin;         // plain: high parts of the positions at the last skin build
     unsigned *skin_flag;     // plain: nonzero when the next rebuild must rebuild the skin
+    unsigned *place;         // per residue, its copy at the last rebuild to 10 bits an axis (unless FixDev::by_step)
+    unsigned *pack_moved;    // batched: per pack, whether a residue has moved too far since the rebuild
+    int *pack_done;          // batched: per pack, steps of the last launch before that
     unsigned long long *list_stats;  // plain: {rebuilds, skin builds} since binding
     unsigned short *skin_ord;  // plain: per tile (tile * T + rank), 1 + its residues by decreasing
                                // skin row length (0 before the first skin search: identity)
@@ -158,8 +168,10 @@ struct DevBufs {
     uint4 *words;            // Philox words (noise samples)
     long long *step_base;    // graph replays: step of the period's first step
     long long *step_next;
-    unsigned *err;
+    unsigned *err;           // ERR_*; plain: MOVED words from it, per layer, nonzero where a residue has moved too
+                             // far since the rebuild, which end where wg_rec begins (to be loaded with it)
 };
+constexpr int MOVED = 2;
 
 struct StepConsts {
     float k_fene, R0sq, inv_R0sq, eps_h, eps_l, sigma2;

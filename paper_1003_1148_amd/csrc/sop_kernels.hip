@@ -119,8 +119,34 @@ __device__ __forceinline__ float3 fix_full_diff(const int4 &a, const int4 &b)
     return make_float3(d[0], d[1], d[2]);
 }
 
+// The same at any distance, from the compensated positions.
+__device__ __forceinline__ float3 fix_exact_diff(const float4 &hi, const float4 &lo, const float4 &hj,
+                                                 const float4 &lj, const FixDev &f)
+{
+    float d[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        const double xi = (double)comp(hi, ax) + (double)comp(lo, ax), xj = (double)comp(hj, ax) + (double)comp(lj, ax);
+        d[ax] = (float)(__builtin_rint(xi * f.scale) - __builtin_rint(xj * f.scale));
+    }
+    return make_float3(d[0], d[1], d[2]);
+}
+
 // Difference of two fixed-point coordinates, modulo 2^32.
 __device__ __forceinline__ int fix_diff(int a, int b) { return (int)((unsigned)a - (unsigned)b); }
+
+// A copy to 10 bits an axis, and whether one that was at `place` then may be
+// further than FixDev::move from it.
+__device__ __forceinline__ unsigned fix_place(const int4 &q)
+{
+    return (unsigned)q.x >> 22 | ((unsigned)q.y >> 22) << 10 | ((unsigned)q.z >> 22) << 20;
+}
+
+__device__ __forceinline__ bool strayed(const int4 &q, unsigned place, const FixDev &f)
+{
+    auto out = [&](int x, unsigned p) { return (unsigned)fix_diff(x, (int)(p << 22)) + f.move > 2u * f.move; };
+    return out(q.x, place) || out(q.y, place >> 10) || out(q.z, place >> 20);
+}
 
 // Bin one residue at high part p into the grid of the next skin search:
 // its cell, a slot in that cell, and a copy of p there.
@@ -380,18 +406,22 @@ __device__ __forceinline__ uint4 noise_words(unsigned tag, unsigned stream, long
 
 // First-order update with the Gaussian components g:
 // (hi, lo) <- TwoSum(hi, f h/zeta + g sqrt(2 kB T h/zeta) + lo) per axis.
+// A step longer than `most` on an axis sets *moved; one that is not leaves
+// finite positions finite.
 __device__ __forceinline__ void update_with_noise(float4 &hi, float4 &lo, const Acc &A, const float g[3],
-                                                  const StepConsts &c, unsigned *err)
+                                                  const StepConsts &c, float most, unsigned *moved, unsigned *err)
 {
 #pragma clang fp contract(off)
     if (__float_as_uint(hi.w) >> 31)
         return;  // fixed residue
     float nh[3], nl[3];
+    bool within = true;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         const float f = ax == 0 ? A.fx : (ax == 1 ? A.fy : A.fz);
         const float h0 = comp(hi, ax), l0 = comp(lo, ax);
         const float delta = __builtin_fmaf(c.c_drift, f, c.c_noise * g[ax]);
+        within &= fabsf(delta) <= most;
         const float y = delta + l0;
         const float t = h0 + y;
         const float bp = t - h0;
@@ -399,9 +429,12 @@ __device__ __forceinline__ void update_with_noise(float4 &hi, float4 &lo, const 
         nl[ax] = (h0 - ap) + (y - bp);
         nh[ax] = t;
     }
-    if (!isfinite(nh[0]) || !isfinite(nh[1]) || !isfinite(nh[2]) || !isfinite(nl[0]) ||
-        !isfinite(nl[1]) || !isfinite(nl[2]))
-        atomicOr(err, ERR_NONFINITE);
+    if (__builtin_expect(!within, 0)) {
+        *moved = 1u;
+        if (!isfinite(nh[0]) || !isfinite(nh[1]) || !isfinite(nh[2]) || !isfinite(nl[0]) ||
+            !isfinite(nl[1]) || !isfinite(nl[2]))
+            atomicOr(err, ERR_NONFINITE);
+    }
     hi = make_float4(nh[0], nh[1], nh[2], hi.w);
     lo = make_float4(nl[0], nl[1], nl[2], lo.w);
 }
@@ -416,7 +449,8 @@ struct UdConsts {
 };
 
 __device__ __forceinline__ void underdamped_update(float4 &hi, float4 &lo, float4 &v, const Acc &A,
-                                                   const float g[3], const UdConsts &u, unsigned *err)
+                                                   const float g[3], const UdConsts &u, float most, unsigned *moved,
+                                                   unsigned *err)
 {
 #pragma clang fp contract(off)
     if (__float_as_uint(hi.w) >> 31) {
@@ -424,12 +458,14 @@ __device__ __forceinline__ void underdamped_update(float4 &hi, float4 &lo, float
         return;
     }
     float nh[3], nl[3], nv[3];
+    bool within = true;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         const float f = ax == 0 ? A.fx : (ax == 1 ? A.fy : A.fz);
         const float w0 = __builtin_fmaf(u.kick, f, comp(v, ax));
         const float w1 = __builtin_fmaf(u.c1, w0, u.c2 * g[ax]);
         const float delta = __builtin_fmaf(u.half_h, w0, u.half_h * w1);
+        within &= fabsf(delta) <= most;
         const float h0 = comp(hi, ax), l0 = comp(lo, ax);
         const float y = delta + l0;
         const float t = h0 + y;
@@ -439,6 +475,8 @@ __device__ __forceinline__ void underdamped_update(float4 &hi, float4 &lo, float
         nh[ax] = t;
         nv[ax] = w1;
     }
+    if (__builtin_expect(!within, 0))
+        *moved = 1u;
     if (!isfinite(nh[0]) || !isfinite(nh[1]) || !isfinite(nh[2]) || !isfinite(nv[0]) ||
         !isfinite(nv[1]) || !isfinite(nv[2]))
         atomicOr(err, ERR_NONFINITE);
@@ -602,6 +640,7 @@ __global__ __launch_bounds__(NT, NT > 256 ? 4 : (TILE == 64 ? 5 : 2)) void k_til
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         // every rebuild starts here (the kernels after it do not read these)
         ++a.stats[0];
+        a.err[MOVED] = a.err[MOVED + 1] = 0u;
         if (a.step_base) {
             // graph replays: this rebuild starts the next list period
             const long long nb = *a.step_next;
@@ -1002,6 +1041,8 @@ struct FilterArgs {
     WgRec *wg_rec;
     int *cell_count;
     unsigned *skin_flag;
+    const int4 *fixed;               // k_filter: fixed-point copies of the positions
+    unsigned *place;
     FixDev fix;
     float rc2;
     int cap, n_cells, top_rounds;
@@ -1292,6 +1333,8 @@ __global__ __launch_bounds__(256, NL == 1 ? 2 : 5) void k_filter(FilterArgs a)
     const int r = t / NL * R::W + part;
     const bool in = r < tcnt;
     const int rho = in ? ranked(a.skin_ord, (size_t)tile * TILE + r, r) : 0;
+    if (!a.fix.by_step && in && t % NL == 0)
+        a.place[first + rho] = fix_place(a.fixed[first + rho]);
     WgRec wr;
     filter_rows<TILE, NL>(a, wg, tile, t, first, tcnt, in, rho, region, ring, bb, wr);
 }
@@ -1575,7 +1618,9 @@ struct TileArgs {
     const int4 *qin;        // fixed-point copies of the positions
     const uint2 *list16;
     const int *stage;
-    int n_wg, chunks, top_rounds, has_pull, do_bin;
+    int n_wg, chunks, top_rounds;
+    int layer;  // of the MOVED words, read; the other is written, so that all workgroups of a launch read the same
+    int has_pull, do_bin;
     FixDev fix;
     StepConsts c;
     UdConsts ud;
@@ -1594,6 +1639,7 @@ struct TileArgs {
     // new positions for the next skin search (do_bin)
     const float4 *hi_skin;
     unsigned *skin_flag;
+    unsigned *place;
     const int4 *traj_cell;
     int *cell_count;
     float4 *cells;
@@ -1634,8 +1680,9 @@ __device__ __forceinline__ float lane_xor(float v, int off)
 //  3. After the barrier the list chunks are summed from LDS.  Where the
 //     residues do not fit around one origin (wide), or the slots one window,
 //     the copies themselves are staged and subtracted.  A workgroup with a bonded or native pair out of the
-//     copies' reach (far), and a list whose cutoff is (list_far), take the
-//     compensated positions from memory.
+//     copies' reach (far), a list whose cutoff is (list_far), and every
+//     workgroup once a residue has moved too far since the rebuild (moved),
+//     take the compensated positions from memory.
 //     The NL partial sums of a residue are added by butterfly shuffles,
 //     which give every lane the same bits.
 //  4. After a second barrier the last RW lanes add the external terms and
@@ -1723,8 +1770,13 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
     int rhou = ue;
     if (W > 1 && !FIRST)
         rhou = a.grho[wg * RW + max(ue, 0)];
-    if (!FIRST)
+    int2 mv = make_int2(0, 0);
+    if (!FIRST) {
         wr = a.wg_rec[wg];
+        mv = reinterpret_cast<const int2 *>(a.wg_rec)[-1];
+    }
+    // a residue strayed since the rebuild (which this launch follows if FIRST)
+    const bool moved = !FIRST && (a.layer ? mv.y : mv.x) != 0;
     const long long step = (a.step_base ? *a.step_base : 0) + a.step_off;
     const int first = wr.first, tcnt = wr.count, S = wr.slots;
     const bool upd = ue >= 0 && ru < tcnt;
@@ -1740,7 +1792,10 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
     float4 hu = a.pin[2 * iu], lu = a.pin[2 * iu + 1];
     const int4 qi = a.qin[i];
     // ---- 2. positions, noise and external terms (update lanes), bonded/native ----
-    const bool fast = !a.fix.list_far && !(wr.flags & WG_WIDE) && S <= SW;
+    const bool list_far = a.fix.list_far || moved, bond_far = a.fix.bond_far || moved;
+    const bool fast = !list_far && !(wr.flags & WG_WIDE) && S <= SW;
+    if (FIRST && !a.fix.by_step && q == 0 && g * W + part < tcnt)
+        a.place[i] = fix_place(qi);
     float *sr = reinterpret_cast<float *>(region);  // x, y, z of slot s at s, XS + s, 2 XS + s
     const int *st = a.stage + (size_t)tile * SM;
     if (wr.flags & WG_IDS32) {
@@ -1797,13 +1852,13 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
     Acc A;   // bonded and native terms
     {
         // in fixed-point units unless a pair is out of the copies' range
-        const bool far = a.fix.bond_far || (wr.flags & WG_FAR);
+        const bool far = bond_far || (wr.flags & WG_FAR);
         const float eu = k.eh12 * a.fix.unit;
         bool broken = false;
         auto diff = [&](const int4 &p) {
             return make_float3((float)fix_diff(qi.x, p.x), (float)fix_diff(qi.y, p.y), (float)fix_diff(qi.z, p.z));
         };
-        auto out_of_range = [&](unsigned x) { return far && (a.fix.bond_far || x >= FAR_ENTRY); };
+        auto out_of_range = [&](unsigned x) { return far && (bond_far || x >= FAR_ENTRY); };
         auto delta = [&](unsigned x) {
             const unsigned j = x & ~FAR_ENTRY;
             return pair_delta(a.pin[2 * i], a.pin[2 * i + 1], a.pin[2 * j], a.pin[2 * j + 1]);
@@ -1917,7 +1972,7 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
                 chunk(w);
             }
         }
-    } else if (!a.fix.list_far) {
+    } else if (!list_far) {
         // the copies, window by window: the entries ascend, so a lane goes
         // on where the window before ended
         lscale = k.c6 * a.fix.unit;
@@ -2017,16 +2072,20 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
         return;
     }
     float4 hi = hu, lo = lu;
+    unsigned *moved_out = a.err + MOVED + (a.layer ^ 1);
     if (a.vel) {
         float4 v = a.vel[iu];
-        underdamped_update(hi, lo, v, F, gn, a.ud, a.err);
+        underdamped_update(hi, lo, v, F, gn, a.ud, a.fix.jump, moved_out, a.err);
         a.vel[iu] = v;
     } else {
-        update_with_noise(hi, lo, F, gn, a.c, a.err);
+        update_with_noise(hi, lo, F, gn, a.c, a.fix.jump, moved_out, a.err);
     }
     a.pout[2 * iu] = hi;
     a.pout[2 * iu + 1] = lo;
-    a.qout[iu] = fix_pos(hi, lo, a.fix);
+    const int4 qn = fix_pos(hi, lo, a.fix);
+    a.qout[iu] = qn;
+    if (__builtin_expect(moved || !a.fix.by_step, 0) && (moved || strayed(qn, a.place[iu], a.fix)))
+        *moved_out = 1u;
     if (a.check_thr2 > 0.0f) {
         // moved farther than skin/2 from the last skin build: the next
         // rebuild rebuilds the skin
@@ -2220,6 +2279,8 @@ struct PairUpdArgs {
     const long long *step_base;
     const float4 *hi_skin;
     unsigned *skin_flag;
+    const unsigned *place;
+    int layer;  // as in TileArgs, for particle-based steps, if the mode changes within a period
     float4 *vel;
     const int4 *traj_cell;
     int *cell_count;
@@ -2278,16 +2339,20 @@ __global__ __launch_bounds__(256) void k_pair_update(PairUpdArgs a)
         g[2] = gaussian_axis(w, 2);
     }
     float4 hi = hi0, lo = lo0;
+    unsigned *moved_out = a.err + MOVED + (a.layer ^ 1);
     if (a.vel) {
         float4 v = a.vel[i];
-        underdamped_update(hi, lo, v, F, g, a.ud, a.err);
+        underdamped_update(hi, lo, v, F, g, a.ud, a.fix.jump, moved_out, a.err);
         a.vel[i] = v;
     } else {
-        update_with_noise(hi, lo, F, g, a.c, a.err);
+        update_with_noise(hi, lo, F, g, a.c, a.fix.jump, moved_out, a.err);
     }
     a.pout[2 * i] = hi;
     a.pout[2 * i + 1] = lo;
-    a.qout[i] = fix_pos(hi, lo, a.fix);
+    const int4 qn = fix_pos(hi, lo, a.fix);
+    a.qout[i] = qn;
+    if (a.err[MOVED + a.layer] != 0u || (!a.fix.by_step && strayed(qn, a.place[i], a.fix)))
+        *moved_out = 1u;
     if (a.check_thr2 > 0.0f) {
         const float4 hs = a.hi_skin[i];
         const float dx = hi.x - hs.x, dy = hi.y - hs.y, dz = hi.z - hs.z;
@@ -2315,6 +2380,23 @@ __device__ __forceinline__ int4 lds_pos(const char *base, unsigned off)
     return make_int4(v.x, v.y, v.z, v.w);
 }
 
+// Four of them, the reads all in flight before the first is used (100 steps of
+// 200 chains 1,148 -> 1,053 us, of 4,096 chains 5.96 -> 5.70 ms against a wait
+// for each).
+template <class M>
+__device__ __forceinline__ void lds_pos4(const char *base, const unsigned (&off)[4], M m, int4 (&p)[4])
+{
+    typedef int vec4 __attribute__((ext_vector_type(4)));
+    vec4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        v[u] = *reinterpret_cast<const vec4 *>(base + (u < m ? off[u] : 0u));
+    asm volatile("" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        p[u] = make_int4(v[u].x, v[u].y, v[u].z, v[u].w);
+}
+
 struct BatchArgs {
     const float4 *pin;
     float4 *pout;
@@ -2329,6 +2411,9 @@ struct BatchArgs {
     const PullDev *pulls;
     unsigned short *list;     // entry k of residue i at i*cap + k
     int *list_cnt;
+    unsigned *place;          // per residue, as fix_place (unless by_step)
+    unsigned *moved;          // per pack
+    int *done;                // per pack: steps of this launch that k_batch took
     double *energy;
     double *f_ext;
     float4 *fout;
@@ -2392,8 +2477,15 @@ __device__ __forceinline__ void traj_sums(double *red, int t, double (&v)[3], in
 // longest rows: 54.5, 10.3 and 10.5; two lanes a residue (batch_split): 9.7.
 constexpr int NBUCKET = 64;
 
-template <int WGS, int MODE, int SPLIT>
-__global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
+// FAR: the list's differences are taken over the periods (FixDev::list_far), in
+// a kernel of its own, as what they take in registers the others spill.
+// EXACT: a residue has moved too far since the rebuild for differences of the
+// copies (or lay too far off then); all are taken from the compensated
+// positions instead, shared through the layer that is written, with the same
+// bits wherever the copies hold.  The other form leaves such a pack where it
+// is (`done`) to a launch of this one behind it.
+template <int WGS, int MODE, int SPLIT, bool FAR, bool EXACT>
+__device__ __forceinline__ void batch_pack(const BatchArgs &a, int p)
 {
     static_assert(SPLIT == 1 || (SPLIT == 2 && MODE == 0), "records are taken by one lane a residue");
     constexpr int TH = WGS * SPLIT;
@@ -2414,8 +2506,8 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
     __shared__ double esum[2][MODE == 0 ? 1 : WGS];  // record steps: list energy and virial of each residue
     __shared__ int hist[WGS / 64][NBUCKET];
     __shared__ int sres[WGS];           // residue of each local slot
+    __shared__ unsigned moved_s;        // a residue has moved too far since the rebuild
     __shared__ float3 bblo[WGS / 32], bbhi[WGS / 32];  // list rebuild: boxes of 32-slot blocks
-    const int p = blockIdx.x;
     const int off = a.pack_off[p];
     const int n = a.pack_off[p + 1] - off;
     // slot of this lane; SPLIT 2: lanes in the upper half of the workgroup
@@ -2433,19 +2525,32 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
     int tlo = 0, thi = 0;
     int2 row = make_int2(0, 0);
     int cnt = 0;
+    // positions as they are in memory while this pack is stepped
+    const float4 *live = MODE == 1 ? a.pin : a.pout;
     if (act) {
-        hi = a.pin[2 * i];
-        lo = a.pin[2 * i + 1];
+        hi = EXACT ? live[2 * i] : a.pin[2 * i];
+        lo = EXACT ? live[2 * i + 1] : a.pin[2 * i + 1];
         tlo = a.traj_lo[i] + shift;
         thi = a.traj_hi[i] + shift;
         row = a.trow[i];
         cnt = a.list_cnt[i];
     }
     int4 qi = fix_pos(hi, lo, a.fix);
+    const long long s0 = (a.step_base ? *a.step_base : 0) + a.step_off;
+    const int q0 = EXACT ? a.done[p] : 0;
+    const bool fresh = (q0 == 0 && a.stale) || (s0 + q0) % a.list_every == 0;  // starts with a rebuild
     if (own) {
         sq[t] = qi;
         sres[t] = i;
+        if (!isfinite(hi.x) || !isfinite(hi.y) || !isfinite(hi.z))
+            atomicOr(a.err, ERR_NONFINITE);
+        if (t == 0)
+            moved_s = fresh ? 0u : a.moved[p];
     }
+    // what is compared with a residue's place: its copy, or the periods below it
+    auto coarse = [&](const int4 &q) {
+        return a.fix.list_far ? make_int4(q.w << 22, (q.w >> 10) << 22, (q.w >> 20) << 22, 0) : q;
+    };
     const int nb = row.y & 4095, ntop = nb + (row.y >> 12);
     // the pack's bonded/native entries in LDS (entries past TCAP stay in
     // global memory)
@@ -2473,7 +2578,6 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
     };
     // rows are residue-major: entry k (a local slot) of residue i at i cap + k
     uint2 *rowp = reinterpret_cast<uint2 *>(a.list + (size_t)i * a.cap);
-    const long long s0 = (a.step_base ? *a.step_base : 0) + a.step_off;
     const PairConsts kc = pair_consts(a.c);
     const int traj = __float_as_int(lo.w);
     // this trajectory's temperature (fixed within a launch)
@@ -2573,8 +2677,8 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
     // the next rebuild (the full ones give the same bits within it)
     bool far = false;
     auto check_reach = [&]() {
-        far = false;
-        if (!topo)
+        far = FAR;
+        if (!topo || FAR || EXACT)
             return;
         const float lim = a.fix.reach * (float)a.fix.scale;
         const int4 p = sq[tr];
@@ -2587,18 +2691,24 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
         }
     };
     __syncthreads();
-    if (!(a.stale || s0 % a.list_every == 0)) {
+    if (!fresh) {
         check_reach();
         assign();
     }
 
-    for (int q = 0; q < a.n_steps; ++q) {
+    int q = q0;
+    for (; q < a.n_steps; ++q) {
         const long long step = s0 + q;
         if ((q == 0 && a.stale) || step % a.list_every == 0) {
             check_reach();
             __syncthreads();
-            if (own)
+            if (own) {
                 shh[t] = hi;  // the high parts, until the rows are written
+                if (__builtin_expect(!a.fix.by_step, 0) && act)
+                    a.place[i] = fix_place(coarse(qi));
+                if (t == 0)
+                    moved_s = 0u;
+            }
             {
                 // boxes of the 32-slot blocks (empty slots add nothing)
                 float3 bl = act ? make_float3(hi.x, hi.y, hi.z) : make_float3(3.0e38f, 3.0e38f, 3.0e38f);
@@ -2620,6 +2730,11 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
             }
             if (SPLIT == 2 && !own)
                 hi = shh[t];  // where its slot's own lane has moved it
+            if (act && own) {
+                const float4 o = shh[tlo];
+                if (!(fmaxf(fmaxf(fabsf(hi.x - o.x), fabsf(hi.y - o.y)), fabsf(hi.z - o.z)) <= a.fix.spread))
+                    moved_s = 1u;
+            }
             // Algorithm 3 over the trajectory: r < r_list, not bonded or
             // native. Candidates are tested a 32-slot block at a time into a
             // bit word (blocks whose box is out of reach of every lane of the
@@ -2748,6 +2863,12 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
         // mode 0 never records (no FP64 sums in its registers); mode 2
         // records at multiples of the energy interval, in a copy of the
         // forces and update compiled for record steps alone
+        if (!EXACT && __builtin_expect(__builtin_amdgcn_readfirstlane((int)moved_s) != 0, 0))
+            break;
+        auto exact_diff = [&](int slot, int partner_slot) {
+            const int ri = sres[slot], rj = sres[partner_slot];
+            return fix_exact_diff(live[2 * ri], live[2 * ri + 1], live[2 * rj], live[2 * rj + 1], a.fix);
+        };
         const bool rec_step = MODE == 1 || (MODE == 2 && a.energy_every > 0 && step % a.energy_every == 0);
         auto forces_and_update = [&](auto rec_tag) {
             constexpr bool rec = decltype(rec_tag)::value;
@@ -2764,17 +2885,15 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
                 const uint2 *rh = reinterpret_cast<const uint2 *>(rp) + half;
                 const int last = max((my >> 16) - 1, 0) >> 3, left = (my >> 16) & 7;
                 Acc L, M;
-                auto sweep = [&](auto list_far) {
+                auto sweep = [&](auto general) {
                     // four partners, `m` of them the row's (all of them: a constant)
                     auto chunk = [&](Acc &L, unsigned wx, unsigned wy, auto m) {
                         const unsigned off[4] = {wx & 0xffffu, wx >> 16, wy & 0xffffu, wy >> 16};
                         int4 pj[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            pj[u] = lds_pos(sqb, u < m ? off[u] : 0u);
+                        lds_pos4(sqb, off, m, pj);
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
-                            if (list_far()) {
+                            if (general()) {
                                 const float3 d = fix_full_diff(pr, pj[u]);
                                 if (u < m)
                                     add_repulsive_u(L,
@@ -2811,10 +2930,18 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
                             chunk(L, w.x, w.y, left - 4 * half);
                     }
                 };
-                if (a.fix.list_far)
-                    sweep(std::true_type{});
-                else
-                    sweep(std::false_type{});
+                if constexpr (EXACT) {
+                    const unsigned short *row16 = reinterpret_cast<const unsigned short *>(rp);
+#pragma unroll 1
+                    for (int e = 0; e < my >> 16; ++e) {
+                        Acc P = (e & 4) ? M : L;
+                        const float3 d = exact_diff(r, row16[e] >> 4);
+                        add_repulsive_u(P, make_float3(d.x * a.fix.unit, d.y * a.fix.unit, d.z * a.fix.unit), kc, rec);
+                        ((e & 4) ? M : L) = P;
+                    }
+                } else {
+                    sweep(std::integral_constant<bool, FAR>{});
+                }
                 if (t < n) {
                     if (SPLIT == 2) {
                         lsum[3 * half][r] = L.fx;
@@ -2839,11 +2966,11 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
             // term's code alone.  Record steps take every lane's own residue
             // (its energies belong there), others the slot sorted to the lane.
             {
-                auto terms = [&](const int4 &p, int off0, int x, int sh, int nbond, int nall, auto general) {
+                auto terms = [&](const int4 &p, int slot, int off0, int x, int sh, int nbond, int nall, auto general) {
                     auto next = [&](int e, int &j, float &r0) -> float3 {
                         if (general()) {
                             entry(off0, x, sh, nbond, e, j, r0);
-                            return fix_full_diff(p, lds_pos(sqb, j));
+                            return EXACT ? exact_diff(slot, j >> 4) : fix_full_diff(p, lds_pos(sqb, j));
                         }
                         j = tpart[off0 + e];
                         r0 = tr0[off0 + e];
@@ -2866,13 +2993,13 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
                     }
                 };
                 if (rec) {
-                    terms(qi, toff, row.x, shift, nb, ntop, std::true_type{});
+                    terms(qi, t, toff, row.x, shift, nb, ntop, std::true_type{});
                 } else if (topo) {
                     const int4 p = sq[tr];
-                    if (__any(far || !tr_lds))
-                        terms(p, tr_off, tr_x, tr_shift, tr_nb, tr_ntop, std::true_type{});
+                    if (FAR || EXACT || __any(far || !tr_lds))
+                        terms(p, tr, tr_off, tr_x, tr_shift, tr_nb, tr_ntop, std::true_type{});
                     else
-                        terms(p, tr_off, tr_x, tr_shift, tr_nb, tr_ntop, std::false_type{});
+                        terms(p, tr, tr_off, tr_x, tr_shift, tr_nb, tr_ntop, std::false_type{});
                     if (t < n) {
                         tsum[0][tr] = A.fx;
                         tsum[1][tr] = A.fy;
@@ -2895,7 +3022,7 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
             if (act && own) {
                 add_external(A, e_x, f_rep, hi, lo, step, a.c.h, a.has_pull ? a.pull_slot[i] : -1, a.pulls,
                              a.tip, rec, a.err);
-                const float ls = a.fix.list_far ? kc.c6 : kc.c6 * a.fix.unit;
+                const float ls = FAR || EXACT ? kc.c6 : kc.c6 * a.fix.unit;
                 float l[3] = {lsum[0][t], lsum[1][t], lsum[2][t]};
                 if (SPLIT == 2) {
 #pragma unroll
@@ -2936,15 +3063,22 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
             if (act && own) {
                 if (SPLIT == 1)
                     draw_noise(gn, hi, step, stream, cn);
-                update_with_noise(hi, lo, A, gn, cn, a.err);
+                update_with_noise(hi, lo, A, gn, cn, a.fix.jump, &moved_s, a.err);
                 qi = fix_pos(hi, lo, a.fix);
                 sq[t] = qi;
+                if (EXACT) {
+                    a.pout[2 * i] = hi;
+                    a.pout[2 * i + 1] = lo;
+                }
+                if (__builtin_expect(!a.fix.by_step, 0) && strayed(coarse(qi), a.place[i], a.fix))
+                    moved_s = 1u;
             }
             __syncthreads();
         };
         if constexpr (MODE == 1) {
             forces_and_update(std::true_type{});
-            return;
+            ++q;
+            break;
         } else if constexpr (MODE == 0) {
             forces_and_update(std::false_type{});
         } else {
@@ -2954,9 +3088,38 @@ __global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
                 forces_and_update(std::false_type{});
         }
     }
-    if (MODE != 1 && act && own) {
+    if (MODE != 1 && !EXACT && act && own) {
         a.pout[2 * i] = hi;
         a.pout[2 * i + 1] = lo;
+    }
+    if (threadIdx.x == 0) {
+        a.moved[p] = moved_s;
+        if (!EXACT)
+            a.done[p] = q;
+    }
+}
+
+template <int WGS, int MODE, int SPLIT, bool FAR>
+__global__ __launch_bounds__(WGS * SPLIT, 4) void k_batch(BatchArgs a)
+{
+    batch_pack<WGS, MODE, SPLIT, FAR, false>(a, blockIdx.x);
+}
+
+// The packs that k_batch left (none, as a rule: 2 us a launch), of any size.
+constexpr int EXACT_GRID = 256;
+
+template <int MODE>
+__global__ __launch_bounds__(1024, 4) void k_batch_exact(BatchArgs a, int n_packs)
+{
+    bool left = false;
+    for (int p = blockIdx.x + EXACT_GRID * threadIdx.x; p < n_packs; p += EXACT_GRID * 1024)
+        left |= a.done[p] < a.n_steps;
+    if (!__syncthreads_or(left))
+        return;
+    for (int p = blockIdx.x; p < n_packs; p += EXACT_GRID) {
+        if (a.done[p] < a.n_steps)  // uniform
+            batch_pack<1024, MODE, 1, false, true>(a, p);
+        __syncthreads();
     }
 }
 
@@ -3141,6 +3304,8 @@ FilterArgs filter_args(const DevBufs &b, int cur, int cap, int tile, int n_cells
     a.wg_rec = b.wg_rec;
     a.cell_count = b.cell_count;
     a.skin_flag = b.skin_flag;
+    a.fixed = b.fix[cur];
+    a.place = b.place;
     a.rc2 = rc2;
     a.fix = fix;
     a.cap = cap;
@@ -3311,6 +3476,8 @@ void launch_pair_step(const DevBufs &b, int cur, int n, int cap, int tile, const
     u.step_base = step_base;
     u.hi_skin = b.hi_skin;
     u.skin_flag = b.skin_flag;
+    u.place = b.place;
+    u.layer = cur;
     u.step_off = step_off;
     u.check_thr2 = mode == 0 ? check_thr2 : 0.0f;
     u.vel = const_cast<float4 *>(vel);
@@ -3365,6 +3532,8 @@ void launch_step(const DevBufs &b, int cur, int n, int cap, int tile, const Step
     a.cell_of = b.cell_of;
     a.hi_skin = b.hi_skin;
     a.skin_flag = b.skin_flag;
+    a.place = b.place;
+    a.layer = cur;
     a.check_thr2 = mode == 0 ? check_thr2 : 0.0f;
     a.n_wg = workgroups(b, tile);
     a.pin = b.pos[cur];
@@ -3444,6 +3613,9 @@ void launch_batch(const DevBufs &b, int cur, int n_packs, int wg, int cap, const
     a.pulls = b.pulls;
     a.list = b.list16;
     a.list_cnt = b.list_cnt;
+    a.place = b.place;
+    a.moved = b.pack_moved;
+    a.done = b.pack_done;
     a.energy = b.energy;
     a.f_ext = b.f_ext;
     a.fout = b.fout;
@@ -3462,24 +3634,34 @@ void launch_batch(const DevBufs &b, int cur, int n_packs, int wg, int cap, const
     a.rc2 = rc2;
     a.tscale = tscale;
     const dim3 grid(n_packs);
-    auto run = [&](auto W) {
+    auto run = [&](auto W, auto F) {
         constexpr int WGS = decltype(W)::value;
+        constexpr bool FAR = decltype(F)::value;
         if (mode == 1)
-            hipLaunchKernelGGL((k_batch<WGS, 1, 1>), grid, dim3(WGS), 0, s, a);
+            hipLaunchKernelGGL((k_batch<WGS, 1, 1, FAR>), grid, dim3(WGS), 0, s, a);
         else if (mode == 2)
-            hipLaunchKernelGGL((k_batch<WGS, 2, 1>), grid, dim3(WGS), 0, s, a);
+            hipLaunchKernelGGL((k_batch<WGS, 2, 1, FAR>), grid, dim3(WGS), 0, s, a);
         else
-            hipLaunchKernelGGL((k_batch<WGS, 0, 1>), grid, dim3(WGS), 0, s, a);
+            hipLaunchKernelGGL((k_batch<WGS, 0, 1, FAR>), grid, dim3(WGS), 0, s, a);
     };
-    if (mode == 0 && batch_split(n_packs, wg)) {
-        hipLaunchKernelGGL((k_batch<256, 0, 2>), grid, dim3(512), 0, s, a);
-        return;
-    }
-    switch (wg) {
-    case 256: run(std::integral_constant<int, 256>{}); break;
-    case 512: run(std::integral_constant<int, 512>{}); break;
-    default: run(std::integral_constant<int, 1024>{}); break;
-    }
+    auto sized = [&](auto F) {
+        switch (wg) {
+        case 256: run(std::integral_constant<int, 256>{}, F); break;
+        case 512: run(std::integral_constant<int, 512>{}, F); break;
+        default: run(std::integral_constant<int, 1024>{}, F); break;
+        }
+    };
+    if (fix.list_far)
+        sized(std::true_type{});
+    else if (mode == 0 && batch_split(n_packs, wg))
+        hipLaunchKernelGGL((k_batch<256, 0, 2, false>), grid, dim3(512), 0, s, a);
+    else
+        sized(std::false_type{});
+    const dim3 exact(std::min(n_packs, EXACT_GRID));
+    if (mode == 1)
+        hipLaunchKernelGGL(k_batch_exact<1>, exact, dim3(1024), 0, s, a, n_packs);
+    else
+        hipLaunchKernelGGL(k_batch_exact<2>, exact, dim3(1024), 0, s, a, n_packs);
 }
 
 void launch_exchange(const DevBufs &b, int n_rep, int n_groups, double kbt_ref, long long round,
