@@ -86,17 +86,21 @@ __global__ __launch_bounds__(RAMP_WG) void k_ramp(float2 *__restrict__ x, long l
 // 1e3 particles 230 -> 97 -> 83 us, 32e3 230 -> 125 -> 115, 1e5 330 -> 270 ->
 // 260, 1e6 2,030 -> 1,880 -> 1,850.
 constexpr int NOISE_WAVES = 8, NOISE_STEPS = 8;
+// A grid has fewer than 2^32 lanes, and eight serve a particle: more
+// particles than this take several launches.
+constexpr long long NOISE_SLICE = 1LL << 28;
+static_assert(NOISE_SLICE % 64 == 0 && NOISE_SLICE * NOISE_WAVES < 1LL << 32, "lanes of a launch");
 
 template <bool COMP>
-__global__ __launch_bounds__(64 * NOISE_WAVES) void k_ramp_noise(float2 *__restrict__ x, long long m_count,
-                                                                 long long step0, long long n_steps,
-                                                                 RampConsts c)
+__global__ __launch_bounds__(64 * NOISE_WAVES) void k_ramp_noise(float2 *__restrict__ x, long long m0,
+                                                                 long long m_count, long long step0,
+                                                                 long long n_steps, RampConsts c)
 {
     constexpr int S = (NOISE_WAVES - 1) * NOISE_STEPS;  // steps of a chunk
     __shared__ float g[2][S][64];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long m = (long long)blockIdx.x * 64 + lane;
+    const long long m = m0 + (long long)blockIdx.x * 64 + lane;
     const bool adv = w == 0 && m < m_count;
     float hi = 0.0f, lo = 0.0f;
     if (adv) {
@@ -226,7 +230,10 @@ sop_status ramp_launch(const sop_ramp_params *rp, int64_t n_particles, float *x,
     auto run = [&](auto comp) {
         constexpr bool COMP = decltype(comp)::value;
         if (noise)
-            k_ramp_noise<COMP><<<(int)((M + 63) / 64), 64 * NOISE_WAVES, 0, s>>>(xv, M, step0, n_steps, c);
+            for (long long m0 = 0; m0 < M; m0 += NOISE_SLICE) {
+                const long long m = std::min(NOISE_SLICE, M - m0);
+                k_ramp_noise<COMP><<<(int)((m + 63) / 64), 64 * NOISE_WAVES, 0, s>>>(xv, m0, m0 + m, step0, n_steps, c);
+            }
         else
             k_ramp<COMP><<<(int)((M + RAMP_WG - 1) / RAMP_WG), RAMP_WG, 0, s>>>(xv, M, step0, n_steps, c);
     };
