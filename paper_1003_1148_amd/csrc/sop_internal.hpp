@@ -235,8 +235,8 @@ void launch_noise(const DevBufs &b, int cur, int n, const StepConsts &c, long lo
 // workgroups, and the residue of rank r in skin_ord belongs to group r / W of
 // workgroup tile W + r % W.  A residue's partners are dealt to its lanes by
 // their id modulo nl, in ascending order, so which lane sums a partner, and in
-// which order, depends on the list alone; a row that would give one lane more
-// than its share of the capacity and 16 is dealt in turn instead.  A lane's
+// which order, depends on the list alone; a list row that would give one lane
+// more than its share of the capacity and 16 is dealt in turn instead.  A lane's
 // entries (4 * slot, 16 bits) lie four to a chunk of 8 bytes, chunk k of a
 // workgroup's 256 lanes side by side: a wave reads its chunks as one
 // contiguous piece at an address that needs no row length, and a lane filters

@@ -1079,6 +1079,9 @@ __device__ __forceinline__ int ranked(const unsigned short *ord, size_t at, int 
 constexpr int WG_FAR = 1, WG_WIDE = 2;
 constexpr int WG_IDS32 = 4;  // the tile's slot ids do not fit stage16
 
+// Beside a lane's skin entries: its residue's row is dealt in turn.
+constexpr int SKIN_TURN = 0x8000;
+
 // Filters the skin entries of every lane of a workgroup; returns the number
 // of list entries of this lane, and the workgroup's record.  Every lane of a
 // wave gets as many chunks as the wave's longest, padded with the far-away
@@ -1108,7 +1111,9 @@ __device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile
     const int chunks = lane_chunks(a.cap, NL);
     const uint4 *src = a.skin16 + (size_t)wg * (chunks / 2) * 256 + t;
     uint2 *dst = a.list16 + (size_t)wg * chunks * 256 + t;
-    const int len = a.skin_len[wg * 256 + t];
+    const int own = a.skin_len[wg * 256 + t];
+    const bool turn = (own & SKIN_TURN) != 0;
+    const int len = turn ? 0 : own;
     const int np = (len + 7) >> 3;
     // straight-line loads (the first STAGE_MIN slots and TOP_MIN rounds are
     // there for any tile): ids and entries first, then all their positions
@@ -1280,6 +1285,43 @@ __device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile
                 ++p;
             }
         }
+    }
+    if (__builtin_expect(turn, 0)) {
+        // a skin row dealt in turn: each lane walks the residue's whole row, in
+        // ascending order, for what it has of the list: its class, or where one
+        // class is more than a lane holds, in turn.  So also here the list
+        // alone decides which lane sums a partner.
+        const int q = t % NL, cap_lane = 8 * (chunks / 2);
+        int row = own & ~SKIN_TURN;
+#pragma unroll
+        for (int off = 1; off < NL; off <<= 1)
+            row += __shfl_xor(row, off, NL);
+        const unsigned short *sk = reinterpret_cast<const unsigned short *>(src) - 8 * q;
+        auto walk = [&](auto f) {  // f(entry, id) of every partner in the list
+#pragma unroll 1
+            for (int k = 0; k < row; ++k) {
+                const int e = k / NL;
+                const unsigned v = sk[((size_t)(e >> 3) * 256 + k % NL) * 8 + (e & 7)];
+                const int id = st[v >> 2];
+                if (within_cutoff(pi, a.pos[2 * id], a.rc2))
+                    f(v, id);
+            }
+        };
+        int most = 0;
+        walk([&](unsigned, int id) { most += (id & (NL - 1)) == q ? 1 : 0; });
+#pragma unroll
+        for (int off = 1; off < NL; off <<= 1)
+            most = max(most, __shfl_xor(most, off, NL));
+        int rank = 0;
+        walk([&](unsigned v, int id) {
+            if ((most > cap_lane ? rank : id) % NL == q) {
+                at(c9) = (unsigned short)v;
+                c9 += 512u;
+                if (c9 - f9 >= 2048u)
+                    flush();
+            }
+            ++rank;
+        });
     }
     const int m = (int)(c9 >> 9);
     int nk = (m + 3) >> 2;
@@ -1572,8 +1614,10 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
 #pragma unroll
             for (int off = 1; off < NL; off <<= 1)
                 most = max(most, __shfl_xor(most, off, NL));
-            if (most > cap_lane) {
-                // more of one class than a lane holds: the row is dealt in turn
+            const bool turn = most > cap_lane;
+            if (turn) {
+                // more of one class than a lane holds: the row is dealt in
+                // turn, and the filter deals the list anew
                 c = 0;
                 int pos = 0;
                 for (int x = 0; x < words; ++x)
@@ -1581,7 +1625,7 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
                         if (pos % NL == q)
                             put(4u * (unsigned)(32 * x + __ffs(b) - 1));
             }
-            a.skin_len[wg * 256 + t] = (unsigned short)c;
+            a.skin_len[wg * 256 + t] = (unsigned short)(turn ? c | SKIN_TURN : c);
             while (c & 7)
                 put(4u * (unsigned)R::SW);  // the far-away slot
         }
