@@ -365,14 +365,20 @@ StepConsts step_consts(const sop_ctx *c)
     return k;
 }
 
-// Scale of the fixed-point copies: the coarsest power of two
-// that keeps 2.5 times the distance a listed pair can have (r_list, and 16
-// standard deviations of the thermal drift of a list period, eight for each
-// partner) inside half the period of 2^32 units, H.  At r_list = 20 A: k = 25,
-// H 64 A, unit 3e-8 A.  Bonded and native terms, which are steep where the forces cancel,
-// use the copies only while a unit is below 2^-24 of the shortest reference
-// length (the rounding of that length in single precision), the list only
-// while it is below 2e-6 sigma.
+// Scale of the fixed-point copies: the coarsest power of two that keeps 2.5
+// times the distance a listed pair can have (r_list, and 16 standard deviations
+// of the thermal drift of a list period, eight for each partner) inside half
+// the period of 2^32 units, H.  At r_list = 20 A: k = 25, H 64 A, unit 3e-8 A.
+// Bonded and native terms, which are steep where the forces cancel, use the
+// copies only while a unit is at most 2^-26 of the shortest reference length, a
+// quarter of what rounding that length to single precision leaves: L2 force
+// error 5.84e-7 against 5.94e-7 of compensated positions for 1,500 residues at
+// 3.8 A; at twice the unit, as r_list = 24 to 45 A would have, 5.99e-7, at four
+// times 6.46e-7.  Beyond it the plain schedule takes the compensated positions
+// for them (20,000 residues at 30 A 10.7 -> 10.95 us a step), the batched one
+// a finer unit, and the list over the periods from r_list = 0.75 H (48 A) on
+// (200 chains 13.7 -> 18.1 us a step at the same list).  The list uses the
+// copies only while a unit is below 2e-6 sigma.
 // `narrow`: copies relative to a tile's origin wrap at H, and a list partner
 // lies up to r_list further out than the tile's residues, plus what it moves
 // until the next rebuild, for which a margin is left.  At 300 K and the time
@@ -406,7 +412,7 @@ FixDev fix_consts(const sop_ctx *c)
     // batched: bonded and native terms have the copies alone, so the unit
     // follows the shortest reference length where that asks for a finer one
     if (c->schedule == SOP_SCHEDULE_BATCHED)
-        k = std::max(k, std::min(28, 24 - (int)std::floor(std::log2(std::min(std::max(c->min_r0, 1e-9), 1e30)))));
+        k = std::max(k, std::min(k + 8, 26 - (int)std::floor(std::log2(std::min(std::max(c->min_r0, 1e-9), 1e30)))));
     k = std::max(-60, std::min(60, k));
     const double H = std::ldexp(1.0, 31 - k);
     FixDev f{};
@@ -417,8 +423,10 @@ FixDev fix_consts(const sop_ctx *c)
     f.s2 = (float)std::ldexp(1.0, 2 * k);
     f.reach = (float)std::ldexp(1.0, 30 - k);
     f.direct = (float)std::ldexp(1.0, 50 - k);
-    f.list_far = (half > H || f.unit > 2e-6 * c->p.sigma) ? 1 : 0;
-    f.bond_far = f.unit > std::ldexp(c->min_r0, -24) ? 1 : 0;
+    // batched: pairs of r_list, and an eighth of H of movement for either partner
+    const bool wraps = c->schedule == SOP_SCHEDULE_BATCHED ? c->p.r_list > 0.75 * H : half > H;
+    f.list_far = (wraps || f.unit > 2e-6 * c->p.sigma) ? 1 : 0;
+    f.bond_far = f.unit > std::ldexp(c->min_r0, -26) ? 1 : 0;
     const double share = 8.5 * noise * steps, periods = 256 * H;  // 128 of them
     double move, grain = 1.0;
     if (c->schedule == SOP_SCHEDULE_BATCHED) {
