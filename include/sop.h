@@ -351,9 +351,9 @@ sop_status sop_get_list_stats(sop_ctx *ctx, int64_t *rebuilds, int64_t *skin_bui
  * skin rows.
  * The step launches reuse the current list, so the coordinates and the list
  * are restored afterwards (the step counter does not move).  Batched schedule:
- * n_steps steps in persistent launches, each timed with events and waited
- * for; ms_out[0] = mean duration of one launch, ms_out[1] = 0, ms_out[2] =
- * steps per launch (these steps advance the state).
+ * n_steps steps in the launches that sop_step makes, each timed with events
+ * and waited for; ms_out[0] = mean duration of ms_out[2] steps, ms_out[1] = 0,
+ * ms_out[2] = steps per launch (these steps advance the state).
  */
 sop_status sop_step_timed(sop_ctx *ctx, int64_t n_steps, double *ms_out);
 

@@ -1906,7 +1906,9 @@ sop_status sop_step_timed(sop_ctx *c, int64_t n_steps, double *ms_out)
         long long cnt = 0, q = 0;
         sop_status out = SOP_OK;
         while (q < n_steps) {
-            const long long k = std::min<long long>(c->batch_steps, n_steps - q);
+            // the launches that sop_step makes; the last counts only if whole
+            const long long whole = std::min<long long>(c->batch_steps, record_span(c, c->step));
+            const long long k = std::min(whole, (long long)(n_steps - q));
             const long long rec = last_record(c, c->step, k);
             (void)hipEventRecord(ev[0], c->stream);
             batch_launch(c, c->stream, (int)k, c->list_valid ? 0 : 1, 0, nullptr, c->step, rec >= 0);
@@ -1917,9 +1919,9 @@ sop_status sop_step_timed(sop_ctx *c, int64_t n_steps, double *ms_out)
                 break;
             }
             float ms = 0.0f;
-            if (k == c->batch_steps && hipEventElapsedTime(&ms, ev[0], ev[1]) == hipSuccess) {
+            if (k == whole && hipEventElapsedTime(&ms, ev[0], ev[1]) == hipSuccess) {
                 sum += ms;
-                ++cnt;
+                cnt += k;
             }
             if (rec >= 0)
                 c->energy_step = rec;
@@ -1930,7 +1932,7 @@ sop_status sop_step_timed(sop_ctx *c, int64_t n_steps, double *ms_out)
         }
         for (auto &e : ev)
             (void)hipEventDestroy(e);
-        ms_out[0] = cnt ? sum / (double)cnt : 0.0;
+        ms_out[0] = cnt ? sum / (double)cnt * (double)c->batch_steps : 0.0;
         ms_out[1] = 0.0;
         ms_out[2] = (double)c->batch_steps;
         if (out == SOP_OK)
