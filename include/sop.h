@@ -196,8 +196,9 @@ sop_status sop_get_tile(const sop_ctx *ctx, int32_t *tile);
  * while that many steps remain from a period start.  Graphs are used only when
  * the energy interval is 0 or a multiple of k*list_every, and then start only
  * on multiples of k*list_every, so every record step is a graph's first step.
- * After 64 replays a context also makes a graph of at least ten list periods
- * and replays that where the steps of a call and the next record allow.
+ * After 64 replays a context also makes a graph of up to ten list periods (or
+ * 128 steps) and replays that where the steps of a call and the next record
+ * allow.
  * Changing k drops the graphs already captured.  Default: 1.
  */
 sop_status sop_set_graph_steps(sop_ctx *ctx, int32_t k);
