@@ -405,8 +405,14 @@ constexpr double NARROW_MAX = 40.0;
 
 FixDev fix_consts(const sop_ctx *c)
 {
-    const double noise = std::sqrt(2.0 * c->p.kBT * c->p.h / c->p.zeta), steps = c->p.list_every;
-    const double drift = 16.0 * noise * std::sqrt(steps);
+    const double steps = c->p.list_every;
+    double noise = std::sqrt(2.0 * c->p.kBT * c->p.h / c->p.zeta), drift = 16.0 * noise * std::sqrt(steps);
+    if (c->integrator == SOP_INTEGRATOR_UNDERDAMPED) {
+        // no further than at the thermal velocity (low friction)
+        const double flight = std::sqrt(c->p.kBT / c->mass) * c->p.h;
+        noise = std::min(noise, flight);
+        drift = std::min(drift, 16.0 * flight * steps);
+    }
     const double half = 2.5 * (c->p.r_list + drift);
     int k = 31 - (int)std::ceil(std::log2(std::min(std::max(half, 1e-9), 1e30)));
     // batched: bonded and native terms have the copies alone, so the unit
@@ -1224,10 +1230,18 @@ sop_status sop_set_integrator(sop_ctx *c, int32_t kind, double mass)
         return fail(c, SOP_E_ARG, "the mass must be positive and finite");
     if (kind == SOP_INTEGRATOR_UNDERDAMPED && c->schedule != SOP_SCHEDULE_PLAIN)
         return fail(c, SOP_E_STATE, "the underdamped integrator runs on the plain schedule");
+    const double scale = fix_consts(c).scale;
     c->integrator = kind;
     if (kind == SOP_INTEGRATOR_UNDERDAMPED)
         c->mass = mass;
     c->ud_half = true;
+    if (c->bound && c->coords && c->schedule == SOP_SCHEDULE_PLAIN && fix_consts(c).scale != scale) {
+        // the copies are in another unit: binned (and copied) anew before the
+        // next rebuild, and not read until then
+        c->binned_at = -1;
+        launch_distrust_copies(c->b, c->cur, c->stream);
+        HIP_TRY(c, hipGetLastError());
+    }
     destroy_graphs(c);  // the integrator's constants are kernel arguments
     return SOP_OK;
 }

@@ -194,6 +194,9 @@ void launch_rebuild(const DevBufs &b, int cur, int n_res, int cap, int tile, con
                     int list_every, bool binned, bool filter = true);
 // Sets the skin flag so that the next rebuild rebuilds the skin.
 void launch_force_skin(const DevBufs &b, hipStream_t s);
+// As if a residue had moved too far: until the next rebuild the steps take the
+// compensated positions.
+void launch_distrust_copies(const DevBufs &b, int cur, hipStream_t s);
 // Clears the cells, bins every residue at its current position and writes
 // the fixed-point copies of the layer.
 void launch_bin_all(const DevBufs &b, int cur, int n_res, const GridDev &g, const FixDev &fix, hipStream_t s);

@@ -3477,6 +3477,11 @@ void launch_force_skin(const DevBufs &b, hipStream_t s)
     hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(64), 0, s, b.skin_flag, 1u);
 }
 
+void launch_distrust_copies(const DevBufs &b, int cur, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(64), 0, s, b.err + MOVED + cur, 1u);
+}
+
 void launch_pair_step(const DevBufs &b, int cur, int n, int cap, int tile, const StepConsts &c,
                       const FixDev &fix, const TipDev &tip, int has_pull, bool energy, int mode, const long long *step_base,
                       long long step_off, float check_thr2, hipStream_t s, const float4 *vel,
