@@ -196,8 +196,10 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
     d.skin_len = (unsigned short *)take(wg_elems * 256 * sizeof(unsigned short));
     d.llen = (unsigned short *)take(wg_elems * 256 * sizeof(unsigned short));
     d.grho = (unsigned char *)take(wg_elems * 256);
-    d.wg_rec = (WgRec *)take((wg_elems + 1) * sizeof(WgRec)) + 1;
-    d.err = (unsigned *)d.wg_rec - MOVED - 2;
+    if (char *rec = take((wg_elems + 1) * sizeof(WgRec))) {
+        d.wg_rec = (WgRec *)rec + 1;
+        d.err = (unsigned *)d.wg_rec - MOVED - 2;
+    }
     d.tile_top = (int4 *)take(n_tiles_max * sizeof(int4));
     d.ltop = (uint2 *)take(ltop_elems * sizeof(uint2));
     for (auto &f : d.fix)
