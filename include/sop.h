@@ -92,7 +92,9 @@ typedef struct sop_ctx sop_ctx;
 sop_status sop_create(const sop_params *params, void *hip_stream, sop_ctx **out);
 
 /* Destroy a context.  Frees host memory and library-owned streams and
- * graphs; the caller's workspace is not freed. */
+ * graphs; the caller's workspace is not freed.  A bound context owns up to
+ * 4 MiB of page-locked host memory that results and coordinates pass through;
+ * freeing it may wait for work of other streams. */
 sop_status sop_destroy(sop_ctx *ctx);
 
 /* ---- topology (Algorithm 2's P_p / PairsMap, built once on the host) ------ */

@@ -172,7 +172,7 @@ size_t layout(const sop_ctx *c, char *base, DevBufs *b)
             chunk_elems = std::max(chunk_elems, wgs * 1024 * (size_t)lane_chunks(c->cap, nl));
             ltop_elems = std::max(ltop_elems, wgs * 256 * (size_t)top_rounds(c->max_bonds, c->max_natives, nl));
             wg_elems = std::max(wg_elems, wgs);
-            stage_elems = std::max(stage_elems, nt * (size_t)stage_max_host((int)T));
+            stage_elems = std::max(stage_elems, nt * (size_t)STAGE_MAX);
             n_tiles_max = std::max(n_tiles_max, nt);
             tf_elems[k] = nt + 1;
         }
@@ -1698,7 +1698,7 @@ sop_status sop_get_pairlist(sop_ctx *c, int64_t cap, int32_t *ij, int64_t *n_pai
         }
     } else {
         // rows hold slots of their tile, in lane order; the tile's stage maps slots to ids
-        const int T = c->tile, SM = stage_max_host(T);
+        const int T = c->tile, SM = STAGE_MAX;
         const auto &tl = c->tiles[tile_index(T)];
         const int n_tiles = (int)tl.size() - 1, nl = lanes_for(T, n_tiles), W = T * nl / 256;
         const int chunks = lane_chunks(c->cap, nl);

@@ -60,9 +60,11 @@ struct GridDev {
 constexpr int CELL_CAP = 256;
 // Bonded plus native partners per residue (larger is rejected at load).
 constexpr int TOPO_CAP = 64;
-// Largest staging set of a tile of the plain schedule (slots are 16-bit; the
-// kernels hold some 1,800 to 3,000 of them in LDS at once).
+// Largest staging set of a tile of the plain schedule (the kernels hold some
+// 1,800 to 3,000 of its slots in LDS at once), of any tile size.  The rows
+// hold four times the slot in 16 bits.
 constexpr int STAGE_MAX = 4096;
+static_assert(4 * STAGE_MAX <= 0xffff, "16-bit entries");
 
 // Fixed-point copies of the positions: whole numbers of units of 2^-k, modulo
 // 2^32 units.  `direct`: 2^50 units.  `reach` is a quarter of the period, in
@@ -135,7 +137,7 @@ struct DevBufs {
     unsigned long long *re_stats;  // batched, replica exchange: {accepted, attempted} per ladder pair
     float4 *facc;            // plain, pair-based forces: per-residue force accumulator
     double4 *eacc;           // plain, pair-based forces: per-residue energies of the pairs in its row
-    int *stage;       // plain: per tile, global ids of its slots (stage_max per tile)
+    int *stage;       // plain: per tile, global ids of its slots (STAGE_MAX per tile)
     int *stage_raw;   // the same in the search's order
     unsigned short *stage16;  // plain: the same less the tile's lowest id (tile_top), where all
                               // differences fit 16 bits: half the bytes of every step's ids
@@ -274,8 +276,6 @@ inline int top_rounds(int max_bonds, int max_natives, int nl)
 }
 SOP_HD size_t top_index(int wg, int round, int lane, int rounds) { return ((size_t)wg * rounds + round) * 256 + lane; }
 
-// The slots a tile of `tile` residues can stage.
-inline int stage_max_host(int) { return 4096; }
 inline int tile_index(int tile) { return tile == 64 ? 0 : (tile == 128 ? 1 : 2); }
 
 }  // namespace sop

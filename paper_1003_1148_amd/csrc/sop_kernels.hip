@@ -501,11 +501,9 @@ __device__ __forceinline__ void draw_noise(float (&g)[3], const float4 &hi, long
 
 // ---------------------------------------------------------------------------
 // Plain schedule, tile staging: at each skin search, the list partners of a
-// tile of consecutive residues become a sorted set of at most stage_max slots,
+// tile of consecutive residues become a sorted set of at most STAGE_MAX slots,
 // and rows are rewritten as 16-bit slots into that set.
 // ---------------------------------------------------------------------------
-template <int TILE>
-constexpr int stage_max() { return 4096; }
 // Slots held in LDS at once by the kernels that read the staging set (12
 // bytes each: 21 KiB leave room for five workgroups a CU beside the rings of
 // the period's first step); a tile with more slots is taken in windows of
@@ -613,7 +611,7 @@ template <int TILE, bool MULTI, int NT>
 __global__ __launch_bounds__(NT, NT > 256 ? 4 : (TILE == 64 ? 5 : 2)) void k_tile_build(BuildArgs a)
 {
     constexpr int NLB = NT / TILE;
-    constexpr int SM = stage_max<TILE>();
+    constexpr int SM = STAGE_MAX;
     constexpr int CM = cand_win<TILE>();
     constexpr int NW = CM / 32;
     constexpr int CELLS_MAX = cells_max<TILE>();
@@ -1096,12 +1094,11 @@ constexpr int SKIN_TURN = 0x8000;
 // filter alone took (us, with two early exits before it) 71 -> 62 at 250,000
 // residues, 27 -> 24 at 75,000, 13.0 -> 11.5 at 4,801 at protein density.
 template <int TILE, int NL>
-__device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile, int t, int first, int tcnt, bool in,
-                                           int rho, unsigned char *region, unsigned short *ring, float *bb,
-                                           WgRec &wr)
+__device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile, int t, int first, int tcnt, int rho,
+                                           unsigned char *region, unsigned short *ring, float *bb, WgRec &wr)
 {
     using R = Rows<TILE, NL>;
-    constexpr int SM = stage_max<TILE>();
+    constexpr int SM = STAGE_MAX;
     constexpr int SW = R::SW, XS = R::XS;
     const int i = first + rho;
     float *hx = reinterpret_cast<float *>(region);
@@ -1378,7 +1375,7 @@ __global__ __launch_bounds__(256, NL == 1 ? 2 : 5) void k_filter(FilterArgs a)
     if (!a.fix.by_step && in && t % NL == 0)
         a.place[first + rho] = fix_place(a.fixed[first + rho]);
     WgRec wr;
-    filter_rows<TILE, NL>(a, wg, tile, t, first, tcnt, in, rho, region, ring, bb, wr);
+    filter_rows<TILE, NL>(a, wg, tile, t, first, tcnt, rho, region, ring, bb, wr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1413,7 +1410,7 @@ __global__ __launch_bounds__(256) void k_canon(CanonArgs a)
 {
     using R = Rows<TILE, NL>;
     constexpr int RW = R::RW, W = R::W;
-    constexpr int SM = stage_max<TILE>();
+    constexpr int SM = STAGE_MAX;
     constexpr int MW = SM / 32;     // mask words per row, at most
     constexpr int BW = 2048;        // bitmap words: ids spanning up to 65,536 values
     // the ranks (bitmap and word prefixes, or the ids) and the masks use one
@@ -1744,7 +1741,7 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
 {
     using R = Rows<TILE, NL>;
     constexpr int RW = R::RW, W = R::W;
-    constexpr int SM = stage_max<TILE>();
+    constexpr int SM = STAGE_MAX;
     constexpr int SW = R::SW, XS = R::XS;
     constexpr int PER = 4;           // staging slots per lane loaded together
     constexpr int EPI = 256 - RW;    // first lane of the update lanes
@@ -1798,7 +1795,7 @@ __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_st
         f.wg_rec = const_cast<WgRec *>(a.wg_rec);
         f.fix = a.fix;
         f.top_rounds = a.top_rounds;
-        filter_rows<TILE, NL>(f, wg, tile, t, first, tcnt, in, rho, region, ring, bb, wr);
+        filter_rows<TILE, NL>(f, wg, tile, t, first, tcnt, rho, region, ring, bb, wr);
     } else {
         rho = a.grho[wg * RW + g];
     }
@@ -2197,7 +2194,7 @@ template <int TILE, int NL, bool ENERGY>
 __global__ __launch_bounds__(256) void k_pair_forces(PairArgs a)
 {
     using R = Rows<TILE, NL>;
-    constexpr int SM = stage_max<TILE>();
+    constexpr int SM = STAGE_MAX;
     constexpr int SW = R::SW;
     __shared__ float acc_s[3][SW];  // slots beyond SW take device-wide atomics
     const int wg = blockIdx.x, t = threadIdx.x;
