@@ -1382,9 +1382,10 @@ __global__ __launch_bounds__(256, NL == 1 ? 2 : 5) void k_filter(FilterArgs a)
 // Canonical order after a skin search: a tile's slots are renumbered in the
 // order of their residues' global ids, and every skin row is dealt to its
 // residue's lanes by partner id, in ascending order, whatever the cell grid.
-// The list rows the filter derives keep that order, so the order in which a
-// residue's pair terms are summed depends on its list alone, not on when or
-// with which skin the last search ran.
+// The list rows the filter derives keep that order (a row that has to be dealt
+// in turn it deals anew), so the order in which a residue's pair terms are
+// summed depends on its list alone, not on when or with which skin the last
+// search ran.
 // ---------------------------------------------------------------------------
 struct CanonArgs {
     const int *tile_first;
@@ -1732,10 +1733,12 @@ __device__ __forceinline__ float lane_xor(float v, int off)
 // the list rows are filtered from the skin rows first (filter_rows): the same
 // rows, sums and bits as a filter kernel followed by a plain step.
 // Against rows by residue, 32-byte positions rounded to the tile's frame by
-// every reader and partners gathered through the rows (us a launch): 250,000
-// residues 40.7 -> 34.4, 75,000 13.5 -> 13.6, 20,000 8.2 -> 6.5, 4,801 at
-// protein density 22.2 -> 8.3, 1,000 10.3 -> 4.6, 56 4.6 -> 3.9; the first
-// step of a period at 75,000 38.1 -> 34.
+// every reader and partners gathered through the rows (us a launch in traces of
+// the calls of perf/cases.py, last steps of a period among them; the movement
+// check takes up to 0.5 of the second): 250,000 residues 41.9 -> 36.2, a shell of
+// 75,000 with a tip 13.9 -> 13.9, 20,000 underdamped 8.6 -> 7.4, 4,801 at protein
+// density 22.3 -> 9.1, 1,000 10.8 -> 5.1, 56 4.5 -> 4.3; the first step of a
+// period, with its filter, 106 -> 97, 38 -> 31, 20 -> 17, 48 -> 18, 22 -> 11, 9.3 -> 9.2.
 template <int TILE, int NL, bool ENERGY, int MODE, bool FIRST>
 __global__ __launch_bounds__(256, ENERGY ? 2 : (NL <= 2 ? 3 : 5)) void k_tile_step(TileArgs a)
 {
@@ -2516,6 +2519,8 @@ __device__ __forceinline__ void traj_sums(double *red, int t, double (&v)[3], in
 // chains of the exchange ladder 15.4 -> 12.3.  Two partial sums, slots of
 // equal row length in slot order, and the fewest entries in the wave with the
 // longest rows: 54.5, 10.3 and 10.5; two lanes a residue (batch_split): 9.7.
+// With the movement check, the far list in a kernel of its own and four reads
+// in flight: 57.7, 10.5 and 9.7.
 constexpr int NBUCKET = 64;
 
 // FAR: the list's differences are taken over the periods (FixDev::list_far), in
