@@ -377,10 +377,10 @@ StepConsts step_consts(const sop_ctx *c)
 // error 5.84e-7 against 5.94e-7 of compensated positions for 1,500 residues at
 // 3.8 A; at twice the unit, as r_list = 24 to 45 A would have, 5.99e-7, at four
 // times 6.46e-7.  Beyond it the plain schedule takes the compensated positions
-// for them (20,000 residues at 30 A 10.7 -> 10.95 us a step), the batched one
-// a finer unit, and the list over the periods from r_list = 0.75 H (48 A) on
-// (200 chains 13.7 -> 18.1 us a step at the same list).  The list uses the
-// copies only while a unit is below 2e-6 sigma.
+// for them (20,000 residues at 30 A 10.4 -> 10.95 us a step, the movement check
+// in the second), the batched one a finer unit, and the list over the periods
+// from r_list = 0.75 H (48 A) on (200 chains 13.7 -> 18.1 us a step at the same
+// list).  The list uses the copies only while a unit is below 2e-6 sigma.
 // `narrow`: copies relative to a tile's origin wrap at H, and a list partner
 // lies up to r_list further out than the tile's residues, plus what it moves
 // until the next rebuild, for which a margin is left.  At 300 K and the time
@@ -395,14 +395,13 @@ StepConsts step_consts(const sop_ctx *c)
 // comparison a step, for list periods up to some 100 steps (H / 8).  Longer ones
 // compare every residue with its place at the rebuild, to 10 bits an axis
 // (`move`, from below; a step of at most `jump`, four times it, cannot go
-// round).  us a step
-// kernel without a check, by step, by place: 56 residues 4.0, 4.1, 4.2; 4,801
-// 8.4, 8.8, 8.9; 75,000 13.5, 13.6, 13.9; 250,000 35.2, 35.7, 36.3.
-// Batched: H / 8, as a launch within a list period takes the reach of bonded and
-// native pairs anew; 128 periods where differences are taken over the periods,
-// of which the copies hold 1,024, and a trajectory may span 256.  500 steps of
-// 200 chains 6.04 -> 6.27 ms with the check and the launches behind (k_batch_exact),
-// of 4,096 31.6 -> 31.9.
+// round).  us a step kernel without a check, by step, by place: 56 residues 4.0,
+// 4.1, 4.2; 4,801 8.4, 8.8, 8.9; 75,000 13.5, 13.6, 13.9; 250,000 35.2, 35.7,
+// 36.3.  Batched: H / 8, as a launch within a list period takes the reach of
+// bonded and native pairs anew; 128 periods where differences are taken over
+// the periods, of which the copies hold 1,024, and a trajectory may span 256.
+// 500 steps of 200 chains 6.04 -> 6.27 ms with the check and the launches
+// behind (k_batch_exact), of 4,096 31.6 -> 31.9.
 constexpr double NARROW_MAX = 40.0;
 
 FixDev fix_consts(const sop_ctx *c)
@@ -444,7 +443,9 @@ FixDev fix_consts(const sop_ctx *c)
     } else {
         f.by_step = share <= H / 8 ? 1 : 0;
         f.narrow = (float)std::min(NARROW_MAX, H - c->p.r_list - std::max({drift, H / 16, f.by_step ? share : 0.0}));
-        move = f.list_far ? H / 4 : std::min(H / 4, H - f.narrow - c->p.r_list);
+        // less the low parts, which neither the tile's box nor the list has
+        // (up to |x| = 2^14 H, some 1e6 A)
+        move = f.list_far ? H / 4 : std::min(H / 4, H - f.narrow - c->p.r_list - H / 512);
     }
     f.move = (unsigned)(move * f.scale * grain) - (1u << 22);
     f.jump = (float)(f.by_step ? move / steps : 4 * move);

@@ -1197,7 +1197,7 @@ __device__ __forceinline__ int filter_rows(const FilterArgs &a, int wg, int tile
                 hi = fmaxf(hi, bb[6 * w + 3 + ax]);
             }
             o[ax] = 0.5f * lo + 0.5f * hi;
-            half = fmaxf(half, hi - o[ax]);
+            half = fmaxf(half, fmaxf(hi - o[ax], o[ax] - lo));
         }
         if (!(half < a.fix.narrow))
             flags |= WG_WIDE;
